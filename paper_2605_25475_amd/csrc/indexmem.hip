@@ -13,6 +13,7 @@
 #include <mutex>
 
 #include "im_kernels.h"
+#include "im_score.h"
 #include "im_decode.h"
 
 struct im_handle {
@@ -22,15 +23,15 @@ struct im_handle {
   int max_live;
   bool ws_ready;
   // workspace layout (byte offsets)
-  size_t off_status, off_qy, off_alpha, off_mem, off_attn, off_dpart, off_dcand, off_dqm, off_spart, off_xk, off_hspart, total;
+  size_t off_status, off_qy, off_alpha, off_mem, off_attn, off_dpart, off_dcand, off_dqm, off_xk, off_hspart, total;
+  size_t off_qf, off_al16, off_qblk, off_recu, off_reci, off_nlist, off_list;   // scores of many queries
   int mem_split, attn_chunks, dec_splits;
+  size_t rec_keys;   // (group, key) records of a scan that the workspace holds
   // optional kernel timing (im_profile_start / im_profile_stop)
   hipEvent_t* prof_ev;
   int prof_max, prof_n, prof_span;
   char err[256];
 };
-
-#define IM_SCORE_GROUPS 8   // query groups of a scoring launch over a short cache
 
 // Scratch of the entry point that allocates nothing (im_decode_attn_with_readout_static): a status
 // word in the first 256 bytes, then the attention partials.  Every GPU the library runs on holds
@@ -91,6 +92,19 @@ const char* config_problem(const im_config* c, int* code) {
   return nullptr;
 }
 
+size_t score_block_bytes(const im_config* c) {
+  if (c->head_shared) return c->n_idx_heads <= 8 ? ScoreBlock<IM_DI_SHARED, 8>::BYTES : ScoreBlock<IM_DI_SHARED, 16>::BYTES;
+  return c->n_idx_heads <= 8 ? ScoreBlock<IM_DI, 8>::BYTES : ScoreBlock<IM_DI, 16>::BYTES;
+}
+
+// workgroups a scan aims at: with query groups it has at most this many (rounded up by one group), and a
+// workgroup covers at most 256 keys, which bounds its records
+#define IM_SCORE_WGS 2048
+size_t score_rec_keys(size_t sets, size_t capacity) {
+  const size_t all = IM_SCORE_GROUPS * sets * capacity, few = (size_t)IM_SCORE_WGS * 256 + sets * capacity;
+  return all < few ? all : few;
+}
+
 void layout(const im_config* c, im_handle* h) {
   const size_t B = c->batch, Hi = c->n_idx_heads, units = (size_t)c->batch * c->n_kv_heads;
   h->mem_split = (c->capacity + 1023) / 1024;
@@ -108,7 +122,16 @@ void layout(const im_config* c, im_handle* h) {
   h->off_dpart = off;  off = align256(off + units * h->dec_splits * DEC_GMAX * DEC_REC * sizeof(float));  // upper bound: G <= 8
   h->off_dcand = off;  off = align256(off + units * h->dec_splits * DEC_CAND * sizeof(uint32_t));
   h->off_dqm = off;    off = align256(off + units * DEC_GMAX * DEC_QM * sizeof(float));
-  h->off_spart = off;  off = align256(off + (size_t)IM_SCORE_GROUPS * units * c->capacity * sizeof(float));
+  // scores of many queries: normalised features, gates, operand blocks of 16 queries, the scan's records, listed keys
+  const size_t rows = B * c->max_queries, sets = c->head_shared ? B : units, qblk = (c->max_queries + 15) / 16;
+  h->off_qf = off;     off = align256(off + rows * Hi * c->idx_dim * sizeof(float));
+  h->off_al16 = off;   off = align256(off + rows * 16 * sizeof(float));
+  h->off_qblk = off;   off = align256(off + B * qblk * score_block_bytes(c));
+  h->rec_keys = score_rec_keys(sets, c->capacity);
+  h->off_recu = off;   off = align256(off + h->rec_keys * 4 * sizeof(float2));
+  h->off_reci = off;   off = align256(off + h->rec_keys * 4 * sizeof(int32_t));
+  h->off_nlist = off;  off = align256(off + B * sizeof(int32_t));
+  h->off_list = off;   off = align256(off + sets * c->capacity * sizeof(int2));
   // head_shared: U_k X of the rows of one append, fp64
   h->off_xk = off;     off = align256(off + (c->head_shared ? B * c->capacity * IM_DI_SHARED * sizeof(double) : 0));
   h->off_hspart = off; off = align256(off + (c->head_shared ? B * HS_NSC * sizeof(uint4) : 0));
@@ -179,6 +202,48 @@ void gemm_nt(hipStream_t s, const bf16_t* A, const bf16_t* B, double* Cm, int M,
   } else {
     k_gemm_nt_mfma<2, 2><<<dim3((N + 63) / 64, (M + 63) / 64), 256, 0, s>>>(A, B, Cm, M, N, Kd);
   }
+}
+
+// the scores of n_q >= H_idx queries from their raw projections in the workspace
+template <int DI, int HM>
+void score_many(im_handle* h, const im_state* st, const bf16_t* norm_q_w, const int32_t* q_pos, int n_q,
+                double alpha_denom, float* scores, hipStream_t s) {
+  const im_config& c = h->cfg;
+  const int units = n_sets(c), per_b = units / c.batch, live = h->max_live, nblk = (n_q + 15) / 16;
+  char* ws = h->ws;
+  float* qf = (float*)(ws + h->off_qf);
+  float* al16 = (float*)(ws + h->off_al16);
+  char* blocks = ws + h->off_qblk;
+  float2* rec_u = (float2*)(ws + h->off_recu);
+  int32_t* rec_i = (int32_t*)(ws + h->off_reci);
+  int32_t* n_listed = (int32_t*)(ws + h->off_nlist);
+  int2* listed = (int2*)(ws + h->off_list);
+  const bf16_t* Kidx = (const bf16_t*)st->Kidx;
+  k_score_features<DI, HM><<<dim3(nblk, c.batch), 256, 0, s>>>((const double*)(ws + h->off_qy),
+      (const double*)(ws + h->off_alpha), q_pos, norm_q_w, c.rms_eps, alpha_denom, n_q, c.n_idx_heads, qf, al16, blocks,
+      n_listed);
+  // a scan over a short cache has few (256-key tile, unit) workgroups: its query blocks then go in up to
+  // IM_SCORE_GROUPS groups with workgroups of their own; a very short one also drops to 16 keys per wave
+  const long long tiles4 = (long long)((live + 255) / 256) * units;
+  const bool small = tiles4 * IM_SCORE_GROUPS < 1024;
+  const int tiles = small ? (live + 63) / 64 : (live + 255) / 256;
+  int groups = (int)((IM_SCORE_WGS + (long long)tiles * units - 1) / ((long long)tiles * units));
+  if (groups > IM_SCORE_GROUPS) groups = IM_SCORE_GROUPS;
+  if (groups > nblk) groups = nblk;
+  const int per_group = (nblk + groups - 1) / groups;
+  groups = (nblk + per_group - 1) / per_group;
+  const dim3 grid(tiles * units, groups);
+  if (small)
+    k_score_scan<DI, HM, 1><<<grid, 256, 0, s>>>(Kidx, st->pos, st->len, st->n_projected, blocks, q_pos, n_q, per_b,
+                                                 c.capacity, c.n_idx_heads, live, units, per_group, live, rec_u, rec_i);
+  else
+    k_score_scan<DI, HM, 4><<<grid, 256, 0, s>>>(Kidx, st->pos, st->len, st->n_projected, blocks, q_pos, n_q, per_b,
+                                                 c.capacity, c.n_idx_heads, live, units, per_group, live, rec_u, rec_i);
+  k_score_exact<DI, HM><<<dim3((live + 63) / 64, units), 256, 0, s>>>(
+      Kidx, st->pos, st->len, blocks, qf, al16, q_pos, n_q, per_b, c.capacity, c.n_idx_heads, live, groups, live, rec_u,
+      rec_i, scores, n_listed, listed);
+  k_score_listed<DI, HM><<<512, 256, 0, s>>>(Kidx, st->pos, blocks, qf, al16, c.batch, n_q, per_b, c.capacity,
+                                             c.n_idx_heads, scores, n_listed, listed);
 }
 
 }  // namespace
@@ -369,20 +434,14 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
   double* al = (double*)(h->ws + h->off_alpha);
 
   const int M = c.batch * n_q, Nq = c.n_idx_heads * di, Kq = c.n_q_heads * IM_D;
-  const int rows = M * c.n_idx_heads;
   const double alpha_denom = sqrt((double)(c.n_idx_heads * di));
-  // fewer queries than indexer heads (a decode step): the heads of a query are the scoring product's columns
-  const bool few = n_q < c.n_idx_heads && c.n_idx_heads <= 16;
   if (M <= 32) {
-    // a decode-size call: the key projection of the new rows and both query-side products in one launch,
-    // the QK-Norm and the gate scaling in another
+    // a decode-size call: the key projection of the new rows and both query-side products in one launch
     const int n_proj = c.head_shared ? 0 : units;
     k_query_side_few<<<n_proj * IM_PROJ_WGS + (Nq + 1) / 2 + (c.n_idx_heads + 1) / 2, 256, 0, s>>>(
         (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, Nq, Kq, (const bf16_t*)x_gate, (const bf16_t*)p->G, al,
         c.n_idx_heads, c.gate_in_dim, M, n_proj, (const bf16_t*)st->K, (bf16_t*)st->Kidx, st->len, st->n_projected,
         (const bf16_t*)p->Uk, (const bf16_t*)p->norm_k_w, c.capacity, h->max_live, c.rms_eps, status_ptr(h));
-    k_qnorm_alpha<<<(rows + 3) / 4 + (rows + 255) / 256, 256, 0, s>>>(qy, rows, di, (const bf16_t*)p->norm_q_w,
-                                                                     c.rms_eps, al, rows, alpha_denom);
   } else {
     if (!c.head_shared)
       k_project_keys<<<dim3((h->max_live + 63) / 64, units), 256, 0, s>>>(
@@ -390,10 +449,12 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
           (const bf16_t*)p->norm_k_w, c.capacity, h->max_live, c.rms_eps, status_ptr(h));
     gemm_nt(s, (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M, Nq, Kq);
     gemm_nt(s, (const bf16_t*)x_gate, (const bf16_t*)p->G, al, M, c.n_idx_heads, c.gate_in_dim);
-    k_qnorm<<<(rows + 3) / 4, 256, 0, s>>>(qy, rows, di, (const bf16_t*)p->norm_q_w, c.rms_eps);
-    k_alpha_scale<<<(rows + 255) / 256, 256, 0, s>>>(al, rows, alpha_denom);
   }
-  if (few) {
+  // fewer queries than indexer heads (a decode step): the heads of a query are the scoring product's columns
+  if (n_q < c.n_idx_heads) {
+    const int rows = M * c.n_idx_heads;
+    k_qnorm_alpha<<<(rows + 3) / 4 + (rows + 255) / 256, 256, 0, s>>>(qy, rows, di, (const bf16_t*)p->norm_q_w,
+                                                                     c.rms_eps, al, rows, alpha_denom);
     const dim3 grid((h->max_live + 63) / 64, units);
     if (c.head_shared)
       k_score_few<IM_DI_SHARED><<<grid, 256, 0, s>>>((const bf16_t*)st->Kidx, st->pos, st->len, st->n_projected, qy, al,
@@ -405,33 +466,14 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
                                               c.n_idx_heads, h->max_live, scores_out);
     return launch_check(h, "im_index_score");
   }
-  // a launch over a short cache has few (256-key tile, unit) workgroups: its queries then go in up
-  // to IM_SCORE_GROUPS groups with workgroups of their own (partial maxima in the workspace,
-  // folded by k_score_max); a very short one also drops to 16 keys per wave
-  const long long tile_wgs = (long long)((h->max_live + 255) / 256) * units;
-  const bool small = tile_wgs * IM_SCORE_GROUPS < 1024;
-  int groups = 1, q_per_group = n_q;
-  if (tile_wgs < 1024 && n_q >= 32) {
-    // (aiming at 2048 workgroups, 8 per CU: measured against 1024 at 256 and 288 tile workgroups, the
-    // scoring launch is 12 % and 6 % shorter)
-    const int want = (int)((2048 + tile_wgs - 1) / tile_wgs), most = (n_q + 15) / 16;
-    groups = want < most ? want : most;
-    if (groups > IM_SCORE_GROUPS) groups = IM_SCORE_GROUPS;
-    q_per_group = ((n_q + groups - 1) / groups + 15) & ~15;
-    groups = (n_q + q_per_group - 1) / q_per_group;
+  const bf16_t* nqw = (const bf16_t*)p->norm_q_w;
+  if (c.head_shared) {
+    if (c.n_idx_heads <= 8) score_many<IM_DI_SHARED, 8>(h, st, nqw, q_pos, n_q, alpha_denom, scores_out, s);
+    else score_many<IM_DI_SHARED, 16>(h, st, nqw, q_pos, n_q, alpha_denom, scores_out, s);
+  } else {
+    if (c.n_idx_heads <= 8) score_many<IM_DI, 8>(h, st, nqw, q_pos, n_q, alpha_denom, scores_out, s);
+    else score_many<IM_DI, 16>(h, st, nqw, q_pos, n_q, alpha_denom, scores_out, s);
   }
-  float* sc_out = groups > 1 ? (float*)(h->ws + h->off_spart) : scores_out;
-  // (the kernel's "units" are the sets; H_kv / H_set of them belong to one batch element)
-#define IM_SCORE(TPW, DI)                                                                                    \
-  k_score<TPW, DI><<<dim3((h->max_live + 64 * TPW - 1) / (64 * TPW), units, groups), 256, 0, s>>>(           \
-      (const bf16_t*)st->Kidx, st->pos, st->len, st->n_projected, qy, al, q_pos, n_q,                        \
-      c.n_kv_heads / heads_per_set(c), c.capacity, c.n_idx_heads, h->max_live, sc_out, q_per_group)
-  if (c.head_shared) { if (small) IM_SCORE(1, IM_DI_SHARED); else IM_SCORE(4, IM_DI_SHARED); }
-  else { if (small) IM_SCORE(1, IM_DI); else IM_SCORE(4, IM_DI); }
-#undef IM_SCORE
-  if (groups > 1)
-    k_score_max<<<dim3((h->max_live + 255) / 256, units), 256, 0, s>>>(sc_out, groups, st->len, c.capacity,
-                                                                      h->max_live, scores_out);
   return launch_check(h, "im_index_score");
 }
 

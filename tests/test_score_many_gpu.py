@@ -1,0 +1,69 @@
+"""im_index_score with at least as many queries as indexer heads: bounds of all pairs on the fp16 matrix cores, fp64
+for the pairs that can be a key's maximum.  The scores must be the oracle's fp32 numbers bit for bit, at the edges
+of its tiles (16 queries, 64 and 256 keys) and where the bounds decide nothing: equal queries, gates of zero, and
+values outside the range in which bounds are formed."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_25475_amd as im
+from helpers import f64
+from parity import LockStep, LockStepShared
+from workloads import WORKLOADS
+
+pytestmark = pytest.mark.gpu
+
+
+def _scaled(**factors):
+    def mod(p):
+        for name, f in factors.items():
+            p[name] = (p[name].float() * f).to(torch.bfloat16)
+    return mod
+
+
+MODES = {
+    "plain": {},
+    "equal-queries": {},                                            # every query is a candidate of every key
+    "zero-gates": dict(params_mod=_scaled(G=0.0)),                  # every score is 0
+    "tiny-gates": dict(params_mod=_scaled(G=2.0 ** -100)),          # no bound is formed: everything in fp64
+    "large-norm-weights": dict(params_mod=_scaled(norm_q_w=2.0 ** 20, norm_k_w=2.0 ** 20)),
+    "small-norm-weights": dict(params_mod=_scaled(norm_q_w=2.0 ** -20, norm_k_w=2.0 ** -20)),
+}
+
+
+@pytest.mark.parametrize("mode", sorted(MODES))
+@pytest.mark.parametrize("heads", [(32, 8), (28, 4), (64, 8)], ids=["8", "7", "16"])   # indexer heads
+@pytest.mark.parametrize("shared", [False, True], ids=["per-unit", "head-shared"])
+def test_scores_of_many_queries_are_the_oracles(mode, heads, shared):
+    for n_q, n in ((16, 1), (17, 63), (31, 64), (32, 65), (33, 257), (140, 300)):
+        kw = dict(context=n, budget=n, decode_steps=n_q, batch=2, n_layers=1, n_q_heads=heads[0], n_kv_heads=heads[1])
+        w = WORKLOADS["cfg1"].shared(**kw) if shared else WORKLOADS["cfg1"].scaled(**kw)
+        cls, args = (LockStepShared, {}) if shared else (LockStep, dict(max_queries=n_q))
+        if shared:   # (its handle takes at most `context` queries)
+            w = w.scaled(context=max(n, n_q), decode_steps=0)
+        ls = cls(w, capacity=max(n, n_q), **args, **MODES[mode])
+        g, ref, d = ls.gpu, ls.ref, (lambda t: t.cuda())
+        k, v = ls.K[:, :, :n].contiguous(), ls.V[:, :, :n].contiguous()
+        pos = torch.arange(n, dtype=torch.int32).repeat(w.batch, 1).contiguous()
+        q = ls.Q[:, -n_q:].contiguous()
+        if mode == "equal-queries":
+            q[:] = q[:, :1].clone()
+        # positions in no order: some queries see every key, some a part, some none
+        rng = np.random.default_rng(n_q * 1000 + n)
+        qpos = torch.tensor(rng.integers(-3, n + 2, (w.batch, n_q)), dtype=torch.int32)
+        if shared:
+            x = ls.X[:, :n].contiguous()
+            im.im_append_kv_hidden(ls.handle, ls.params, g.st, d(k), d(v), d(x), d(pos))
+            ref.append_kv_hidden(f64(k), f64(v), f64(x), pos.numpy())
+        else:
+            im.im_append_kv(ls.handle, g.st, d(k), d(v), d(pos))
+            ref.append_kv(f64(k), f64(v), pos.numpy())
+        im.im_set_max_live(ls.handle, n)
+        xg = q.view(w.batch, n_q, -1)
+        im.im_index_score(ls.handle, ls.params, g.st, d(q), d(xg), d(qpos), g.scores)
+        torch.cuda.synchronize()
+        want = ref.index_score(f64(q), f64(xg), qpos.numpy())[..., :n]
+        got = g.scores[..., :n].cpu().numpy().astype(np.float64)
+        same = (got == want) | (np.isneginf(got) & np.isneginf(want))
+        assert same.all(), f"{n_q} queries, {n} keys: {int((~same).sum())} of {same.size} scores differ"
+        assert im.im_query_status(ls.handle) == 0
