@@ -1,0 +1,244 @@
+// Large products of bf16 matrices with an exact sum: C[m][n] = sum_k A[m][k] B[n][k], rounded to fp64 once.
+//
+// The query projection of a prompt needs fp64 sums of 4096 bf16 products (everything that decides an eviction
+// is taken in fp64), and the fp64 matrix cores give 78 TFLOP/s.  The int8 ones give 5000: a row is written as
+// integers of a common unit, x = X 2^(E - 149) with E the row's largest (biased) exponent, so |X| <= 255 2^22, in four
+// signed base-256 digits, and the 16 products of digits, accumulated exactly in 7 int32 sums (one per power of
+// 256), give the exact sum of X W: a third of the time of the fp64 cores.  Elements more than 2^22 below their
+// row's largest lose bits in X: they are listed with their remainder (1 in 2.6 million for Gaussian values) and
+// added in fp64 afterwards; should a list overflow, the fp64 kernel computes the product instead.
+//   k_exact_prep : row exponents of A; exponents and digit planes of B
+//   k_exact_gemm : the product
+//   k_exact_fix  : remainders
+#pragma once
+#include "im_kernels.h"
+
+typedef int im_i4 __attribute__((ext_vector_type(4)));
+typedef int im_i16 __attribute__((ext_vector_type(16)));
+
+#define XG_BM 64            // rows of A, rows of B, and contraction length per workgroup step
+#define XG_BN 128
+#define XG_BK 64
+#define XG_MAX_K 8192       // sums of 4 digit products stay below 2^29, and the two halves of the result below 2^53
+#define XG_LIST_A 65536     // listed elements
+#define XG_LIST_B 4096
+// counters: [0] listed elements of A, [1] of B.  Entries: (row, k).  k_score_features clears the counters for
+// the next product.
+struct ExactLists {
+  int32_t* count;
+  int2 *a, *b;
+};
+
+__device__ __forceinline__ bool exact_overflow(const ExactLists& l) {
+  return l.count[0] > XG_LIST_A || l.count[1] > XG_LIST_B;
+}
+// the scale 2^(149 - E) that makes a row's elements integers; rows of very small numbers take a larger unit
+__device__ __forceinline__ int exact_clamp_exp(int e) { return max(e, 40); }
+__device__ __forceinline__ float exact_scale(int e) { return __uint_as_float((uint32_t)(127 + 156 - e) << 23); }
+// (unit of X: 2^(E - 127 - 7 - 22) = 2^(E - 156))
+
+// the largest exponent of 8 bf16 values
+__device__ __forceinline__ int exact_max_exp(const uint4& u, int e) {
+  const uint32_t v[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) e = max(e, (int)max((v[i] >> 7) & 255u, (v[i] >> 23) & 255u));
+  return e;
+}
+
+// 8 values -> their 4 digit planes (8 bytes each, lowest digit first); lost: a bit mask of the values that X truncates
+__device__ __forceinline__ void exact_digits(const uint4& u, float scale, uint2 (&plane)[4], uint32_t& lost) {
+  const uint32_t v[4] = {u.x, u.y, u.z, u.w};
+  uint32_t x[8];
+  lost = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float f = ((i & 1) ? bf_hi(v[i >> 1]) : bf_lo(v[i >> 1])) * scale;
+    const int xi = (int)f;                         // towards zero
+    if ((float)xi != f) lost |= 1u << i;           // (X has at most 8 significant bits: the way back is exact)
+    // digits d_0 .. d_3 in -128 .. 127: the bytes of X + 0x80808080, each less 128
+    x[i] = ((uint32_t)xi + 0x80808080u) ^ 0x80808080u;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {                    // 4 x 4 byte transpose
+    const uint32_t a = x[4 * h], b = x[4 * h + 1], c = x[4 * h + 2], d = x[4 * h + 3];
+    const uint32_t ab0 = __builtin_amdgcn_perm(b, a, 0x05010400u), ab1 = __builtin_amdgcn_perm(b, a, 0x07030602u);
+    const uint32_t cd0 = __builtin_amdgcn_perm(d, c, 0x05010400u), cd1 = __builtin_amdgcn_perm(d, c, 0x07030602u);
+    const uint32_t p0 = __builtin_amdgcn_perm(cd0, ab0, 0x05040100u), p1 = __builtin_amdgcn_perm(cd0, ab0, 0x07060302u);
+    const uint32_t p2 = __builtin_amdgcn_perm(cd1, ab1, 0x05040100u), p3 = __builtin_amdgcn_perm(cd1, ab1, 0x07060302u);
+    if (h == 0) { plane[0].x = p0; plane[1].x = p1; plane[2].x = p2; plane[3].x = p3; }
+    else { plane[0].y = p0; plane[1].y = p1; plane[2].y = p2; plane[3].y = p3; }
+  }
+}
+
+// x - X unit for a listed element
+__device__ __forceinline__ double exact_rest(bf16_t x, int e) {
+  const float f = bf2f(x) * exact_scale(e);
+  return ldexp((double)f - (double)(int)f, e - 156);
+}
+
+// Byte offset, inside the operand of a 32-row tile and a 32-wide step, of digit plane 0 of 8 values k = 8 p .. (p = 0 .. 3)
+// of a row: lane (row % 32, k / 16) of the 32x32x32 product reads 16 bytes.  A plane has 1 KB.
+__device__ __forceinline__ int exact_place(int row, int p) { return (((p >> 1) * 32 + (row & 31)) << 4) + (p & 1) * 8; }
+
+// grid (ceil(M / 4) + ceil(Np / 4)), one wave per row; Np = N rounded up to XG_BN (rows past N are zeros).
+// expA [M], expB [Np]; planes [Np / 32][K / 32][4 digits][1 KB]
+__global__ __launch_bounds__(256) void k_exact_prep(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int M, int N,
+                                                    int Np, int K, int32_t* __restrict__ expA,
+                                                    int32_t* __restrict__ expB, char* __restrict__ planes,
+                                                    ExactLists lists) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, mb = (M + 3) / 4;
+  const bool isb = (int)blockIdx.x >= mb;
+  const int row = (isb ? (int)blockIdx.x - mb : (int)blockIdx.x) * 4 + w;
+  if (row >= (isb ? Np : M)) return;
+  const bf16_t* src = isb ? B + (size_t)min(row, N - 1) * K : A + (size_t)row * K;
+  int e = 0;
+#pragma unroll 4
+  for (int k = lane * 8; k < K; k += 512) e = exact_max_exp(*(const uint4*)(src + k), e);
+  e = exact_clamp_exp((int)wave_max_u((uint32_t)e));
+  if (lane == 0) (isb ? expB : expA)[row] = e;
+  if (!isb) return;
+  const float scale = row < N ? exact_scale(e) : 0.f;
+  for (int k = lane * 8; k < K; k += 512) {
+    uint2 pl[4];
+    uint32_t lost;
+    exact_digits(*(const uint4*)(src + k), scale, pl, lost);
+    char* dst = planes + ((size_t)(row / 32) * (K / 32) + k / 32) * 4096 + exact_place(row, (k / 8) & 3);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) *(uint2*)(dst + d * 1024) = pl[d];
+    while (lost) {   // (in practice a handful in the whole matrix)
+      const int i = __builtin_ctz(lost);
+      lost &= lost - 1;
+      const int at = atomicAdd(lists.count + 1, 1);
+      if (at < XG_LIST_B) lists.b[at] = make_int2(row, k + i);
+    }
+  }
+}
+
+// grid (ceil(M / XG_BM) * Np / XG_BN), 8 waves as 2 x 4; a wave owns a 32 x 32 tile of C in 7 int32 accumulators.
+// Two LDS buffers of one step (64 values): B's planes are copied straight into LDS, A's rows are loaded as bf16,
+// one step ahead, and written as digits by the thread that loaded them.  Matrix-core-bound: 16 products of 32
+// cycles per 32 x 32 x 32, against about 9 vector instructions per element of A and step.
+__global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict__ A, const char* __restrict__ planes,
+                                                       const int32_t* __restrict__ expA,
+                                                       const int32_t* __restrict__ expB, double* __restrict__ C, int M,
+                                                       int N, int Np, int K, ExactLists lists) {
+  __shared__ __attribute__((aligned(16))) char sA[2][XG_BM * XG_BK * 4], sB[2][XG_BN * XG_BK * 4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w & 1, wn = w >> 1;
+  // workgroups go to the 8 XCDs round-robin: an XCD keeps to one column tile where there are 1, 2, 4 or 8 of them, so
+  // that its part of B's planes stays in its L2
+  const int nt = Np / XG_BN, bid = blockIdx.x;
+  int tn, tm;
+  if (8 % nt == 0) { tn = (bid & 7) % nt; tm = (bid >> 3) * (8 / nt) + (bid & 7) / nt; }
+  else { tn = bid % nt; tm = bid / nt; }
+  const int m0 = tm * XG_BM, n0 = tn * XG_BN;
+  if (m0 >= M) return;
+  // this thread's piece of A: row arow, values 8 ap .. of every step
+  const int arow = tid >> 3, ap = tid & 7;
+  const int am = min(m0 + arow, M - 1);
+  const bf16_t* asrc = A + (size_t)am * K + ap * 8;
+  const float ascale = exact_scale(expA[am]);
+  const int aplace = ((arow >> 5) * 2 + (ap >> 2)) * 4096 + exact_place(arow, ap & 3);
+  const bool lister = tn == 0 && m0 + arow < M;
+  auto fetchB = [&](int c, int buf) {   // 4 row tiles x 2 steps x 4 KB: 4 pieces of 1 KB per wave
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int piece = w * 4 + i, t = piece >> 3, rest = piece & 7;
+      const char* src = planes + ((size_t)(n0 / 32 + t) * (K / 32) + 2 * c) * 4096 + rest * 1024 + lane * 16;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                       (__attribute__((address_space(3))) void*)&sB[buf][piece * 1024], 16, 0, 0);
+    }
+  };
+  auto putA = [&](const uint4& v, int c, int buf) {
+    uint2 pl[4];
+    uint32_t lost;
+    exact_digits(v, ascale, pl, lost);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) *(uint2*)(&sA[buf][aplace + d * 1024]) = pl[d];
+    if (lister) {
+      while (lost) {
+        const int i = __builtin_ctz(lost);
+        lost &= lost - 1;
+        const int at = atomicAdd(lists.count, 1);
+        if (at < XG_LIST_A) lists.a[at] = make_int2(am, c * XG_BK + ap * 8 + i);
+      }
+    }
+  };
+  im_i16 acc[7];
+#pragma unroll
+  for (int p = 0; p < 7; ++p)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[p][r] = 0;
+  const int nc = K / XG_BK;
+  fetchB(0, 0);
+  putA(*(const uint4*)asrc, 0, 0);
+  int buf = 0;
+#pragma unroll 1
+  for (int c = 0; c < nc; ++c, buf ^= 1) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    uint4 an = make_uint4(0, 0, 0, 0);
+    if (c + 1 < nc) {
+      an = *(const uint4*)(asrc + (c + 1) * XG_BK);
+      fetchB(c + 1, buf ^ 1);
+    }
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      im_i4 a[4], b[4];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        a[d] = *(const im_i4*)(&sA[buf][(wm * 2 + st) * 4096 + d * 1024 + lane * 16]);
+        b[d] = *(const im_i4*)(&sB[buf][(wn * 2 + st) * 4096 + d * 1024 + lane * 16]);
+      }
+      // pairs of digits in an order that leaves other sums between two products of the same sum
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          const int i = d, j = (d + s) & 3;
+          acc[i + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i + j], 0, 0, 0);
+        }
+    }
+    if (c + 1 < nc) putA(an, c + 1, buf ^ 1);
+  }
+  // result register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
+  const int n = n0 + 32 * wn + (lane & 31);
+  if (n >= N) return;
+  const int eb = expB[n];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + 32 * wm + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    if (m >= M) continue;
+    // both parts are exact (|acc| <= 2^29): one rounding
+    const double lo = fma(fma(fma((double)acc[3][r], 256.0, (double)acc[2][r]), 256.0, (double)acc[1][r]), 256.0, (double)acc[0][r]);
+    const double hi = fma(fma((double)acc[6][r], 256.0, (double)acc[5][r]), 256.0, (double)acc[4][r]);
+    C[(size_t)m * N + n] = ldexp(fma(hi, 4294967296.0, lo), expA[m] + eb - 312);
+  }
+}
+
+// remainders of the listed elements: of A against the whole of B, then of B against the integers of A.
+// Grid-stride over the lists (usually a few entries); with an overflowed list, over the tiles of the fp64 product.
+__global__ __launch_bounds__(256) void k_exact_fix(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int M, int N, int K,
+                                                   const int32_t* __restrict__ expA, const int32_t* __restrict__ expB,
+                                                   double* __restrict__ C, ExactLists lists) {
+  if (exact_overflow(lists)) {
+    const int tx = (N + 63) / 64, tiles = tx * ((M + 63) / 64);
+    for (int t = blockIdx.x; t < tiles; t += gridDim.x) gemm_nt_tile<2, 2>(A, B, C, M, N, K, t % tx, t / tx);
+    return;
+  }
+  const int na = lists.count[0], nb = lists.count[1];
+  for (int i = blockIdx.x; i < na; i += gridDim.x) {
+    const int2 mk = lists.a[i];
+    const double r = exact_rest(A[(size_t)mk.x * K + mk.y], expA[mk.x]);
+    for (int n = threadIdx.x; n < N; n += 256)
+      atomicAdd(C + (size_t)mk.x * N + n, r * (double)bf2f(B[(size_t)n * K + mk.y]));
+  }
+  for (int i = 0; i < nb; ++i) {
+    const int2 nk = lists.b[i];
+    const double r = exact_rest(B[(size_t)nk.x * K + nk.y], expB[nk.x]);
+    for (int m = blockIdx.x * 256 + threadIdx.x; m < M; m += gridDim.x * 256) {
+      const bf16_t x = A[(size_t)m * K + nk.y];
+      atomicAdd(C + (size_t)m * N + nk.x, r * ((double)bf2f(x) - exact_rest(x, expA[m])));
+    }
+  }
+}

@@ -333,14 +333,13 @@ __global__ __launch_bounds__(256) void k_gemm_nt_f64(const bf16_t* __restrict__ 
 // L2 in 32-wide chunks (lane (l16, kq) loads the 8 values k = 32 c + 8 kq .. + 7 of row l16 of a
 // tile; step e of the chunk contracts k = 32 c + 8 kq + e over the 4 kq).  Result register r of
 // lane (l16, kq) is C[row 4 r + kq of the A tile][row l16 of the B tile].
-// grid (ceil(N / (32 TN)), ceil(M / (32 TM))).
+// tile (bx, by) of ceil(N / (32 TN)) x ceil(M / (32 TM)).
 template <int TM, int TN>
-__global__ __launch_bounds__(256) void k_gemm_nt_mfma(const bf16_t* __restrict__ A,
-                                                      const bf16_t* __restrict__ B,
-                                                      double* __restrict__ Cm, int M, int N, int Kd) {
+__device__ __forceinline__ void gemm_nt_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
+                                             double* __restrict__ Cm, int M, int N, int Kd, int bx, int by) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
-  const int m0 = (blockIdx.y * 2 + (w >> 1)) * 16 * TM, n0 = (blockIdx.x * 2 + (w & 1)) * 16 * TN;
-  if (m0 >= M || n0 >= N) return;   // wave-uniform; no barrier in this kernel
+  const int m0 = (by * 2 + (w >> 1)) * 16 * TM, n0 = (bx * 2 + (w & 1)) * 16 * TN;
+  if (m0 >= M || n0 >= N) return;   // wave-uniform; no barrier here
   const bf16_t* ap[TM];
   const bf16_t* bp[TN];
 #pragma unroll
@@ -396,6 +395,12 @@ __global__ __launch_bounds__(256) void k_gemm_nt_mfma(const bf16_t* __restrict__
         const int m = m0 + 16 * i + 4 * r + kq, n = n0 + 16 * j + l16;
         if (m < M && n < N) Cm[(size_t)m * N + n] = acc[i][j][r];
       }
+}
+
+template <int TM, int TN>
+__global__ __launch_bounds__(256) void k_gemm_nt_mfma(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
+                                                      double* __restrict__ Cm, int M, int N, int Kd) {
+  gemm_nt_tile<TM, TN>(A, B, Cm, M, N, Kd, blockIdx.x, blockIdx.y);
 }
 
 // The same for small products: ONE 16 x 16 output tile per workgroup, its 4 waves take a quarter of

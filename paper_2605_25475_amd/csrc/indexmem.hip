@@ -14,6 +14,7 @@
 
 #include "im_kernels.h"
 #include "im_score.h"
+#include "im_exact.h"
 #include "im_decode.h"
 
 struct im_handle {
@@ -24,6 +25,7 @@ struct im_handle {
   bool ws_ready;
   // workspace layout (byte offsets)
   size_t off_status, off_qy, off_alpha, off_mem, off_attn, off_dpart, off_dcand, off_dqm, off_xk, off_hspart, total;
+  size_t off_xcount, off_xexp, off_xplanes, off_xlist;              // exact products
   size_t off_qf, off_al16, off_qblk, off_recu, off_reci, off_nlist, off_list;   // scores of many queries
   int mem_split, attn_chunks, dec_splits;
   size_t rec_keys;   // (group, key) records of a scan that the workspace holds
@@ -105,6 +107,15 @@ size_t score_rec_keys(size_t sets, size_t capacity) {
   return all < few ? all : few;
 }
 
+// The query projection of M rows goes through the exact int8 product (im_exact.h) where it has more than 2048 tiles
+// of 16 x 16: below, its 64 x 128 tiles leave most of the chip idle and the fp64 kernel that splits the contraction is
+// faster (512 rows x 512: 32 us against 80).
+size_t exact_np(const im_config* c) { return ((size_t)c->n_idx_heads * c->idx_dim + XG_BN - 1) / XG_BN * XG_BN; }
+bool exact_fits(const im_config* c, long long M) {
+  const long long N = c->n_idx_heads * c->idx_dim, K = (long long)c->n_q_heads * IM_D;
+  return K <= XG_MAX_K && M < (1 << 30) && ((M + 15) / 16) * ((N + 15) / 16) > 2048;
+}
+
 void layout(const im_config* c, im_handle* h) {
   const size_t B = c->batch, Hi = c->n_idx_heads, units = (size_t)c->batch * c->n_kv_heads;
   h->mem_split = (c->capacity + 1023) / 1024;
@@ -132,6 +143,13 @@ void layout(const im_config* c, im_handle* h) {
   h->off_reci = off;   off = align256(off + h->rec_keys * 4 * sizeof(int32_t));
   h->off_nlist = off;  off = align256(off + B * sizeof(int32_t));
   h->off_list = off;   off = align256(off + sets * c->capacity * sizeof(int2));
+  // exact products: the largest one is the query projection
+  const size_t np = exact_np(c), xk = (size_t)c->n_q_heads * IM_D;
+  const bool exact = exact_fits(c, c->batch * c->max_queries);
+  h->off_xcount = off; off = align256(off + 2 * sizeof(int32_t));
+  h->off_xexp = off;   off = align256(off + (exact ? (rows + np) * sizeof(int32_t) : 0));
+  h->off_xplanes = off; off = align256(off + (exact ? np * xk * 4 : 0));
+  h->off_xlist = off;  off = align256(off + (exact ? (XG_LIST_A + XG_LIST_B) * sizeof(int2) : 0));
   // head_shared: U_k X of the rows of one append, fp64
   h->off_xk = off;     off = align256(off + (c->head_shared ? B * c->capacity * IM_DI_SHARED * sizeof(double) : 0));
   h->off_hspart = off; off = align256(off + (c->head_shared ? B * HS_NSC * sizeof(uint4) : 0));
@@ -148,6 +166,7 @@ int ensure_ws(im_handle* h, hipStream_t s) {
   if (h->ws_ready) return IM_OK;
   const int n_words = 32 + h->cfg.batch * h->cfg.n_kv_heads;
   k_fill_i32<<<(n_words + 255) / 256, 256, 0, s>>>((int32_t*)(h->ws + h->off_status), n_words, 0);
+  k_fill_i32<<<1, 64, 0, s>>>((int32_t*)(h->ws + h->off_xcount), 2, 0);
   int rc = launch_check(h, "workspace clear");
   if (rc == IM_OK) h->ws_ready = true;
   return rc;
@@ -204,6 +223,21 @@ void gemm_nt(hipStream_t s, const bf16_t* A, const bf16_t* B, double* Cm, int M,
   }
 }
 
+// the query projection of M rows as an exact product (exact_fits)
+void exact_project(im_handle* h, hipStream_t s, const bf16_t* q, const bf16_t* Uq, double* y, int M) {
+  const im_config& c = h->cfg;
+  const int N = c.n_idx_heads * c.idx_dim, K = c.n_q_heads * IM_D, np = (int)exact_np(&c);
+  int32_t* expA = (int32_t*)(h->ws + h->off_xexp);
+  int32_t* expB = expA + (size_t)c.batch * c.max_queries;
+  char* planes = h->ws + h->off_xplanes;
+  const ExactLists lists = {(int32_t*)(h->ws + h->off_xcount), (int2*)(h->ws + h->off_xlist),
+                            (int2*)(h->ws + h->off_xlist) + XG_LIST_A};
+  k_exact_prep<<<(M + 3) / 4 + (np + 3) / 4, 256, 0, s>>>(q, Uq, M, N, np, K, expA, expB, planes, lists);
+  const int nt = np / XG_BN, mt = (M + XG_BM - 1) / XG_BM, per = 8 % nt == 0 ? 8 / nt : 1;
+  k_exact_gemm<<<(mt + per - 1) / per * per * nt, 512, 0, s>>>(q, planes, expA, expB, y, M, N, np, K, lists);
+  k_exact_fix<<<512, 256, 0, s>>>(q, Uq, M, N, K, expA, expB, y, lists);
+}
+
 // the scores of n_q >= H_idx queries from their raw projections in the workspace
 template <int DI, int HM>
 void score_many(im_handle* h, const im_state* st, const bf16_t* norm_q_w, const int32_t* q_pos, int n_q,
@@ -221,7 +255,7 @@ void score_many(im_handle* h, const im_state* st, const bf16_t* norm_q_w, const 
   const bf16_t* Kidx = (const bf16_t*)st->Kidx;
   k_score_features<DI, HM><<<dim3(nblk, c.batch), 256, 0, s>>>((const double*)(ws + h->off_qy),
       (const double*)(ws + h->off_alpha), q_pos, norm_q_w, c.rms_eps, alpha_denom, n_q, c.n_idx_heads, qf, al16, blocks,
-      n_listed);
+      n_listed, (int32_t*)(ws + h->off_xcount));
   // a scan over a short cache has few (256-key tile, unit) workgroups: its query blocks then go in up to
   // IM_SCORE_GROUPS groups with workgroups of their own; a very short one also drops to 16 keys per wave
   const long long tiles4 = (long long)((live + 255) / 256) * units;
@@ -447,7 +481,8 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
       k_project_keys<<<dim3((h->max_live + 63) / 64, units), 256, 0, s>>>(
           (const bf16_t*)st->K, (bf16_t*)st->Kidx, st->len, st->n_projected, (const bf16_t*)p->Uk,
           (const bf16_t*)p->norm_k_w, c.capacity, h->max_live, c.rms_eps, status_ptr(h));
-    gemm_nt(s, (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M, Nq, Kq);
+    if (n_q >= c.n_idx_heads && exact_fits(&c, M)) exact_project(h, s, (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M);
+    else gemm_nt(s, (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M, Nq, Kq);
     gemm_nt(s, (const bf16_t*)x_gate, (const bf16_t*)p->G, al, M, c.n_idx_heads, c.gate_in_dim);
   }
   // fewer queries than indexer heads (a decode step): the heads of a query are the scoring product's columns

@@ -67,3 +67,46 @@ def test_scores_of_many_queries_are_the_oracles(mode, heads, shared):
         same = (got == want) | (np.isneginf(got) & np.isneginf(want))
         assert same.all(), f"{n_q} queries, {n} keys: {int((~same).sum())} of {same.size} scores differ"
         assert im.im_query_status(ls.handle) == 0
+
+
+def _shrink(t, share, seed):
+    """A share of the values becomes 2^-26 of its size: 22 bits below a row's largest value is where the exact
+    product's integers end, and what they lose is added from lists."""
+    g = torch.Generator().manual_seed(seed)
+    small = torch.rand(t.shape, generator=g) < share
+    return torch.where(small, (t.float() * 2.0 ** -26).to(torch.bfloat16), t)
+
+
+@pytest.mark.parametrize("share_q,share_u", [(0.0, 0.0), (0.002, 0.0), (0.002, 0.0005), (0.0, 0.01), (0.05, 0.0)],
+                         ids=["plain", "lists-q", "lists-both", "overflow-u", "overflow-q"])
+@pytest.mark.parametrize("heads,n_q,shared", [((32, 8), 1089, False), ((28, 4), 1207, False), ((32, 8), 2081, True)],
+                         ids=["512", "448", "128"])   # columns of the query projection
+def test_query_projection_as_an_exact_product(heads, n_q, shared, share_q, share_u):
+    # row counts that are no multiple of the product's 64-row tiles; 448 columns are no multiple of its 128
+    n = 40
+    kw = dict(context=n_q, budget=n, decode_steps=0, batch=2, n_layers=1, n_q_heads=heads[0], n_kv_heads=heads[1])
+    w = WORKLOADS["cfg1"].shared(**kw) if shared else WORKLOADS["cfg1"].scaled(**kw)
+
+    def mod(p):
+        p["Uq"] = _shrink(p["Uq"], share_u, 5)
+    ls = (LockStepShared if shared else LockStep)(w, params_mod=mod)
+    g, ref, d = ls.gpu, ls.ref, (lambda t: t.cuda())
+    k, v = ls.K[:, :, :n].contiguous(), ls.V[:, :, :n].contiguous()
+    pos = torch.arange(n, dtype=torch.int32).repeat(w.batch, 1).contiguous()
+    q = _shrink(ls.Q.contiguous(), share_q, 6)
+    qpos = torch.arange(n_q, dtype=torch.int32).repeat(w.batch, 1).contiguous() % (n + 3)
+    if shared:
+        x = ls.X[:, :n].contiguous()
+        im.im_append_kv_hidden(ls.handle, ls.params, g.st, d(k), d(v), d(x), d(pos))
+        ref.append_kv_hidden(f64(k), f64(v), f64(x), pos.numpy())
+    else:
+        im.im_append_kv(ls.handle, g.st, d(k), d(v), d(pos))
+        ref.append_kv(f64(k), f64(v), pos.numpy())
+    im.im_set_max_live(ls.handle, n)
+    want = ref.index_score(f64(q), f64(q.view(w.batch, n_q, -1)), qpos.numpy())[..., :n]
+    for _ in range(2):   # the second call finds the first one's lists
+        g.scores.fill_(float("nan"))
+        im.im_index_score(ls.handle, ls.params, g.st, d(q), d(q).view(w.batch, n_q, -1), d(qpos), g.scores)
+        torch.cuda.synchronize()
+        got = g.scores[..., :n].cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, want), f"{int((got != want).sum())} of {want.size} scores differ"
