@@ -45,16 +45,30 @@ __device__ __forceinline__ int exact_max_exp(const uint4& u, int e) {
   return e;
 }
 
-// 8 values -> their 4 digit planes (8 bytes each, lowest digit first); lost: a bit mask of the values that X truncates
-__device__ __forceinline__ void exact_digits(const uint4& u, float scale, uint2 (&plane)[4], uint32_t& lost) {
+// lists those of 8 values (row, k ..) that X truncates
+__device__ __forceinline__ void exact_list(const uint4& u, float scale, int row, int k, int32_t* count, int2* list, int room) {
   const uint32_t v[4] = {u.x, u.y, u.z, u.w};
-  uint32_t x[8];
-  lost = 0;
+  uint32_t lost = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const float f = ((i & 1) ? bf_hi(v[i >> 1]) : bf_lo(v[i >> 1])) * scale;
-    const int xi = (int)f;                         // towards zero
-    if ((float)xi != f) lost |= 1u << i;           // (X has at most 8 significant bits: the way back is exact)
+    lost |= (f != truncf(f)) ? 1u << i : 0u;
+  }
+  while (lost) {   // (in practice a handful in the whole matrix)
+    const int i = __builtin_ctz(lost);
+    lost &= lost - 1;
+    const int at = atomicAdd(count, 1);
+    if (at < room) list[at] = make_int2(row, k + i);
+  }
+}
+
+// 8 values -> their 4 digit planes (8 bytes each, lowest digit first)
+__device__ __forceinline__ void exact_digits(const uint4& u, float scale, uint2 (&plane)[4]) {
+  const uint32_t v[4] = {u.x, u.y, u.z, u.w};
+  uint32_t x[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int xi = (int)(((i & 1) ? bf_hi(v[i >> 1]) : bf_lo(v[i >> 1])) * scale);   // towards zero
     // digits d_0 .. d_3 in -128 .. 127: the bytes of X + 0x80808080, each less 128
     x[i] = ((uint32_t)xi + 0x80808080u) ^ 0x80808080u;
   }
@@ -91,38 +105,46 @@ __global__ __launch_bounds__(256) void k_exact_prep(const bf16_t* __restrict__ A
   const int row = (isb ? (int)blockIdx.x - mb : (int)blockIdx.x) * 4 + w;
   if (row >= (isb ? Np : M)) return;
   const bf16_t* src = isb ? B + (size_t)min(row, N - 1) * K : A + (size_t)row * K;
+  uint4 v[XG_MAX_K / 512];   // the row: 8 values per lane and piece (absent pieces repeat the first)
+  const int pieces = K / 512, rest = K % 512;
+#pragma unroll
+  for (int i = 0; i < XG_MAX_K / 512; ++i) {
+    if (i * 512 < K) v[i] = *(const uint4*)(src + ((i < pieces || lane * 8 < rest) ? i * 512 + lane * 8 : 0));
+  }
   int e = 0;
-#pragma unroll 4
-  for (int k = lane * 8; k < K; k += 512) e = exact_max_exp(*(const uint4*)(src + k), e);
+#pragma unroll
+  for (int i = 0; i < XG_MAX_K / 512; ++i)
+    if (i * 512 < K) e = exact_max_exp(v[i], e);
   e = exact_clamp_exp((int)wave_max_u((uint32_t)e));
   if (lane == 0) (isb ? expB : expA)[row] = e;
-  if (!isb) return;
-  const float scale = row < N ? exact_scale(e) : 0.f;
-  for (int k = lane * 8; k < K; k += 512) {
+  const float scale = row < N || !isb ? exact_scale(e) : 0.f;
+#pragma unroll
+  for (int i = 0; i < XG_MAX_K / 512; ++i) {
+    const int k = i * 512 + lane * 8;
+    if (i * 512 >= K || k >= K) continue;
+    if (!isb) {
+      exact_list(v[i], scale, row, k, lists.count, lists.a, XG_LIST_A);
+      continue;
+    }
+    exact_list(v[i], scale, row, k, lists.count + 1, lists.b, XG_LIST_B);
     uint2 pl[4];
-    uint32_t lost;
-    exact_digits(*(const uint4*)(src + k), scale, pl, lost);
+    exact_digits(v[i], scale, pl);
     char* dst = planes + ((size_t)(row / 32) * (K / 32) + k / 32) * 4096 + exact_place(row, (k / 8) & 3);
 #pragma unroll
     for (int d = 0; d < 4; ++d) *(uint2*)(dst + d * 1024) = pl[d];
-    while (lost) {   // (in practice a handful in the whole matrix)
-      const int i = __builtin_ctz(lost);
-      lost &= lost - 1;
-      const int at = atomicAdd(lists.count + 1, 1);
-      if (at < XG_LIST_B) lists.b[at] = make_int2(row, k + i);
-    }
   }
 }
 
 // grid (ceil(M / XG_BM) * Np / XG_BN), 8 waves as 2 x 4; a wave owns a 32 x 32 tile of C in 7 int32 accumulators.
-// Two LDS buffers of one step (64 values): B's planes are copied straight into LDS, A's rows are loaded as bf16,
-// one step ahead, and written as digits by the thread that loaded them.  Matrix-core-bound: 16 products of 32
-// cycles per 32 x 32 x 32, against about 9 vector instructions per element of A and step.
+// A step is 64 values of the contraction: 32 products of 32 cycles per wave, two waves per SIMD, 1 us.  B's planes are
+// copied straight into LDS two steps ahead and A's rows (bf16) three (a load from HBM takes up to 2 us); the thread
+// that copied 8 values of A turns them into digits one step ahead, between the products.
 __global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict__ A, const char* __restrict__ planes,
                                                        const int32_t* __restrict__ expA,
                                                        const int32_t* __restrict__ expB, double* __restrict__ C, int M,
-                                                       int N, int Np, int K, ExactLists lists) {
-  __shared__ __attribute__((aligned(16))) char sA[2][XG_BM * XG_BK * 4], sB[2][XG_BN * XG_BK * 4];
+                                                       int N, int Np, int K) {
+  __shared__ __attribute__((aligned(16))) char sA[2][XG_BM * XG_BK * 4], sB[3][XG_BN * XG_BK * 4];
+  __shared__ __attribute__((aligned(16))) char sR[3][XG_BM * XG_BK * 2];   // A's rows as they are
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w & 1, wn = w >> 1;
   // workgroups go to the 8 XCDs round-robin: an XCD keeps to one column tile where there are 1, 2, 4 or 8 of them, so
@@ -137,31 +159,17 @@ __global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict_
   const int arow = tid >> 3, ap = tid & 7;
   const int am = min(m0 + arow, M - 1);
   const bf16_t* asrc = A + (size_t)am * K + ap * 8;
+  const int nc = K / XG_BK;
   const float ascale = exact_scale(expA[am]);
   const int aplace = ((arow >> 5) * 2 + (ap >> 2)) * 4096 + exact_place(arow, ap & 3);
-  const bool lister = tn == 0 && m0 + arow < M;
-  auto fetchB = [&](int c, int buf) {   // 4 row tiles x 2 steps x 4 KB: 4 pieces of 1 KB per wave
+  // a step's copies: 8 KB of A (each wave the 8 rows that its threads convert), 4 row tiles x 2 steps x 4 KB of B
+  auto fetchA = [&](int c, int buf) { copy_to_lds_1k((const char*)(asrc + min(c, nc - 1) * XG_BK), &sR[buf][w * 1024]); };
+  auto fetchB = [&](int c, int buf) {
+    c = min(c, nc - 1);   // (past the end: not used)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int piece = w * 4 + i, t = piece >> 3, rest = piece & 7;
-      const char* src = planes + ((size_t)(n0 / 32 + t) * (K / 32) + 2 * c) * 4096 + rest * 1024 + lane * 16;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                       (__attribute__((address_space(3))) void*)&sB[buf][piece * 1024], 16, 0, 0);
-    }
-  };
-  auto putA = [&](const uint4& v, int c, int buf) {
-    uint2 pl[4];
-    uint32_t lost;
-    exact_digits(v, ascale, pl, lost);
-#pragma unroll
-    for (int d = 0; d < 4; ++d) *(uint2*)(&sA[buf][aplace + d * 1024]) = pl[d];
-    if (lister) {
-      while (lost) {
-        const int i = __builtin_ctz(lost);
-        lost &= lost - 1;
-        const int at = atomicAdd(lists.count, 1);
-        if (at < XG_LIST_A) lists.a[at] = make_int2(am, c * XG_BK + ap * 8 + i);
-      }
+      copy_to_lds_1k(planes + ((size_t)(n0 / 32 + t) * (K / 32) + 2 * c) * 4096 + rest * 1024 + lane * 16, &sB[buf][piece * 1024]);
     }
   };
   im_i16 acc[7];
@@ -169,50 +177,76 @@ __global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict_
   for (int p = 0; p < 7; ++p)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[p][r] = 0;
-  const int nc = K / XG_BK;
+  fetchA(0, 0);
+  fetchA(1, 1);
   fetchB(0, 0);
-  putA(*(const uint4*)asrc, 0, 0);
-  int buf = 0;
-#pragma unroll 1
-  for (int c = 0; c < nc; ++c, buf ^= 1) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    uint4 an = make_uint4(0, 0, 0, 0);
-    if (c + 1 < nc) {
-      an = *(const uint4*)(asrc + (c + 1) * XG_BK);
-      fetchB(c + 1, buf ^ 1);
-    }
+  fetchA(2, 2);
+  fetchB(1, 1);
+  copy_wait<5>();
+  {
+    uint2 pl[4];
+    exact_digits(*(const uint4*)(&sR[0][tid * 16]), ascale, pl);
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      im_i4 a[4], b[4];
+    for (int d = 0; d < 4; ++d) *(uint2*)(&sA[0][aplace + d * 1024]) = pl[d];
+  }
+  int bA = 0, b3 = 0;
+#pragma unroll 1
+  for (int c = 0; c < nc; ++c) {
+    const int next = b3 == 2 ? 0 : b3 + 1;
+    copy_wait<5>();    // all but the youngest step's copies: B of this step and A of the next are here
+    __syncthreads();   // ... for every wave, and the buffers of the step before are free
+    fetchA(c + 3, b3);
+    fetchB(c + 2, b3 == 0 ? 2 : b3 - 1);
+    im_i4 a[2][4], b[2][4];
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
-        a[d] = *(const im_i4*)(&sA[buf][(wm * 2 + st) * 4096 + d * 1024 + lane * 16]);
-        b[d] = *(const im_i4*)(&sB[buf][(wn * 2 + st) * 4096 + d * 1024 + lane * 16]);
+        a[st][d] = *(const im_i4*)(&sA[bA][(wm * 2 + st) * 4096 + d * 1024 + lane * 16]);
+        b[st][d] = *(const im_i4*)(&sB[b3][(wn * 2 + st) * 4096 + d * 1024 + lane * 16]);
       }
-      // pairs of digits in an order that leaves other sums between two products of the same sum
+    uint2 pl[4];
+    exact_digits(*(const uint4*)(&sR[next][tid * 16]), ascale, pl);
+    // pairs of digits in an order that leaves other sums between two products of the same sum
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-          const int i = d, j = (d + s) & 3;
-          acc[i + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i + j], 0, 0, 0);
+          const int j = (d + s) & 3;
+          acc[d + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[st][d], b[st][j], acc[d + j], 0, 0, 0);
         }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) *(uint2*)(&sA[bA ^ 1][aplace + d * 1024]) = pl[d];
+    // the conversion goes between the products: a product keeps the matrix core busy for 8 vector instructions
+    __builtin_amdgcn_sched_group_barrier(0x100, 17, 0);
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
     }
-    if (c + 1 < nc) putA(an, c + 1, buf ^ 1);
+    __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
+    bA ^= 1;
+    b3 = next;
   }
+  copy_wait<0>();
   // result register r of lane l: row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
   const int n = n0 + 32 * wn + (lane & 31);
   if (n >= N) return;
   const int eb = expB[n];
+  int4 ea[4];   // (rows past M: words of the workspace behind the exponents, not used)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) ea[i] = *(const int4*)(expA + m0 + 32 * wm + 8 * i + 4 * (lane >> 5));
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int m = m0 + 32 * wm + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    const int em = (r & 3) == 0 ? ea[r >> 2].x : (r & 3) == 1 ? ea[r >> 2].y : (r & 3) == 2 ? ea[r >> 2].z : ea[r >> 2].w;
     if (m >= M) continue;
     // both parts are exact (|acc| <= 2^29): one rounding
     const double lo = fma(fma(fma((double)acc[3][r], 256.0, (double)acc[2][r]), 256.0, (double)acc[1][r]), 256.0, (double)acc[0][r]);
     const double hi = fma(fma((double)acc[6][r], 256.0, (double)acc[5][r]), 256.0, (double)acc[4][r]);
-    C[(size_t)m * N + n] = ldexp(fma(hi, 4294967296.0, lo), expA[m] + eb - 312);
+    C[(size_t)m * N + n] = ldexp(fma(hi, 4294967296.0, lo), em + eb - 312);
   }
 }
 

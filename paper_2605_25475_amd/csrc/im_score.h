@@ -190,12 +190,6 @@ __device__ __forceinline__ im_f4 score_product(const char* head, int lane, const
   }
 }
 
-// 1 KB of a query block per wave instruction, straight into LDS
-__device__ __forceinline__ void score_copy_kb(const char* src, char* dst, int lane) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + lane * 16),
-                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-}
-
 // grid (ceil(max_live / (64 TPW)) * units, groups), 4 waves; a wave owns TPW tiles of 16 keys, their fp16 operands in
 // registers, and the workgroup walks over the query blocks (two LDS buffers, the next block on its way while one is
 // in use), from the last one down to the first that sees the tile: every resident workgroup then reads the
@@ -260,13 +254,13 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_scan(const bf16_
   for (int t = 0; t < TPW; ++t) { u1[t] = u2[t] = -INFINITY; i1[t] = 0; }
   auto fetch = [&](int blk, int buf) {
     for (int c = w; c < SB::BYTES / 1024; c += 4)
-      score_copy_kb(src + (size_t)blk * SB::BYTES + c * 1024, &sq[buf][c * 1024], lane);
+      copy_to_lds_1k(src + (size_t)blk * SB::BYTES + c * 1024 + lane * 16, &sq[buf][c * 1024]);
   };
   if (b_hi > b_lo) fetch(b_hi - 1, 0);
   int buf = 0;
 #pragma unroll 1
   for (int blk = b_hi - 1; blk >= b_lo; --blk, buf ^= 1) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part of the block has arrived
+    copy_wait<0>();                                     // this wave's part of the block has arrived
     __syncthreads();                                    // ... and everyone's; the other buffer is free again
     if (blk > b_lo) fetch(blk - 1, buf ^ 1);
     const char* q = sq[buf];

@@ -234,7 +234,7 @@ void exact_project(im_handle* h, hipStream_t s, const bf16_t* q, const bf16_t* U
                             (int2*)(h->ws + h->off_xlist) + XG_LIST_A};
   k_exact_prep<<<(M + 3) / 4 + (np + 3) / 4, 256, 0, s>>>(q, Uq, M, N, np, K, expA, expB, planes, lists);
   const int nt = np / XG_BN, mt = (M + XG_BM - 1) / XG_BM, per = 8 % nt == 0 ? 8 / nt : 1;
-  k_exact_gemm<<<(mt + per - 1) / per * per * nt, 512, 0, s>>>(q, planes, expA, expB, y, M, N, np, K, lists);
+  k_exact_gemm<<<(mt + per - 1) / per * per * nt, 512, 0, s>>>(q, planes, expA, expB, y, M, N, np, K);
   k_exact_fix<<<512, 256, 0, s>>>(q, Uq, M, N, K, expA, expB, y, lists);
 }
 
