@@ -322,16 +322,17 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_scan(const bf16_
 // grid (ceil(max_live / 64), units), 4 waves of 16 keys each.  A candidate is a record's block: its 4 queries are
 // evaluated in fp64 by the whole wave (lane (query r = lane / 16, p): dims 4 p .. of every head), the heads' terms
 // added in head order.  A second candidate block inside one record is not known by name: the key goes to the list.
-template <int DI>
+template <int DI, int HM>
 __device__ __forceinline__ float score_exact4(const float* __restrict__ qrow, const float* __restrict__ al, int H_idx,
                                               const float* kd, int p) {
   constexpr int PD = DI / 16;
   double acc = 0.0;
-#pragma unroll 1
-  for (int j0 = 0; j0 < H_idx; j0 += 4) {
-    float qv[4][PD], av[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+  for (int j0 = 0; j0 < HM; j0 += 8) {
+    if (j0 >= H_idx) break;
+    float qv[8][PD], av[8];   // (heads past the last repeat it, unused)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
       const int j = min(j0 + i, H_idx - 1);
       if constexpr (PD == 4) {
         const float4 t = *(const float4*)(qrow + j * DI + 4 * p);
@@ -340,21 +341,31 @@ __device__ __forceinline__ float score_exact4(const float* __restrict__ qrow, co
         qv[i][0] = qrow[j * DI + p];
       }
     }
-    const float4 a4 = *(const float4*)(al + j0);
-    av[0] = a4.x; av[1] = a4.y; av[2] = a4.z; av[3] = a4.w;
-    double z[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      z[i] = 0.0;
-#pragma unroll
-      for (int m = 0; m < PD; ++m) z[i] = fma((double)qv[i][m], (double)kd[m], z[i]);
-      z[i] = row16_sum_d(z[i]);
+    for (int i = 0; i < 8; i += 4) {
+      const float4 a4 = *(const float4*)(al + j0 + i);
+      av[i] = a4.x; av[i + 1] = a4.y; av[i + 2] = a4.z; av[i + 3] = a4.w;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (j0 + i < H_idx) acc = fma((double)av[i], fmax(z[i], 0.0), acc);
+    for (int i = 0; i < 8; ++i) {
+      double z = 0.0;
+#pragma unroll
+      for (int m = 0; m < PD; ++m) z = fma((double)qv[i][m], (double)kd[m], z);
+      z = row16_sum_d(z);
+      if (j0 + i < H_idx) acc = fma((double)av[i], fmax(z, 0.0), acc);
+    }
   }
   return (float)acc;
+}
+// this lane's share (dims PD p ..) of a key
+template <int DI>
+__device__ __forceinline__ void score_exact_key(const bf16_t* __restrict__ krow, float* kd, int p) {
+  if constexpr (DI == 64) {
+    const uint2 u = *(const uint2*)(krow + 4 * p);
+    kd[0] = bf_lo(u.x); kd[1] = bf_hi(u.x); kd[2] = bf_lo(u.y); kd[3] = bf_hi(u.y);
+  } else {
+    kd[0] = bf2f(krow[p]);
+  }
 }
 
 template <int DI, int HM>
@@ -413,14 +424,9 @@ __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ 
       const int s = 16 * blk + 4 * (ln >> 4) + kq, sc = min(s, n_q - 1);
       const size_t row = (size_t)b * n_q + sc;
       float kd[PD];
-      if constexpr (PD == 4) {
-        const uint2 u = *(const uint2*)(Kidx + ((size_t)unit * C + kbase + kk) * DI + 4 * l16);
-        kd[0] = bf_lo(u.x); kd[1] = bf_hi(u.x); kd[2] = bf_lo(u.y); kd[3] = bf_hi(u.y);
-      } else {
-        kd[0] = bf2f(Kidx[((size_t)unit * C + kbase + kk) * DI + l16]);
-      }
+      score_exact_key<DI>(Kidx + ((size_t)unit * C + kbase + kk) * DI, kd, l16);
       const int qp = q_pos[row];
-      const float v = score_exact4<DI>(qf + row * H_idx * DI, al16 + row * 16, H_idx, kd, l16);
+      const float v = score_exact4<DI, HM>(qf + row * H_idx * DI, al16 + row * 16, H_idx, kd, l16);
       const float m = rows_max_f((s < n_q && qp >= pkk) ? v : -INFINITY);
       if (l16 == kk) best = fmaxf(best, m);
     }
@@ -437,43 +443,63 @@ __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ 
   }
 }
 
-// A fixed number of workgroups over the listed keys: an item is 64 keys of one sequence (16 per wave) against
-// IM_LIST_BLOCKS query blocks.  scores[key] rises by atomic maxima; reading an older value only costs work.
-#define IM_LIST_BLOCKS 16
+// A fixed number of workgroups over the listed keys.  An item is 64 keys of one sequence (16 per wave) against a
+// segment of its query blocks; the segments are as short as fills the grid, and not below IM_LIST_BLOCKS.
+// scores[key] rises by atomic maxima; reading an older value only costs work.
+#define IM_LIST_WGS 1024
+#define IM_LIST_BLOCKS 8
 template <int DI, int HM>
-__global__ __launch_bounds__(256) void k_score_listed(const bf16_t* __restrict__ Kidx, const int32_t* __restrict__ pos,
-                                                      const char* __restrict__ blocks, const float* __restrict__ qf,
-                                                      const float* __restrict__ al16, int B, int n_q, int sets_per_b,
-                                                      int C, int H_idx, float* __restrict__ scores,
-                                                      const int32_t* __restrict__ n_listed,
-                                                      const int2* __restrict__ listed) {
+__global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_listed(const bf16_t* __restrict__ Kidx,
+                                                                       const int32_t* __restrict__ pos,
+                                                                       const char* __restrict__ blocks,
+                                                                       const float* __restrict__ qf,
+                                                                       const float* __restrict__ al16, int B, int n_q,
+                                                                       int sets_per_b, int C, int H_idx,
+                                                                       float* __restrict__ scores,
+                                                                       const int32_t* __restrict__ n_listed,
+                                                                       const int2* __restrict__ listed) {
   using SB = ScoreBlock<DI, HM>;
   constexpr int DPL = DI / 4;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
-  const int nblk = (n_q + 15) / 16, segs = (nblk + IM_LIST_BLOCKS - 1) / IM_LIST_BLOCKS;
+  __shared__ __attribute__((aligned(16))) char sq[2][SB::BYTES];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nblk = (n_q + 15) / 16;
+  long long chunks = 0;
+  for (int b = 0; b < B; ++b) chunks += (n_listed[b] + 63) / 64;
+  if (chunks == 0) return;
+  int segs = (int)min((2 * IM_LIST_WGS + chunks - 1) / chunks, (long long)((nblk + IM_LIST_BLOCKS - 1) / IM_LIST_BLOCKS));
+  const int per_seg = (nblk + segs - 1) / segs;
+  segs = (nblk + per_seg - 1) / per_seg;
   int b = 0;
   long long before = 0;                                    // items of the sequences before b
-  for (long long item = blockIdx.x;; item += gridDim.x) {  // (every workgroup's items ascend, so b does)
-    int cnt = 0;
-    while (b < B) {
-      cnt = n_listed[b];
-      const long long items = (long long)((cnt + 63) / 64) * segs;
-      if (item < before + items) break;
-      before += items;
-      ++b;
+  for (long long item = blockIdx.x; item < chunks * segs; item += gridDim.x) {   // (ascending, so b ascends)
+    int cnt = n_listed[b];
+    while (item >= before + (long long)((cnt + 63) / 64) * segs) {
+      before += (long long)((cnt + 63) / 64) * segs;
+      cnt = n_listed[++b];
     }
-    if (b >= B) return;
     const int k0 = (int)((item - before) / segs) * 64 + 16 * w, seg = (int)((item - before) % segs);
-    if (k0 >= cnt) continue;                               // wave-uniform; no barrier in this kernel
     const int2 uk = listed[(size_t)b * sets_per_b * C + min(k0 + l16, cnt - 1)];   // (past the end: the last one again)
     const size_t at = (size_t)uk.x * C + uk.y;
     const ScoreKey<DI> key = score_key_operand<DI>(Kidx + at * DI, kq);
     const int pk = pos[at];
     const float start = scores[at];
     float best = start;
+    const int b_lo = seg * per_seg, b_hi = min(nblk, b_lo + per_seg);
+    const char* src = blocks + (size_t)b * nblk * SB::BYTES;
+    auto fetch = [&](int blk, int buf) {
+      for (int c = w; c < SB::BYTES / 1024; c += 4)
+        copy_to_lds_1k(src + (size_t)blk * SB::BYTES + c * 1024 + lane * 16, &sq[buf][c * 1024]);
+    };
+    __syncthreads();                                       // (the item before is done with the buffers)
+    fetch(b_lo, 0);
+    int buf = 0;
 #pragma unroll 1
-    for (int blk = seg * IM_LIST_BLOCKS; blk < min(nblk, (seg + 1) * IM_LIST_BLOCKS); ++blk) {
-      const char* q = blocks + ((size_t)b * nblk + blk) * SB::BYTES;
+    for (int blk = b_lo; blk < b_hi; ++blk, buf ^= 1) {
+      copy_wait<0>();
+      __syncthreads();
+      if (blk + 1 < b_hi) fetch(blk + 1, buf ^ 1);
+      const char* q = sq[buf];
       const float* rows = (const float*)(q + SB::OFF);
       const im_f4 t4 = *(const im_f4*)(rows + SB::T * 16 + 4 * kq), e4 = *(const im_f4*)(rows + SB::ERR * 16 + 4 * kq);
       const int4 qp = *(const int4*)(rows + SB::POS * 16 + 4 * kq);
@@ -481,16 +507,40 @@ __global__ __launch_bounds__(256) void k_score_listed(const bf16_t* __restrict__
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[r] = fmaf(t4[r], z[r], e4[r]);
 #pragma unroll 1
-      for (int j = 0; j < H_idx; ++j) {
-        const im_f4 a4 = *(const im_f4*)(rows + j * 16 + 4 * kq);
-        z = score_product<DI>(q + j * SB::HEAD, lane, key);
+      for (int j0 = 0; j0 < H_idx; j0 += 4) {   // (absent heads' operands and a_j are zero)
+        im_f4 a4[4], zz[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = fmaf(a4[r], fabsf(z[r]), acc[r]);
+        for (int i = 0; i < 4; ++i) {
+          a4[i] = *(const im_f4*)(rows + (j0 + i) * 16 + 4 * kq);
+          zz[i] = score_product<DI>(q + (j0 + i) * SB::HEAD, lane, key);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[r] = fmaf(a4[i][r], fabsf(zz[i][r]), acc[r]);
       }
       const float bar = best * key.scale;
       const bool hit = (qp.x >= pk && acc[0] > bar) || (qp.y >= pk && acc[1] > bar) || (qp.z >= pk && acc[2] > bar) ||
                        (qp.w >= pk && acc[3] > bar);
-      if (!__any(hit)) continue;
+      unsigned long long hits = __ballot(hit);
+      if (!hits) continue;
+      if (__popcll(hits) <= 4) {   // (usual) lane by lane: its 4 queries against its key, as k_score_exact does it
+        while (hits) {
+          const int ln = __builtin_ctzll(hits);
+          hits &= hits - 1;
+          const int unit = __builtin_amdgcn_readlane(uk.x, ln), slot = __builtin_amdgcn_readlane(uk.y, ln);
+          const int pkk = __builtin_amdgcn_readlane(pk, ln);
+          const int s = 16 * blk + 4 * (ln >> 4) + kq;
+          const size_t row = (size_t)b * n_q + min(s, n_q - 1);
+          float kd[DI / 16];
+          score_exact_key<DI>(Kidx + ((size_t)unit * C + slot) * DI, kd, l16);
+          const float v = score_exact4<DI, HM>(qf + row * H_idx * DI, al16 + row * 16, H_idx, kd, l16);
+          const int qps = ((const int*)rows)[SB::POS * 16 + 4 * (ln >> 4) + kq];
+          const float m = rows_max_f((s < n_q && qps >= pkk) ? v : -INFINITY);
+          if (l16 == (ln & 15)) best = fmaxf(best, m);
+        }
+        continue;
+      }
       // fp64 for the whole 16 x 16 block: rows = queries (lane (l16, kq) supplies dims DPL kq .. of query l16), columns
       // = keys; result register r is query 4 r + kq, key l16
       double kd[DPL];

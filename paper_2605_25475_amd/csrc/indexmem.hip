@@ -276,7 +276,7 @@ void score_many(im_handle* h, const im_state* st, const bf16_t* norm_q_w, const 
   k_score_exact<DI, HM><<<dim3((live + 63) / 64, units), 256, 0, s>>>(
       Kidx, st->pos, st->len, blocks, qf, al16, q_pos, n_q, per_b, c.capacity, c.n_idx_heads, live, groups, live, rec_u,
       rec_i, scores, n_listed, listed);
-  k_score_listed<DI, HM><<<512, 256, 0, s>>>(Kidx, st->pos, blocks, qf, al16, c.batch, n_q, per_b, c.capacity,
+  k_score_listed<DI, HM><<<IM_LIST_WGS, 256, 0, s>>>(Kidx, st->pos, blocks, qf, al16, c.batch, n_q, per_b, c.capacity,
                                              c.n_idx_heads, scores, n_listed, listed);
 }
 
