@@ -35,8 +35,6 @@
 // splits) describes the LAST live slot: the entry that moves into the hole, and, when n = 128 S + 1,
 // the one key no split covers (then it also carries that key's rank key and logits).
 
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 struct DecArgs {
@@ -603,9 +601,8 @@ __global__ __launch_bounds__(HS_ST) void k_hs_score(const DecArgs a) {
 struct DecSplitSmem {
   union {
     double zs[DEC_KEYS][17];         // gated similarities alpha_j ReLU(q_j . k) [key][indexer head]
-    float oacc[16][4][IM_D];         // later: output partials of the 16 (wave, key group) streams,
-  };                                 //        4 heads at a time
-  float pl[DEC_KEYS][8];             // probabilities [key][head]
+    float oacc[4][DEC_GMAX * IM_D];  // later: output partials of the 4 attention waves
+  };
   float wm[4][8], wl[4][8];
   float clog[8];
   float xlp[4][8];                   // the leftover key's partial logits [scoring wave][head]
@@ -853,10 +850,9 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
     // ================= attention waves: issue the K, Q and V loads =================
     // Five groups of 4 loads per lane (K tile 0, K tile 1, Q, V tile 0, V tile 1), paced: a group goes out
     // when all but the last 4 loads before it have arrived, so a lane has at most 8 in flight.  With every
-    // workgroup of the launch resident at once, issuing all 20 at the start oversubscribes the memory queues
-    // (measured at configuration 3: 0.832 ms per step unpaced, 0.821 paced; stricter pacing loses again).
-    // Without scoring waves in the workgroup one wait, behind the Q group, does best (the periodic schedule:
-    // 0.699 ms per step unpaced, 0.697 with all three waits, 0.688 with this one).
+    // workgroup of the launch resident at once, issuing all 20 at the start oversubscribes the memory queues.
+    // (With P V on the matrix cores the order hardly matters any more: 13.2 us per launch at 32 units x 2048 entries with
+    // all waits or none, 11.7 without scoring waves.)
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
       const int kr = min(16 * (2 * wl + tt) + l16, nk - 1);
@@ -866,8 +862,7 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
     }
     if constexpr (SCORE) dec_pace4();
     {
-      // lanes past the group read its last head; they are zeroed where the fragments are used (zeroing a
-      // register here would wait for its load, and with it for every load issued before it)
+      // lanes past the group repeat its last head (their logits and probabilities are not used)
       const int jq = min(l16, G - 1);
 #pragma unroll
       for (int c = 0; c < 4; ++c)
@@ -878,7 +873,7 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
     for (int tt = 0; tt < 2; ++tt) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int vr = min(16 * (2 * wl + tt) + 4 * i + kq, nk - 1);
+        const int vr = min(16 * (2 * wl + tt) + 4 * kq + i, nk - 1);
         const bf16_t* vrow = (MERGED && k0 + vr == n_old) ? a.v_new + (size_t)u * IM_D : a.V + (base + vr) * IM_D;
         vf[tt][i] = load_stream16(vrow + 8 * l16);
       }
@@ -950,17 +945,7 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
     // they need no score, so they are taken while the scoring waves are still at work
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
-      v4f acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const uint4 ka = kf[tt][c], qb = (l16 < G) ? qf[c] : make_uint4(0, 0, 0, 0);
-        const v4s a0 = __builtin_bit_cast(v4s, make_uint2(ka.x, ka.y));
-        const v4s a1 = __builtin_bit_cast(v4s, make_uint2(ka.z, ka.w));
-        const v4s b0 = __builtin_bit_cast(v4s, make_uint2(qb.x, qb.y));
-        const v4s b1 = __builtin_bit_cast(v4s, make_uint2(qb.z, qb.w));
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, b0, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b1, acc, 0, 0, 0);
-      }
+      const im_c4 acc = att_logits(kf[tt], qf);
 #pragma unroll
       for (int r = 0; r < 4; ++r) sreg[tt][r] = acc[r] * a.scale;   // this lane: head l16, key 16 T + 4 kq + r
     }
@@ -977,7 +962,6 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
   }
   // ---- attention waves: leave the candidate out, softmax statistics and probabilities PER WAVE
   // (each wave relative to the maximum of its own 32 keys; the final reduction rescales), P V
-  float acc[G][8];
   if (!scoring) {
     float lmax = -INFINITY;
 #pragma unroll
@@ -997,15 +981,12 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
     const float mw = (lmax == -INFINITY) ? -1e30f : lmax;
     float lsum = 0.f;
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const int T = 2 * wl + tt;
+    for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float p = (sreg[tt][r] == -INFINITY) ? 0.f : __expf(sreg[tt][r] - mw);
-        lsum += p;
-        if (l16 < 8) sm.pl[16 * T + 4 * kq + r][l16] = p;
+        sreg[tt][r] = __expf(sreg[tt][r] - mw);   // (exp(-inf) = 0)
+        lsum += sreg[tt][r];
       }
-    }
     lsum = rows_sum_f(lsum);
     if (kq == 0 && l16 < 8) { sm.wm[wl][l16] = mw; sm.wl[wl][l16] = lsum; }
     // the candidate's rows travel with the record (straight from the fragments), so the tail has
@@ -1022,31 +1003,9 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
         for (int c = 0; c < 4; ++c) *(uint4*)(lrec + DEC_CAND_K + 16 * c + 4 * kq) = kf[tt][c];
       }
     }
-    // the probabilities just written are this wave's own keys: read back without a workgroup barrier
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // O[head][d] += P[head][key] V[key][d]; 16 lanes share a key row (8 dims each)
-#pragma unroll
-    for (int j = 0; j < G; ++j)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[j][e] = 0.f;
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const int T = 2 * wl + tt;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int kl = 16 * T + 4 * i + kq;
-        float pv[8], v[8];
-        *(float4*)&pv[0] = *(const float4*)&sm.pl[kl][0];
-        if (G > 4) *(float4*)&pv[4] = *(const float4*)&sm.pl[kl][4];
-        unpack8(vf[tt][i], v);
-#pragma unroll
-        for (int j = 0; j < G; ++j)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[j][e] = fmaf(pv[j], v[e], acc[j][e]);
-      }
-    }
+    im_c4 o[8] = {};
+    att_pv(sreg, vf, o);
+    att_store<G>(o, sm.oacc[wl], l16, kq);
     if (!SCORE && do_x_any && tid < G)   // the leftover key's logits: the 4 waves' partial dot products
       lrec[4 + tid] = __float_as_uint((sm.xlp[0][tid] + sm.xlp[1][tid] + sm.xlp[2][tid] + sm.xlp[3][tid]) * a.scale);
   } else if (SCORE && do_x_any && tid - 256 < G) {
@@ -1054,40 +1013,24 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
     const int j = tid - 256;
     lrec[4 + j] = __float_as_uint((sm.xlp[0][j] + sm.xlp[1][j] + sm.xlp[2][j] + sm.xlp[3][j]) * a.scale);
   }
-  // the 16 (attention wave, key group) streams meet in LDS, 4 heads at a time; all 8 waves add them up
+  // the 4 attention waves meet in LDS; every wave of the workgroup adds them up
   float* prec = a.part + ((size_t)u * a.S_alloc + s) * G * DEC_REC;   // dense [split][head][record]
+  __syncthreads();
+  for (int idx = tid; idx < G * IM_D; idx += (SCORE ? DEC_MT : DEC_MT / 2)) {
+    const int j = idx >> 7, d = idx & 127;
+    // every wave's partial is relative to its own maximum: rescale to the split's
+    const float m = fmaxf(fmaxf(sm.wm[0][j], sm.wm[1][j]), fmaxf(sm.wm[2][j], sm.wm[3][j]));
+    float o = 0.f, l = 0.f;
 #pragma unroll
-  for (int j0 = 0; j0 < G; j0 += 4) {
-    if (j0 > 0) __syncthreads();
-    if (!scoring) {
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        if (j0 + jj < G) {
-          float* dst = &sm.oacc[wl * 4 + kq][jj][8 * l16];
-          *(float4*)dst = make_float4(acc[j0 + jj][0], acc[j0 + jj][1], acc[j0 + jj][2], acc[j0 + jj][3]);
-          *(float4*)(dst + 4) = make_float4(acc[j0 + jj][4], acc[j0 + jj][5], acc[j0 + jj][6], acc[j0 + jj][7]);
-        }
-      }
+    for (int wv = 0; wv < 4; ++wv) {
+      const float sc = __expf(sm.wm[wv][j] - m);
+      o = fmaf(sc, sm.oacc[wv][idx], o);
+      l = fmaf(sc, sm.wl[wv][j], l);
     }
-    __syncthreads();
-    const int nj = (G - j0 < 4) ? G - j0 : 4;
-    for (int idx = tid; idx < nj * IM_D; idx += (SCORE ? DEC_MT : DEC_MT / 2)) {
-      const int jj = idx >> 7, d = idx & 127, j = j0 + jj;
-      // every wave's partial is relative to its own maximum: rescale to the split's
-      const float m = fmaxf(fmaxf(sm.wm[0][j], sm.wm[1][j]), fmaxf(sm.wm[2][j], sm.wm[3][j]));
-      float o = 0.f, l = 0.f;
-#pragma unroll
-      for (int wv = 0; wv < 4; ++wv) {
-        const float sc = __expf(sm.wm[wv][j] - m);
-        o = fmaf(sc, (sm.oacc[4 * wv][jj][d] + sm.oacc[4 * wv + 1][jj][d]) +
-                     (sm.oacc[4 * wv + 2][jj][d] + sm.oacc[4 * wv + 3][jj][d]), o);
-        l = fmaf(sc, sm.wl[wv][j], l);
-      }
-      prec[j * DEC_REC + 2 + d] = o;
-      if (d == 0) {
-        prec[j * DEC_REC] = m;
-        prec[j * DEC_REC + 1] = l;
-      }
+    prec[j * DEC_REC + 2 + d] = o;
+    if (d == 0) {
+      prec[j * DEC_REC] = m;
+      prec[j * DEC_REC + 1] = l;
     }
   }
   if (tid == 0) {
@@ -1108,7 +1051,7 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
       const int T = 2 * wl + tt;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int vr = 16 * T + 4 * i + kq;
+        const int vr = 16 * T + 4 * kq + i;
         if (vr == cl) *(uint4*)(crec + DEC_CAND_V + 4 * l16) = vf[tt][i];
         if (own_last && vr == ll) *(uint4*)(lrec + DEC_CAND_V + 4 * l16) = vf[tt][i];
       }
@@ -1875,7 +1818,7 @@ __global__ __launch_bounds__(DEC_MT, 4) void k_dec_main(const DecArgs a, const d
 
 // the attend-only variant: same grid, 4 waves per workgroup
 template <int G>
-__global__ __launch_bounds__(DEC_MT / 2, G <= 4 ? 3 : 2) void k_att_main(const DecArgs a) {
+__global__ __launch_bounds__(DEC_MT / 2, 3) void k_att_main(const DecArgs a) {
   __shared__ __attribute__((aligned(16))) DecSplitSmem sm;
   const int U = a.B * a.H_kv;
   dec_split<G, false>(a, blockIdx.x % U, blockIdx.x / U, sm, nullptr, nullptr);
@@ -1901,7 +1844,7 @@ __global__ __launch_bounds__(DEC_TT) void k_dec_tail_head(const DecArgs a) {
 // split workgroups take the new token's rows from the inputs): role blocks first, then the
 // (unit, split) workgroups.  Two launches per layer-step instead of three.
 template <int G>
-__global__ __launch_bounds__(DEC_MT / 2, G <= 4 ? 3 : 2) void k_att_merged(const DecArgs a, const int n_roles) {
+__global__ __launch_bounds__(DEC_MT / 2, 3) void k_att_merged(const DecArgs a, const int n_roles) {
   __shared__ __attribute__((aligned(16))) union SM { DecSplitSmem sm; DecPrepSmem ps; __device__ SM() {} } s;
   const int U = a.B * a.H_kv;
   if ((int)blockIdx.x >= n_roles) {

@@ -202,3 +202,79 @@ __device__ __forceinline__ void copy_to_lds_1k(const char* src, char* dst) {
 }
 template <int N>
 __device__ __forceinline__ void copy_wait() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
+
+// ---- attention of one wave over 32 keys (2 tiles of 16) and up to 8 query heads, on the bf16 matrix cores ----
+// Keys are the rows of the logits' product: lane (l16, kq) holds, in s[tile][r], the logit of head l16 and key
+// 16 tile + 4 kq + r.  That is also the order in which the product P V takes P as its left operand (row = head l16,
+// contraction slots 4 tile + r of lane group kq), so the probabilities stay in their registers.
+typedef __bf16 im_bf8 __attribute__((ext_vector_type(8)));
+typedef float im_c4 __attribute__((ext_vector_type(4)));
+
+// logits of one tile: kf = dims 32 c + 8 kq .. + 7 of key l16, qf = the same of head l16
+__device__ __forceinline__ im_c4 att_logits(const uint4 (&kf)[4], const uint4 (&qf)[4]) {
+  im_c4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+    s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(im_bf8, kf[c]), __builtin_bit_cast(im_bf8, qf[c]), s, 0, 0, 0);
+  return s;
+}
+
+// o[e] += P V: lane (l16, kq) receives, in o[e][r], dim 8 l16 + e of head 4 kq + r.  vf[tile][i] = dims 8 l16 .. + 7 of
+// key 16 tile + 4 kq + i.  P keeps its 24 bits: it enters as three bf16 parts (8 + 8 + 8 bits, exact), so the
+// products are those of fp32 and the sums fp32's.  24 products of 16 cycles and 76 vector instructions per wave, where the same
+// on the vector ALU takes 64 + 64 G.
+__device__ __forceinline__ void att_pv(const float (&pr)[2][4], const uint4 (&vf)[2][4], im_c4 (&o)[8]) {
+  uint4 part[3];
+  float rest[2][4];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) rest[t][r] = pr[t][r];
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {   // the upper halves of two words in one
+    uint32_t w[4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        w[2 * t + h] = __builtin_amdgcn_perm(__float_as_uint(rest[t][2 * h + 1]), __float_as_uint(rest[t][2 * h]), 0x07060302u);
+    part[s] = make_uint4(w[0], w[1], w[2], w[3]);
+    if (s < 2) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rest[t][r] -= __uint_as_float(__float_as_uint(rest[t][r]) & 0xffff0000u);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+    uint32_t w[4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint4 a = vf[t][2 * h], b = vf[t][2 * h + 1];
+        const uint32_t wa = (e >> 1) == 0 ? a.x : (e >> 1) == 1 ? a.y : (e >> 1) == 2 ? a.z : a.w;
+        const uint32_t wb = (e >> 1) == 0 ? b.x : (e >> 1) == 1 ? b.y : (e >> 1) == 2 ? b.z : b.w;
+        w[2 * t + h] = __builtin_amdgcn_perm(wb, wa, sel);
+      }
+    const im_bf8 v = __builtin_bit_cast(im_bf8, make_uint4(w[0], w[1], w[2], w[3]));
+#pragma unroll
+    for (int s = 2; s >= 0; --s)   // small parts first
+      o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(im_bf8, part[s]), v, o[e], 0, 0, 0);
+  }
+}
+
+// leaves o in LDS: dst[head * IM_D + dim] of this wave
+template <int G>
+__device__ __forceinline__ void att_store(const im_c4 (&o)[8], float* dst, int l16, int kq) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (4 * kq + r < G) {
+      float* p = dst + (4 * kq + r) * IM_D + 8 * l16;
+      *(float4*)p = make_float4(o[0][r], o[1][r], o[2][r], o[3][r]);
+      *(float4*)(p + 4) = make_float4(o[4][r], o[5][r], o[6][r], o[7][r]);
+    }
+  }
+}

@@ -1382,15 +1382,8 @@ __global__ __launch_bounds__(256) void k_gather_kept(const bf16_t* __restrict__ 
 #define IM_COMB_LDS 512        // chunks whose maxima and denominators the combine stages in LDS
 
 // grid (chunks, units), 4 waves; wave w owns keys 32 w .. 32 w + 31 of the chunk as 2 tiles of 16.
-// Logits on the bf16 matrix cores: S[key][head] = K_tile Q^T, 16x16x16, fp32 accumulation (operand lane
-// (l16, kq): row l16, k = 4 kq .. 4 kq + 3 of a 16-wide step; a 32-dim chunk c of the rows gives two steps,
-// lane (l16, kq) holding dims 32 c + 8 kq .. + 7 of row l16; result register r of the lane is key 4 kq + r,
-// head l16).  Softmax statistics per wave (relative to the maximum of the wave's own 32 keys), the
-// probabilities through LDS, P V with 16 lanes sharing a V row (8 dims each); the 4 waves' partials are
-// rescaled to the chunk's maximum at the end.
-typedef short im_att_v4s __attribute__((ext_vector_type(4)));
-typedef float im_att_v4f __attribute__((ext_vector_type(4)));
-
+// Logits and P V on the bf16 matrix cores (att_logits, att_pv); softmax statistics per wave (relative to the maximum of
+// the wave's own 32 keys); the 4 waves' partials are rescaled to the chunk's maximum at the end.
 template <int G>
 __global__ __launch_bounds__(256) void k_attn_partial(const bf16_t* __restrict__ K,
                                                       const bf16_t* __restrict__ V,
@@ -1400,8 +1393,7 @@ __global__ __launch_bounds__(256) void k_attn_partial(const bf16_t* __restrict__
                                                       float* __restrict__ part, int n_chunks,
                                                       int32_t* __restrict__ status) {
   __shared__ float s_ml[4][G][2];
-  __shared__ float s_acc[4][G][IM_D];
-  __shared__ float pl[IM_ATT_CHUNK][8];   // probabilities [key][head]
+  __shared__ __attribute__((aligned(16))) float s_acc[4][G][IM_D];
   const int unit = blockIdx.y, chunk = blockIdx.x;
   const int b = unit / H_kv, h = unit % H_kv;
   const int n_true = len[unit / H_set];
@@ -1422,7 +1414,7 @@ __global__ __launch_bounds__(256) void k_attn_partial(const bf16_t* __restrict__
     for (int c = 0; c < 4; ++c) kf[tt][c] = load_stream16(Kb + (size_t)kr * IM_D + 32 * c + 8 * kq);
   }
   {
-    const int jq = min(l16, G - 1);   // lanes past the group read its last head; zeroed where used
+    const int jq = min(l16, G - 1);   // lanes past the group repeat its last head (not used)
 #pragma unroll
     for (int c = 0; c < 4; ++c) qf[c] = *(const uint4*)(q + ((size_t)b * H + h * G + jq) * IM_D + 32 * c + 8 * kq);
   }
@@ -1430,22 +1422,14 @@ __global__ __launch_bounds__(256) void k_attn_partial(const bf16_t* __restrict__
   for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int vr = min(16 * (2 * w + tt) + 4 * i + kq, nk - 1);
+      const int vr = min(16 * (2 * w + tt) + 4 * kq + i, nk - 1);
       vf[tt][i] = load_stream16(Vb + (size_t)vr * IM_D + 8 * l16);
     }
   __asm__ volatile("" ::: "memory");   // keep the loads above the arithmetic, in this order
   float sreg[2][4];
 #pragma unroll
   for (int tt = 0; tt < 2; ++tt) {
-    im_att_v4f acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint4 ka = kf[tt][c], qb = (l16 < G) ? qf[c] : make_uint4(0, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(im_att_v4s, make_uint2(ka.x, ka.y)),
-                                                      __builtin_bit_cast(im_att_v4s, make_uint2(qb.x, qb.y)), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(im_att_v4s, make_uint2(ka.z, ka.w)),
-                                                      __builtin_bit_cast(im_att_v4s, make_uint2(qb.z, qb.w)), acc, 0, 0, 0);
-    }
+    const im_c4 acc = att_logits(kf[tt], qf);
 #pragma unroll
     for (int r = 0; r < 4; ++r)   // this lane: head l16, key 16 (2 w + tt) + 4 kq + r
       sreg[tt][r] = (16 * (2 * w + tt) + 4 * kq + r < nk) ? acc[r] * scale : -INFINITY;
@@ -1459,48 +1443,14 @@ __global__ __launch_bounds__(256) void k_attn_partial(const bf16_t* __restrict__
   for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float p = (sreg[tt][r] == -INFINITY) ? 0.f : __expf(sreg[tt][r] - mw);
-      lsum += p;
-      if (l16 < 8) pl[16 * (2 * w + tt) + 4 * kq + r][l16] = p;
+      sreg[tt][r] = __expf(sreg[tt][r] - mw);   // (exp(-inf) = 0)
+      lsum += sreg[tt][r];
     }
   lsum = rows_sum_f(lsum);
   if (kq == 0 && l16 < G) { s_ml[w][l16][0] = mw; s_ml[w][l16][1] = lsum; }
-  // the probabilities just written are this wave's own keys: read back without a workgroup barrier
-  // (LDS operations of one wave complete in order)
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  float acc[G][8];
-#pragma unroll
-  for (int j = 0; j < G; ++j)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[j][e] = 0.f;
-#pragma unroll
-  for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int kl = 16 * (2 * w + tt) + 4 * i + kq;
-      float pv[8];
-      *(float4*)&pv[0] = *(const float4*)&pl[kl][0];
-      if (G > 4) *(float4*)&pv[4] = *(const float4*)&pl[kl][4];
-      const uint4 u = vf[tt][i];
-      const float v[8] = {bf_lo(u.x), bf_hi(u.x), bf_lo(u.y), bf_hi(u.y),
-                          bf_lo(u.z), bf_hi(u.z), bf_lo(u.w), bf_hi(u.w)};
-#pragma unroll
-      for (int j = 0; j < G; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[j][e] = fmaf(pv[j], v[e], acc[j][e]);
-    }
-  // the wave's 4 key streams (the same lane of the four 16-lane rows) share the wave's maximum: plain sums
-#pragma unroll
-  for (int j = 0; j < G; ++j) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[j][e] = rows_sum_f(acc[j][e]);
-    if (kq == 0) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s_acc[w][j][l16 * 8 + e] = acc[j][e];
-    }
-  }
+  im_c4 o[8] = {};
+  att_pv(sreg, vf, o);
+  att_store<G>(o, &s_acc[w][0][0], l16, kq);
   __syncthreads();
   for (int idx = tid; idx < G * IM_D; idx += 256) {
     const int j = idx >> 7, d = idx & 127;
