@@ -1003,7 +1003,7 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
         for (int c = 0; c < 4; ++c) *(uint4*)(lrec + DEC_CAND_K + 16 * c + 4 * kq) = kf[tt][c];
       }
     }
-    im_c4 o[8] = {};
+    im_c4 o[8];
     att_pv(sreg, vf, o);
     att_store<G>(o, sm.oacc[wl], l16, kq);
     if (!SCORE && do_x_any && tid < G)   // the leftover key's logits: the 4 waves' partial dot products

@@ -219,7 +219,23 @@ __device__ __forceinline__ im_c4 att_logits(const uint4 (&kf)[4], const uint4 (&
   return s;
 }
 
-// o[e] += P V: lane (l16, kq) receives, in o[e][r], dim 8 l16 + e of head 4 kq + r.  vf[tile][i] = dims 8 l16 .. + 7 of
+// dim 8 l16 + e of the lane group's 8 keys
+__device__ __forceinline__ im_bf8 att_column(const uint4 (&vf)[2][4], int e) {
+  const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+  uint32_t w[4];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint4 a = vf[t][2 * h], b = vf[t][2 * h + 1];
+      const uint32_t wa = (e >> 1) == 0 ? a.x : (e >> 1) == 1 ? a.y : (e >> 1) == 2 ? a.z : a.w;
+      const uint32_t wb = (e >> 1) == 0 ? b.x : (e >> 1) == 1 ? b.y : (e >> 1) == 2 ? b.z : b.w;
+      w[2 * t + h] = __builtin_amdgcn_perm(wb, wa, sel);
+    }
+  return __builtin_bit_cast(im_bf8, make_uint4(w[0], w[1], w[2], w[3]));
+}
+
+// o[e] = P V: lane (l16, kq) receives, in o[e][r], dim 8 l16 + e of head 4 kq + r.  vf[tile][i] = dims 8 l16 .. + 7 of
 // key 16 tile + 4 kq + i.  P keeps its 24 bits: it enters as three bf16 parts (8 + 8 + 8 bits, exact), so the
 // products are those of fp32 and the sums fp32's.  24 products of 16 cycles and 76 vector instructions per wave, where the same
 // on the vector ALU takes 64 + 64 G.
@@ -248,21 +264,25 @@ __device__ __forceinline__ void att_pv(const float (&pr)[2][4], const uint4 (&vf
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-    uint32_t w[4];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint4 a = vf[t][2 * h], b = vf[t][2 * h + 1];
-        const uint32_t wa = (e >> 1) == 0 ? a.x : (e >> 1) == 1 ? a.y : (e >> 1) == 2 ? a.z : a.w;
-        const uint32_t wb = (e >> 1) == 0 ? b.x : (e >> 1) == 1 ? b.y : (e >> 1) == 2 ? b.z : b.w;
-        w[2 * t + h] = __builtin_amdgcn_perm(wb, wa, sel);
-      }
-    const im_bf8 v = __builtin_bit_cast(im_bf8, make_uint4(w[0], w[1], w[2], w[3]));
+    const im_bf8 v = att_column(vf, e);
+    o[e] = im_c4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 2; s >= 0; --s)   // small parts first
       o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(im_bf8, part[s]), v, o[e], 0, 0, 0);
+  }
+  // an infinity in V times a part that is zero gives NaN where the whole of P gives an infinity: there the first part,
+  // which is zero only with P, decides
+  float any = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) any += (o[e][0] + o[e][1]) + (o[e][2] + o[e][3]);
+  if (__any(any != any)) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const im_c4 h = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(im_bf8, part[0]), att_column(vf, e),
+                                                             im_c4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[e][r] = (o[e][r] != o[e][r]) ? h[r] : o[e][r];
+    }
   }
 }
 

@@ -7,6 +7,7 @@
 // 256), give the exact sum of X W: a third of the time of the fp64 cores.  Elements more than 2^22 below their
 // row's largest lose bits in X: they are listed with their remainder (1 in 2.6 million for Gaussian values) and
 // added in fp64 afterwards; should a list overflow, the fp64 kernel computes the product instead.
+// (A matrix with an infinity or a NaN counts as an overflowed list.)
 //   k_exact_prep : row exponents of A; exponents and digit planes of B
 //   k_exact_gemm : the product
 //   k_exact_fix  : remainders
@@ -116,7 +117,10 @@ __global__ __launch_bounds__(256) void k_exact_prep(const bf16_t* __restrict__ A
   for (int i = 0; i < XG_MAX_K / 512; ++i)
     if (i * 512 < K) e = exact_max_exp(v[i], e);
   e = exact_clamp_exp((int)wave_max_u((uint32_t)e));
-  if (lane == 0) (isb ? expB : expA)[row] = e;
+  if (lane == 0) {
+    (isb ? expB : expA)[row] = e;
+    if (e == 255) atomicOr(lists.count + (isb ? 1 : 0), 1 << 30);   // an infinity or a NaN: the fp64 kernel's case
+  }
   const float scale = row < N || !isb ? exact_scale(e) : 0.f;
 #pragma unroll
   for (int i = 0; i < XG_MAX_K / 512; ++i) {

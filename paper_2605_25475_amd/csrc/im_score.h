@@ -132,9 +132,15 @@ __global__ __launch_bounds__(256) void k_score_features(const double* __restrict
     sane = sane && score_sane(cn);
     err += (1.001f * sqrtf(r2) + 0x1p-16f * cn * f) / f;
     sane = __all(sane && isfinite(err));
-    if (lane < DI) *(_Float16*)(sb + HM * SB::HEAD + place + m * (DI == 64 ? 16 : 8)) = hv;
+    if (lane < DI) *(_Float16*)(sb + HM * SB::HEAD + place + m * (DI == 64 ? 16 : 8)) = sane ? hv : (_Float16)0.f;
+    if (!sane) {   // (operands of zero: infinities and NaN stay out of the sum, whose bound is then infinite)
+      for (int j = hl; j < H_idx; j += HP) {
+        *(_Float16*)(sb + j * SB::HEAD + place + m * (DI == 64 ? 16 : 8)) = (_Float16)0.f;
+        if (d == 0) rows[j * 16 + m] = 0.f;
+      }
+    }
     if (lane == 0) {
-      rows[SB::T * 16 + m] = 1.f / f;
+      rows[SB::T * 16 + m] = sane ? 1.f / f : 0.f;
       rows[SB::ERR * 16 + m] = sane ? 1.01f * 4096.f * err : INFINITY;   // out of range: always a candidate
       ((int*)rows)[SB::POS * 16 + m] = q_pos[row];
     }
@@ -144,7 +150,9 @@ __global__ __launch_bounds__(256) void k_score_features(const double* __restrict
   for (int i = tid; i < SB::BYTES / 16; i += 256) dst[i] = ((const uint4*)sb)[i];
 }
 
-// a key's fp16 operand for one lane (dims DPL kq .. of the key), scaled so that the key's norm is in [2^11, 2^12)
+// a key's fp16 operand for one lane (dims DPL kq .. of the key), scaled so that the key's norm is in [2^11, 2^12).
+// A key with infinities, NaN or a norm of 2^100 has no bounds: its scale and its products are NaN, and every query is a
+// candidate.
 template <int DI>
 struct ScoreKey {
   im_h8 h[DI == 64 ? 2 : 1];   // (DI = 16: 4 values, in the lower half)
@@ -166,13 +174,14 @@ __device__ __forceinline__ ScoreKey<DI> score_key_operand(const bf16_t* __restri
   float n2 = 0.f;
 #pragma unroll
   for (int i = 0; i < DI / 4; ++i) n2 = fmaf(f[i], f[i], n2);
-  o.scale = score_scale(sqrtf(rows_sum_f(n2)) * 1.0001f);
+  const float norm = sqrtf(rows_sum_f(n2)) * 1.0001f;
+  o.scale = norm < 0x1p100f ? score_scale(norm) : NAN;
   if constexpr (DI == 16) {
 #pragma unroll
     for (int i = 4; i < 8; ++i) o.h[0][i] = (_Float16)0.f;
   }
 #pragma unroll
-  for (int i = 0; i < DI / 4; ++i) o.h[i / 8][i % 8] = score_half(f[i] * o.scale);
+  for (int i = 0; i < DI / 4; ++i) o.h[i / 8][i % 8] = score_half(f[i] * o.scale);   // (NaN stays NaN)
   return o;
 }
 
@@ -220,12 +229,13 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_scan(const bf16_
   const int kbase = t0 + 16 * TPW * w;
   ScoreKey<DI> key[TPW];
   int posk[TPW];
-  int mn = INT_MAX, mx = INT_MIN;
+  int mn = INT_MAX, mx = INT_MIN, wild = 0;
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {   // (keys past the end repeat the last live one; their records are not written)
     const int k = min(kbase + 16 * t + l16, n - 1);
     key[t] = score_key_operand<DI>(Kidx + ((size_t)unit * C + k) * DI, kq);
     posk[t] = pos[(size_t)unit * C + k];
+    wild |= (key[t].scale != key[t].scale) ? 1 << t : 0;
     mn = min(mn, posk[t]);
     mx = max(mx, posk[t]);
   }
@@ -313,6 +323,7 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_scan(const bf16_
     const int k = kbase + 16 * t + l16;
     if (k < n) {
       const size_t at = (((size_t)blockIdx.y * units + unit) * rec_live + k) * 4 + kq;
+      if ((wild >> t & 1) && b_hi > b_lo) { u1[t] = u2[t] = INFINITY; i1[t] = b_lo; }   // (its maxima were of NaN)
       rec_u[at] = make_float2(u1[t], u2[t]);
       rec_i[at] = i1[t];
     }
@@ -520,8 +531,9 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_listed(const bf1
           for (int r = 0; r < 4; ++r) acc[r] = fmaf(a4[i][r], fabsf(zz[i][r]), acc[r]);
       }
       const float bar = best * key.scale;
-      const bool hit = (qp.x >= pk && acc[0] > bar) || (qp.y >= pk && acc[1] > bar) || (qp.z >= pk && acc[2] > bar) ||
-                       (qp.w >= pk && acc[3] > bar);
+      // (negated: a key without bounds is a hit)
+      const bool hit = (qp.x >= pk && !(acc[0] <= bar)) || (qp.y >= pk && !(acc[1] <= bar)) ||
+                       (qp.z >= pk && !(acc[2] <= bar)) || (qp.w >= pk && !(acc[3] <= bar));
       unsigned long long hits = __ballot(hit);
       if (!hits) continue;
       if (__popcll(hits) <= 4) {   // (usual) lane by lane: its 4 queries against its key, as k_score_exact does it

@@ -110,3 +110,74 @@ def test_query_projection_as_an_exact_product(heads, n_q, shared, share_q, share
         torch.cuda.synchronize()
         got = g.scores[..., :n].cpu().numpy().astype(np.float64)
         assert np.array_equal(got, want), f"{int((got != want).sum())} of {want.size} scores differ"
+
+
+@pytest.mark.parametrize("n_q,n", [(33, 300), (1089, 70)], ids=["fp64-projection", "exact-product"])
+@pytest.mark.parametrize("shared", [False, True], ids=["per-unit", "head-shared"])
+def test_infinities_and_nan_count_as_no_similarity(shared, n_q, n):
+    """A non-finite row has NaN features; ReLU takes a NaN similarity as 0, so a query or key with one scores like a
+    row of zeros (which the oracle gets), and a query whose gates are NaN counts for no key."""
+    kw = dict(context=max(n, n_q), budget=n, decode_steps=0, batch=2, n_layers=1)
+    w = WORKLOADS["cfg1"].shared(**kw) if shared else WORKLOADS["cfg1"].scaled(**kw)
+    ls = (LockStepShared if shared else LockStep)(w)
+    g, ref, d = ls.gpu, ls.ref, (lambda t: t.cuda())
+    k, v = ls.K[:, :, :n].contiguous(), ls.V[:, :, :n].contiguous()
+    pos = torch.arange(n, dtype=torch.int32).repeat(w.batch, 1).contiguous()
+    q = ls.Q[:, :n_q].contiguous()
+    xg = q.view(w.batch, n_q, -1).clone()
+    qpos = (torch.arange(n_q, dtype=torch.int32) % (n + 3)).repeat(w.batch, 1).contiguous()
+    inf, nan = float("inf"), float("nan")
+    bad = torch.tensor([inf, -inf, nan], dtype=torch.bfloat16)
+    q0, k0, qpos0 = q.clone(), k.clone(), qpos.clone()
+    for i, s in enumerate((0, 7, n_q - 1)):
+        q[0, s, i, 5 * i] = bad[i]
+        q0[0, s] = 0
+    for i, t in enumerate((0, 31, n - 1)):
+        k[1, :, t, 9 * i] = bad[i]
+        k0[1, :, t] = 0
+    xg0 = xg.clone()
+    xg[1, 3, 0] = nan
+    xg0[1, 3] = 0
+    qpos0[1, 3] = -10 ** 6
+    if shared:   # (indexer keys come from the hidden state)
+        x = ls.X[:, :n].contiguous()
+        x0 = x.clone()
+        for i, t in enumerate((0, 31, n - 1)):
+            x[1, t, 9 * i] = bad[i]
+            x0[1, t] = 0
+        im.im_append_kv_hidden(ls.handle, ls.params, g.st, d(k), d(v), d(x), d(pos))
+        ref.append_kv_hidden(f64(k0), f64(v), f64(x0), pos.numpy())
+    else:
+        im.im_append_kv(ls.handle, g.st, d(k), d(v), d(pos))
+        ref.append_kv(f64(k0), f64(v), pos.numpy())
+    im.im_set_max_live(ls.handle, n)
+    want = ref.index_score(f64(q0), f64(xg0), qpos0.numpy())[..., :n]
+    for _ in range(2):
+        g.scores.fill_(7.0)
+        im.im_index_score(ls.handle, ls.params, g.st, d(q), d(xg), d(qpos), g.scores)
+        torch.cuda.synchronize()
+        got = g.scores[..., :n].cpu().numpy().astype(np.float64)
+        assert np.array_equal(got, want), f"{int((got != want).sum())} of {want.size} scores differ"
+
+
+@pytest.mark.parametrize("call", ["steps", "attend"])
+def test_an_infinity_in_a_value_row_reaches_the_output_as_one(call):
+    """P enters the product P V in three parts; a part that is zero times an infinity is not what P times it is."""
+    w = WORKLOADS["cfg1"].scaled(context=200, budget=200, decode_steps=1, batch=1, n_layers=1)
+    ls = LockStep(w, capacity=256)
+    d = lambda t: t.contiguous().cuda()
+    v = ls.V[:, :, :200].clone()
+    v[0, 0, 17, 3], v[0, 1, 150, 64] = float("inf"), -float("inf")
+    pos = torch.arange(201, dtype=torch.int32).repeat(1, 1)
+    im.im_append_kv(ls.handle, ls.gpu.st, d(ls.K[:, :, :200]), d(v), d(pos[:, :200]))
+    out = torch.zeros((1, w.n_q_heads, 128), dtype=torch.bfloat16, device="cuda")
+    if call == "steps":
+        im.im_decode_attn_with_readout(ls.handle, ls.params, ls.gpu.st, d(ls.Q[:, 200]), out)
+    else:
+        im.im_attend_step(ls.handle, ls.params, ls.gpu.st, d(ls.Q[:, 200]), d(ls.K[:, :, 200:]), d(ls.V[:, :, 200:]),
+                          d(pos[0, 200:]), out)
+    torch.cuda.synchronize()
+    got = out.float().cpu().view(w.n_kv_heads, -1, 128)
+    want = torch.zeros_like(got)
+    want[0, :, 3], want[1, :, 64] = float("inf"), -float("inf")
+    assert torch.equal(torch.where(torch.isfinite(got), torch.zeros_like(got), got), want)
