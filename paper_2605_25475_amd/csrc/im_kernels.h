@@ -902,7 +902,8 @@ __device__ __forceinline__ int im_mem_blocks_per_split(int ne, int fold_block, i
   return (blocks + n_split - 1) / n_split;
 }
 
-// grid (n_split, units), 4 waves.  Two chained bf16 MFMA products per tile of 32 evicted rows:
+// grid (units, n_split), 4 waves (units first: where few splits have rows, those of all units still spread over the
+// XCDs).  Two chained bf16 MFMA products per tile of 32 evicted rows:
 //   Phi^T[c][i] = sum_d W[c][d] K_i[d]            (wave w owns memory rows c = 32 w .. 32 w + 31)
 //   M[c][d]    += sum_i Phi[i][c] V_i[d]          (Phi split into hi + lo bf16 parts, so the
 //                                                  product carries 16 mantissa bits of Phi)
@@ -917,7 +918,7 @@ __global__ __launch_bounds__(256) void k_mem_partial(const bf16_t* __restrict__ 
                                                      float* __restrict__ part) {
   __shared__ float Ps[IM_DM][IM_MEM_TOK + 1];                                  // Phi^T [c][row]
   __shared__ __attribute__((aligned(16))) bf16_t Vs[IM_MEM_TOK][IM_D + 8];     // V rows of the tile
-  const int unit = blockIdx.y, split = blockIdx.x, tid = threadIdx.x;
+  const int unit = blockIdx.x, split = blockIdx.y, tid = threadIdx.x;
   const int ne = n_evict[unit];
   if (ne <= IM_MEM_FEW) return;
   const int bps = im_mem_blocks_per_split(ne, fold_block, n_split);
@@ -1038,7 +1039,7 @@ __global__ __launch_bounds__(256) void k_mem_partial(const bf16_t* __restrict__ 
 // are summed across heads per token): Phi^T = sum_h W K_h and M += sum_h Phi V_h by linearity, so
 // the sums over heads are taken inside the two products' accumulators and no summed row is ever
 // rounded.  K, V are per unit (set * H_set + head); lists, counts and the partials per set.
-// grid (n_split, sets), 4 waves.
+// grid (sets, n_split), 4 waves.
 __global__ __launch_bounds__(256) void k_mem_partial_sets(const bf16_t* __restrict__ K,
                                                           const bf16_t* __restrict__ V,
                                                           const int32_t* __restrict__ evict_idx,
@@ -1048,7 +1049,7 @@ __global__ __launch_bounds__(256) void k_mem_partial_sets(const bf16_t* __restri
                                                           float* __restrict__ part) {
   __shared__ float Ps[IM_DM][IM_MEM_TOK + 1];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[IM_MEM_TOK][IM_D + 8];
-  const int set = blockIdx.y, split = blockIdx.x, tid = threadIdx.x;
+  const int set = blockIdx.x, split = blockIdx.y, tid = threadIdx.x;
   const int ne = n_evict[set];
   if (ne <= IM_MEM_FEW) return;
   const int bps = im_mem_blocks_per_split(ne, fold_block, n_split);
@@ -1251,8 +1252,14 @@ __global__ __launch_bounds__(256) void k_mem_finalize(float* __restrict__ M, flo
   const int bps = im_mem_blocks_per_split(ne, fold_block, n_split);
   const int active = ((ne + fold_block - 1) / fold_block + bps - 1) / bps;
   float s = 0.f;
-  for (int sp = 0; sp < active; ++sp)
-    s += part[((size_t)unit * n_split + sp) * (IM_DM * IM_D + IM_DM) + e];
+  const float* src = part + (size_t)unit * n_split * (IM_DM * IM_D + IM_DM) + e;
+  for (int s0 = 0; s0 < active; s0 += 8) {   // 8 partials in flight (one past the end repeats the last, unused)
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = src[(size_t)min(s0 + i, active - 1) * (IM_DM * IM_D + IM_DM)];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += (s0 + i < active) ? v[i] : 0.f;
+  }
   float* dst = (e < IM_DM * IM_D) ? (M + (size_t)unit * IM_DM * IM_D + e)
                                   : (bvec + (size_t)unit * IM_DM + (e - IM_DM * IM_D));
   *dst = fmaf(lambda, *dst, eta * s);

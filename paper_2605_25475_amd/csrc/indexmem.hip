@@ -116,11 +116,22 @@ bool exact_fits(const im_config* c, long long M) {
   return K <= XG_MAX_K && M < (1 << 30) && ((M + 15) / 16) * ((N + 15) / 16) > 2048;
 }
 
+size_t n_sets_of(const im_config* c) { return (size_t)c->batch * (c->head_shared ? 1 : c->n_kv_heads); }
+
+// Splits of a set's evicted rows over workgroups (k_mem_partial*), `live` bounding their number: as many as give the 512
+// workgroups that the chip holds, of at least 64 rows (sets of several heads: 1024, of 32 rows of every head; 8 sets x 3072
+// rows x 8 heads: 99 us with 256 workgroups, 105 with 384, 86 with 768).  A tile of 32 rows
+// takes a workgroup 5 us per head, a partial of 64 KB far less.  8 units x 1167 rows: 2 splits 79 us, 24 splits 14 us;
+// 8 units x 4096 rows: 8 splits 68 us, 64 splits 23 us.
+int mem_splits(const im_config* c, long long live) {
+  const long long sets = n_sets_of(c), rows = c->head_shared ? 32 : 64;
+  const long long n = (live + rows - 1) / rows, most = ((c->head_shared ? 1024 : 512) + sets - 1) / sets;
+  return (int)(n < most ? n : most);
+}
+
 void layout(const im_config* c, im_handle* h) {
   const size_t B = c->batch, Hi = c->n_idx_heads, units = (size_t)c->batch * c->n_kv_heads;
-  h->mem_split = (c->capacity + 1023) / 1024;
-  if (h->mem_split < 1) h->mem_split = 1;
-  if (h->mem_split > 32) h->mem_split = 32;
+  h->mem_split = mem_splits(c, c->capacity);
   h->attn_chunks = (c->capacity + IM_ATT_CHUNK - 1) / IM_ATT_CHUNK;
   size_t off = 0;
   // status word (in a 32-word slot of its own), then one newest-position word per unit
@@ -128,7 +139,7 @@ void layout(const im_config* c, im_handle* h) {
   h->dec_splits = (c->capacity + DEC_KEYS - 1) / DEC_KEYS + 1;   // + the last-slot record
   h->off_qy = off;     off = align256(off + B * c->max_queries * Hi * IM_DI * sizeof(double));
   h->off_alpha = off;  off = align256(off + B * c->max_queries * Hi * sizeof(double));
-  h->off_mem = off;    off = align256(off + units * h->mem_split * (IM_DM * IM_D + IM_DM) * sizeof(float));
+  h->off_mem = off;    off = align256(off + (size_t)n_sets_of(c) * h->mem_split * (IM_DM * IM_D + IM_DM) * sizeof(float));
   h->off_attn = off;   off = align256(off + B * c->n_q_heads * h->attn_chunks * IM_ATT_REC * sizeof(float));
   h->off_dpart = off;  off = align256(off + units * h->dec_splits * DEC_GMAX * DEC_REC * sizeof(float));  // upper bound: G <= 8
   h->off_dcand = off;  off = align256(off + units * h->dec_splits * DEC_CAND * sizeof(uint32_t));
@@ -545,19 +556,18 @@ int32_t im_memory_update(im_handle* h, const im_params* p, const im_state* st,
   const im_config& c = h->cfg;
   const int units = n_sets(c);
   float* part = (float*)(h->ws + h->off_mem);
-  // (the partials' buffer holds mem_split records per (batch element, KV head): a set of H_kv heads has
-  // one memory, so its rows can go to H_kv times as many splits; with only `batch` sets the launch needs them)
-  const int n_split = c.head_shared ? h->mem_split * c.n_kv_heads : h->mem_split;
+  // (a tile of a set holds the rows of all its heads: its splits may be shorter than a fold block)
+  const int n_split = mem_splits(&c, h->max_live), fold = c.head_shared ? IM_MEM_TOK : c.fold_block;
   if (c.head_shared)
-    k_mem_partial_sets<<<dim3(n_split, units), 256, 0, s>>>(
+    k_mem_partial_sets<<<dim3(units, n_split), 256, 0, s>>>(
         (const bf16_t*)st->K, (const bf16_t*)st->V, evict_idx, n_evict, (const bf16_t*)p->Wtheta,
-        c.capacity, c.n_kv_heads, c.fold_block, n_split, part);
+        c.capacity, c.n_kv_heads, fold, n_split, part);
   else
-    k_mem_partial<<<dim3(n_split, units), 256, 0, s>>>(
+    k_mem_partial<<<dim3(units, n_split), 256, 0, s>>>(
         (const bf16_t*)st->K, (const bf16_t*)st->V, evict_idx, n_evict, (const bf16_t*)p->Wtheta,
-        c.capacity, c.fold_block, n_split, part);
+        c.capacity, fold, n_split, part);
   k_mem_finalize<<<dim3((IM_DM * IM_D + IM_DM + 255) / 256, units), 256, 0, s>>>(
-      st->M, st->b, n_evict, part, c.fold_block, n_split, lambda, eta, (const bf16_t*)st->K,
+      st->M, st->b, n_evict, part, fold, n_split, lambda, eta, (const bf16_t*)st->K,
       (const bf16_t*)st->V, evict_idx, (const bf16_t*)p->Wtheta, c.capacity, heads_per_set(c));
   return launch_check(h, "im_memory_update");
 }
