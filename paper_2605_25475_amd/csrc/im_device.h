@@ -178,6 +178,39 @@ __device__ __forceinline__ void wave_sums_butterfly_d(const double* v, double* s
   }
 }
 
+// the same for floats
+template <int NV>
+__device__ __forceinline__ void wave_sums_butterfly_f(const float* v, float* s) {
+  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+  float r[NV / 2];
+#pragma unroll
+  for (int i = 0; i < NV / 2; ++i) {
+    const u2 p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2 * i]), __float_as_uint(v[2 * i + 1]), false, false);
+    r[i] = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < NV / 4; ++i) {
+    const u2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(r[2 * i]), __float_as_uint(r[2 * i + 1]), false, false);
+    float t = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    t += dpp_zero_f<0x111, 0xF>(t);
+    t += dpp_zero_f<0x112, 0xF>(t);
+    t += dpp_zero_f<0x114, 0xF>(t);
+    t += dpp_zero_f<0x118, 0xF>(t);
+    s[i] = t;
+  }
+}
+// the lane that holds value j of a butterfly's register j / 4, and reads of one lane
+__device__ __forceinline__ constexpr int head_lane(int j) { return 16 * (((j >> 1) & 1) | ((j & 1) << 1)) + 15; }
+__device__ __forceinline__ float readlane_f(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ double readlane_d(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 // v + (the same lane of the other 32-lane half), in every lane
 __device__ __forceinline__ float halves_sum_f(float v) {
   typedef unsigned int u2 __attribute__((ext_vector_type(2)));

@@ -52,75 +52,123 @@ __device__ __forceinline__ _Float16 score_half(float x) {
   return (fabsf(x) < 6.103515625e-05f) ? (_Float16)0.f : (_Float16)x;
 }
 
-// grid (ceil(n_q / 16), B), 256 threads: one block of 16 queries, each wave 4 of them in turn.
+// grid (ceil(n_q / 16), B), 16 waves: one block of 16 queries, one per wave.
 // qraw [B n_q, H_idx, DI], araw [B n_q, H_idx]: the raw projections (fp64).  qf: the normalised features (fp32, as
 // the exact evaluation reads them), al16 [B n_q, 16]: alpha (fp32, zero past H_idx).
-// A lane holds dim lane % DI of head (pass * 64 / DI + lane / DI).  The block's operands are put together in LDS and
-// leave in one piece.  HBM-bound: reads 8 and writes 6 bytes per feature.
+// Lane: dim lane % DI of head (pass * 64 / DI + lane / DI), all heads' loads first.  Per-head sums: at DI = 64 for all heads at
+// once by a butterfly (head h of it: lane 15 of row rho of register i, 4 i + 2 (rho & 1) + (rho >> 1)), so that roots, scales
+// and bounds are taken once per 4 heads; at DI = 16 inside the 16-lane rows.  The block's operands are put together
+// in LDS and leave in one piece.  Bound: reads 8 and writes 6 bytes per feature; a short prompt's few workgroups: one
+// chain of latencies (a wave with 4 queries and 8 heads in turn took 27 us for 562 queries, 192 us for 65536).
 template <int DI, int HM>
-__global__ __launch_bounds__(256) void k_score_features(const double* __restrict__ qraw, const double* __restrict__ araw,
-                                                        const int32_t* __restrict__ q_pos,
-                                                        const bf16_t* __restrict__ norm_w, float rms_eps,
-                                                        double alpha_denom, int n_q, int H_idx,
-                                                        float* __restrict__ qf, float* __restrict__ al16,
-                                                        char* __restrict__ blocks, int32_t* __restrict__ n_listed,
-                                                        int32_t* __restrict__ exact_count) {
+__global__ __launch_bounds__(1024) void k_score_features(const double* __restrict__ qraw, const double* __restrict__ araw,
+                                                         const int32_t* __restrict__ q_pos,
+                                                         const bf16_t* __restrict__ norm_w, float rms_eps,
+                                                         double alpha_denom, int n_q, int H_idx,
+                                                         float* __restrict__ qf, float* __restrict__ al16,
+                                                         char* __restrict__ blocks, int32_t* __restrict__ n_listed,
+                                                         int32_t* __restrict__ exact_count) {
   using SB = ScoreBlock<DI, HM>;
-  constexpr int HP = 64 / DI;             // heads per pass of a wave
+  constexpr int HP = 64 / DI, NP = HM / HP;   // heads per pass of a wave, passes
   __shared__ __attribute__((aligned(16))) char sb[SB::BYTES];
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, b = blockIdx.y, d = lane % DI, hl = lane / DI;
+  const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.y, d = lane % DI, hl = lane / DI;
+  const int m = __builtin_amdgcn_readfirstlane(tid >> 6), s = blockIdx.x * 16 + m;
+  const size_t row = (size_t)b * n_q + min(s, n_q - 1);
+  // all loads first (absent heads repeat the last, unused)
+  double v[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) v[i] = qraw[(row * H_idx + min(i * HP + hl, H_idx - 1)) * DI + d];
+  const double a_raw = araw[row * H_idx + min(lane & 15, H_idx - 1)];
+  const float nw = norm_w ? bf2f(norm_w[d]) : 1.f;
+  const int my_pos = q_pos[row];
   if (blockIdx.x == 0 && tid == 0) n_listed[b] = 0;
   if (blockIdx.x == 0 && b == 0 && tid < 2) exact_count[tid] = 0;   // (the product's lists have been used)
-  for (int i = tid; i < SB::BYTES / 4; i += 256) ((uint32_t*)sb)[i] = 0;
+  for (int i = tid; i < SB::BYTES / 4; i += 1024) ((uint32_t*)sb)[i] = 0;
   __syncthreads();
   float* rows = (float*)(sb + SB::OFF);
-  const float nw = norm_w ? bf2f(norm_w[d]) : 1.f;
   // place of dim d in a head's operand: lane (m, kq) holds dims DI/4 kq .. of query m, in steps of 8 (DI = 64)
   constexpr int DPL = DI / 4;
   const int kq = d / DPL, e = d % DPL;
-  const int place = (DI == 64) ? (e / 8) * 1024 + kq * 256 + (e % 8) * 2 : kq * 128 + e * 2;   // + m * 16 (DI = 64), m * 8
-  for (int i = 0; i < 4; ++i) {
-    const int m = 4 * w + i, s = blockIdx.x * 16 + m;
-    if (s >= n_q) {
-      if (lane == 0) { rows[SB::ERR * 16 + m] = -INFINITY; ((int*)rows)[SB::POS * 16 + m] = INT_MAX; }
-      continue;
-    }
-    const size_t row = (size_t)b * n_q + s;
-    if (lane < 16) {
-      const double a = (lane < H_idx) ? araw[row * H_idx + lane] / alpha_denom : 0.0;
-      al16[row * 16 + lane] = (float)a;
-    }
+  const int place = ((DI == 64) ? (e / 8) * 1024 + kq * 256 + (e % 8) * 2 : kq * 128 + e * 2) + m * (DI == 64 ? 16 : 8);
+  if (s >= n_q) {
+    if (lane == 0) { rows[SB::ERR * 16 + m] = -INFINITY; ((int*)rows)[SB::POS * 16 + m] = INT_MAX; }
+  } else {
+    const float al_l = (float)(a_raw / alpha_denom);   // of head lane % 16
+    if (lane < 16) al16[row * 16 + lane] = (lane < H_idx) ? al_l : 0.f;
     double c = 0.0;                       // this lane's share of c[d]
-    float err = 0.f;                      // sum of the heads' terms (per head group hl)
+    float err = 0.f;                      // sum of the heads' terms
     bool sane = true;
-    for (int j0 = 0; j0 < H_idx; j0 += HP) {
-      const int j = j0 + hl;
-      const bool on = j < H_idx;
-      const int jj = min(j, H_idx - 1);
-      const double v = qraw[(row * H_idx + jj) * DI + d];
-      const float al = on ? (float)(araw[row * H_idx + jj] / alpha_denom) : 0.f;
-      double ss = v * v;
-      if constexpr (DI == 64) ss = wave_sum_d(ss); else ss = row16_sum_d(ss);
-      const double rr = sqrt(ss / (double)DI + (double)rms_eps);
-      const float q = (float)(v / rr * (double)nw);
-      if (on) qf[(row * H_idx + j) * DI + d] = q;
-      float n2 = q * q;
-      if constexpr (DI == 64) n2 = wave_sum_f(n2); else n2 = row16_sum_f(n2);
-      const float norm = sqrtf(n2) * 1.0001f, f = score_scale(norm);
-      const _Float16 hv = score_half(q * f);
-      const float r = q * f - (float)hv;
-      float r2 = r * r;
-      if constexpr (DI == 64) r2 = wave_sum_f(r2); else r2 = row16_sum_f(r2);
-      const float a = 0.5f * al / f;
-      sane = sane && score_sane(al) && score_sane(norm);
-      err += fabsf(a) * (1.001f * sqrtf(r2) + 0x1p-16f * norm * f);
-      c = fma(0.5 * (double)al, (double)q, c);
-      if (on) {
-        *(_Float16*)(sb + j * SB::HEAD + place + m * (DI == 64 ? 16 : 8)) = hv;
-        if (d == 0) rows[j * 16 + m] = a;
+    float q[NP];
+    if constexpr (DI == 64) {
+      constexpr int NR = HM / 4;          // registers of the butterfly
+      const int rho = lane >> 4;
+      const bool holds = (lane & 15) == 15;
+      double sq[HM], ss[NR];
+#pragma unroll
+      for (int j = 0; j < HM; ++j) sq[j] = v[j] * v[j];
+      wave_sums_butterfly_d<HM>(sq, ss);
+#pragma unroll
+      for (int i = 0; i < NR; ++i) ss[i] = sqrt(ss[i] / (double)DI + (double)rms_eps);
+      float t[HM], n2[NR], r2[NR], sc[NR];
+#pragma unroll
+      for (int j = 0; j < HM; ++j) {
+        q[j] = (float)(v[j] / readlane_d(ss[j >> 2], head_lane(j)) * (double)nw);
+        t[j] = q[j] * q[j];
+        if (j < H_idx) c = fma(0.5 * (double)readlane_f(al_l, j), (double)q[j], c);
       }
+      wave_sums_butterfly_f<HM>(t, n2);
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        n2[i] = sqrtf(n2[i]) * 1.0001f;
+        sc[i] = score_scale(n2[i]);
+      }
+#pragma unroll
+      for (int j = 0; j < HM; ++j) {
+        const float f = readlane_f(sc[j >> 2], head_lane(j));
+        const _Float16 hv = score_half(q[j] * f);
+        const float r = q[j] * f - (float)hv;
+        t[j] = r * r;
+        if (j < H_idx) *(_Float16*)(sb + j * SB::HEAD + place) = hv;
+      }
+      wave_sums_butterfly_f<HM>(t, r2);
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const int j = 4 * i + 2 * (rho & 1) + (rho >> 1);
+        const float al = __shfl(al_l, j);
+        if (holds && j < H_idx) {
+          const float a = 0.5f * al / sc[i];
+          sane = sane && score_sane(al) && score_sane(n2[i]);
+          err += fabsf(a) * (1.001f * sqrtf(r2[i]) + 0x1p-16f * n2[i] * sc[i]);
+          rows[j * 16 + m] = a;
+        }
+      }
+      err = wave_sum_f(err);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const int j = i * HP + hl;
+        const bool on = j < H_idx;
+        const float al = on ? __shfl(al_l, j) : 0.f;
+        const double rr = sqrt(row16_sum_d(v[i] * v[i]) / (double)DI + (double)rms_eps);
+        q[i] = (float)(v[i] / rr * (double)nw);
+        const float norm = sqrtf(row16_sum_f(q[i] * q[i])) * 1.0001f, f = score_scale(norm);
+        const _Float16 hv = score_half(q[i] * f);
+        const float r = q[i] * f - (float)hv;
+        const float a = 0.5f * al / f, r2 = row16_sum_f(r * r);
+        if (on) {
+          sane = sane && score_sane(al) && score_sane(norm);
+          err += fabsf(a) * (1.001f * sqrtf(r2) + 0x1p-16f * norm * f);
+          c = fma(0.5 * (double)al, (double)q[i], c);
+          *(_Float16*)(sb + j * SB::HEAD + place) = hv;
+          if (d == 0) rows[j * 16 + m] = a;
+        }
+      }
+      c = rows_sum_d(c);
+      err = rows_sum_f(err);
     }
-    if constexpr (DI == 16) { c = rows_sum_d(c); err = rows_sum_f(err); }
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      if (i * HP + hl < H_idx) qf[(row * H_idx + i * HP + hl) * DI + d] = q[i];
     const float cf = (float)c;
     float c2 = cf * cf;
     if constexpr (DI == 64) c2 = wave_sum_f(c2); else c2 = row16_sum_f(c2);
@@ -132,22 +180,22 @@ __global__ __launch_bounds__(256) void k_score_features(const double* __restrict
     sane = sane && score_sane(cn);
     err += (1.001f * sqrtf(r2) + 0x1p-16f * cn * f) / f;
     sane = __all(sane && isfinite(err));
-    if (lane < DI) *(_Float16*)(sb + HM * SB::HEAD + place + m * (DI == 64 ? 16 : 8)) = sane ? hv : (_Float16)0.f;
+    if (lane < DI) *(_Float16*)(sb + HM * SB::HEAD + place) = sane ? hv : (_Float16)0.f;
     if (!sane) {   // (operands of zero: infinities and NaN stay out of the sum, whose bound is then infinite)
       for (int j = hl; j < H_idx; j += HP) {
-        *(_Float16*)(sb + j * SB::HEAD + place + m * (DI == 64 ? 16 : 8)) = (_Float16)0.f;
+        *(_Float16*)(sb + j * SB::HEAD + place) = (_Float16)0.f;
         if (d == 0) rows[j * 16 + m] = 0.f;
       }
     }
     if (lane == 0) {
       rows[SB::T * 16 + m] = sane ? 1.f / f : 0.f;
       rows[SB::ERR * 16 + m] = sane ? 1.01f * 4096.f * err : INFINITY;   // out of range: always a candidate
-      ((int*)rows)[SB::POS * 16 + m] = q_pos[row];
+      ((int*)rows)[SB::POS * 16 + m] = my_pos;
     }
   }
   __syncthreads();
   uint4* dst = (uint4*)(blocks + ((size_t)b * gridDim.x + blockIdx.x) * SB::BYTES);
-  for (int i = tid; i < SB::BYTES / 16; i += 256) dst[i] = ((const uint4*)sb)[i];
+  for (int i = tid; i < SB::BYTES / 16; i += 1024) dst[i] = ((const uint4*)sb)[i];
 }
 
 // a key's fp16 operand for one lane (dims DPL kq .. of the key), scaled so that the key's norm is in [2^11, 2^12).

@@ -264,7 +264,7 @@ void score_many(im_handle* h, const im_state* st, const bf16_t* norm_q_w, const 
   int32_t* n_listed = (int32_t*)(ws + h->off_nlist);
   int2* listed = (int2*)(ws + h->off_list);
   const bf16_t* Kidx = (const bf16_t*)st->Kidx;
-  k_score_features<DI, HM><<<dim3(nblk, c.batch), 256, 0, s>>>((const double*)(ws + h->off_qy),
+  k_score_features<DI, HM><<<dim3(nblk, c.batch), 1024, 0, s>>>((const double*)(ws + h->off_qy),
       (const double*)(ws + h->off_alpha), q_pos, norm_q_w, c.rms_eps, alpha_denom, n_q, c.n_idx_heads, qf, al16, blocks,
       n_listed, (int32_t*)(ws + h->off_xcount));
   // a scan over a short cache has few (256-key tile, unit) workgroups: its query blocks then go in up to
