@@ -140,9 +140,12 @@ __global__ __launch_bounds__(256) void k_exact_prep(const bf16_t* __restrict__ A
 }
 
 // grid (ceil(M / XG_BM) * Np / XG_BN), 8 waves as 2 x 4; a wave owns a 32 x 32 tile of C in 7 int32 accumulators.
-// A step is 64 values of the contraction: 32 products of 32 cycles per wave, two waves per SIMD, 1 us.  B's planes are
-// copied straight into LDS two steps ahead and A's rows (bf16) three (a load from HBM takes up to 2 us); the thread
-// that copied 8 values of A turns them into digits one step ahead, between the products.
+// A step is 64 values of the contraction: 32 products of 32 cycles per wave, two waves per SIMD, 0.85 us.  B's planes are
+// copied straight into LDS and A's rows (bf16) too, three steps ahead (a load from HBM takes up to 2 us); the thread
+// that copied 8 values of A turns them into digits one step ahead, between the products.  A step has two halves of 16
+// products; the operands of a half are read from LDS during the half before it (read at the top of a step, by all
+// waves at once, they took 1024 cycles of the LDS in which no product ran), so the step's barrier lies between
+// its halves.
 __global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict__ A, const char* __restrict__ planes,
                                                        const int32_t* __restrict__ expA,
                                                        const int32_t* __restrict__ expB, double* __restrict__ C, int M,
@@ -159,14 +162,15 @@ __global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict_
   else { tn = bid % nt; tm = bid / nt; }
   const int m0 = tm * XG_BM, n0 = tn * XG_BN;
   if (m0 >= M) return;
-  // this thread's piece of A: row arow, values 8 ap .. of every step
-  const int arow = tid >> 3, ap = tid & 7;
+  // this thread's piece of A: row arow, values 8 ap .. of every step (a wave has 32 rows of 32 bytes: the digits of 8 rows of
+  // 128 bytes met in the same banks four at a time)
+  const int arow = (w >> 2) * 32 + (lane >> 1), ap = 2 * (w & 3) + (lane & 1);
   const int am = min(m0 + arow, M - 1);
   const bf16_t* asrc = A + (size_t)am * K + ap * 8;
   const int nc = K / XG_BK;
   const float ascale = exact_scale(expA[am]);
   const int aplace = ((arow >> 5) * 2 + (ap >> 2)) * 4096 + exact_place(arow, ap & 3);
-  // a step's copies: 8 KB of A (each wave the 8 rows that its threads convert), 4 row tiles x 2 steps x 4 KB of B
+  // a step's copies: 8 KB of A (each wave what its threads convert), 4 row tiles x 2 steps x 4 KB of B
   auto fetchA = [&](int c, int buf) { copy_to_lds_1k((const char*)(asrc + min(c, nc - 1) * XG_BK), &sR[buf][w * 1024]); };
   auto fetchB = [&](int c, int buf) {
     c = min(c, nc - 1);   // (past the end: not used)
@@ -181,56 +185,64 @@ __global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict_
   for (int p = 0; p < 7; ++p)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[p][r] = 0;
+  auto digits = [&](int raw, int buf) {   // this thread's values: digit planes into LDS
+    uint2 pl[4];
+    exact_digits(*(const uint4*)(&sR[raw][tid * 16]), ascale, pl);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) *(uint2*)(&sA[buf][aplace + d * 1024]) = pl[d];
+  };
+  auto operands = [&](im_i4* a, im_i4* b, int bufA, int bufB, int st) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      a[d] = *(const im_i4*)(&sA[bufA][(wm * 2 + st) * 4096 + d * 1024 + lane * 16]);
+      b[d] = *(const im_i4*)(&sB[bufB][(wn * 2 + st) * 4096 + d * 1024 + lane * 16]);
+    }
+  };
+  // pairs of digits in an order that leaves other sums between two products of the same sum
+  auto products = [&](const im_i4* a, const im_i4* b) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const int j = (d + s) & 3;
+        acc[d + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[d], b[j], acc[d + j], 0, 0, 0);
+      }
+  };
   fetchA(0, 0);
   fetchA(1, 1);
   fetchB(0, 0);
   fetchA(2, 2);
   fetchB(1, 1);
   copy_wait<5>();
-  {
-    uint2 pl[4];
-    exact_digits(*(const uint4*)(&sR[0][tid * 16]), ascale, pl);
-#pragma unroll
-    for (int d = 0; d < 4; ++d) *(uint2*)(&sA[0][aplace + d * 1024]) = pl[d];
-  }
+  digits(0, 0);
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the raw values have been read
+  fetchA(3, 0);
+  fetchB(2, 2);
+  __syncthreads();
+  im_i4 a0[4], b0[4], a1[4], b1[4];
+  operands(a0, b0, 0, 0, 0);
   int bA = 0, b3 = 0;
 #pragma unroll 1
   for (int c = 0; c < nc; ++c) {
     const int next = b3 == 2 ? 0 : b3 + 1;
-    copy_wait<5>();    // all but the youngest step's copies: B of this step and A of the next are here
-    __syncthreads();   // ... for every wave, and the buffers of the step before are free
-    fetchA(c + 3, b3);
-    fetchB(c + 2, b3 == 0 ? 2 : b3 - 1);
-    im_i4 a[2][4], b[2][4];
+    // first half; the second half's operands and the next step's digits on their way
+    operands(a1, b1, bA, b3, 1);
+    digits(next, bA ^ 1);
+    products(a0, b0);
+    // (a product keeps the matrix core busy for 8 vector instructions)
+    __builtin_amdgcn_sched_group_barrier(0x100, 9, 0);
 #pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        a[st][d] = *(const im_i4*)(&sA[bA][(wm * 2 + st) * 4096 + d * 1024 + lane * 16]);
-        b[st][d] = *(const im_i4*)(&sB[b3][(wn * 2 + st) * 4096 + d * 1024 + lane * 16]);
-      }
-    uint2 pl[4];
-    exact_digits(*(const uint4*)(&sR[next][tid * 16]), ascale, pl);
-    // pairs of digits in an order that leaves other sums between two products of the same sum
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          const int j = (d + s) & 3;
-          acc[d + j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[st][d], b[st][j], acc[d + j], 0, 0, 0);
-        }
-#pragma unroll
-    for (int d = 0; d < 4; ++d) *(uint2*)(&sA[bA ^ 1][aplace + d * 1024]) = pl[d];
-    // the conversion goes between the products: a product keeps the matrix core busy for 8 vector instructions
-    __builtin_amdgcn_sched_group_barrier(0x100, 17, 0);
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
+    for (int i = 0; i < 16; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
     }
     __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
+    copy_wait<5>();    // all but the youngest group of copies: B of the next step and A of the one after it are here
+    __syncthreads();   // ... for every wave; this step's operands and the next step's raw values have been read
+    fetchA(c + 4, next);
+    fetchB(c + 3, b3);
+    operands(a0, b0, bA ^ 1, next, 0);
+    products(a1, b1);
     bA ^= 1;
     b3 = next;
   }
