@@ -403,14 +403,14 @@ __global__ __launch_bounds__(256) void k_gemm_nt_mfma(const bf16_t* __restrict__
   gemm_nt_tile<TM, TN>(A, B, Cm, M, N, Kd, blockIdx.x, blockIdx.y);
 }
 
-// The same for small products: ONE 16 x 16 output tile per workgroup, its 4 waves take a quarter of
-// the contraction each (Kd % 128 == 0) and meet in LDS.  grid (ceil(N / 16), ceil(M / 16)).
-__global__ __launch_bounds__(256) void k_gemm_nt_mfma_k4(const bf16_t* __restrict__ A,
-                                                         const bf16_t* __restrict__ B,
-                                                         double* __restrict__ Cm, int M, int N, int Kd) {
-  __shared__ double red[3][64][4];
+// The same for small products: ONE 16 x 16 output tile per workgroup, its W waves take 1 / W of the contraction each
+// (Kd % (32 W) == 0) and meet in LDS.  tile (bx, by) of ceil(N / 16) x ceil(M / 16).
+template <int W>
+__device__ __forceinline__ void gemm_nt_tile_split(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
+                                                   double* __restrict__ Cm, int M, int N, int Kd, int bx, int by,
+                                                   double (*red)[64][4]) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
-  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16, kw = Kd / 4;
+  const int m0 = by * 16, n0 = bx * 16, kw = Kd / W;
   const bf16_t* ap = A + (size_t)min(m0 + l16, M - 1) * Kd + w * kw + 8 * kq;
   const bf16_t* bp = B + (size_t)min(n0 + l16, N - 1) * Kd + w * kw + 8 * kq;
   im_v4d acc = {0.0, 0.0, 0.0, 0.0};
@@ -444,9 +444,32 @@ __global__ __launch_bounds__(256) void k_gemm_nt_mfma_k4(const bf16_t* __restric
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = m0 + 4 * r + kq, n = n0 + l16;
-      if (m < M && n < N) Cm[(size_t)m * N + n] = ((acc[r] + red[0][lane][r]) + red[1][lane][r]) + red[2][lane][r];
+      double t = acc[r];
+#pragma unroll
+      for (int i = 0; i < W - 1; ++i) t += red[i][lane][r];
+      if (m < M && n < N) Cm[(size_t)m * N + n] = t;
     }
   }
+}
+
+// grid (ceil(N / 16), ceil(M / 16))
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_gemm_nt_mfma_split(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
+                                                               double* __restrict__ Cm, int M, int N, int Kd) {
+  __shared__ double red[W - 1][64][4];
+  gemm_nt_tile_split<W>(A, B, Cm, M, N, Kd, blockIdx.x, blockIdx.y, red);
+}
+
+// Both query-side products of up to a few hundred queries in one launch: y = q U_q^T and alpha = x G^T (N2 <= 16).  The
+// gate's ceil(M / 16) tiles come first: a chain of loads of 10 to 20 us each, that hides behind the projection's.
+__global__ __launch_bounds__(256) void k_query_side(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Uq,
+                                                    double* __restrict__ y, int M, int N1, int K1,
+                                                    const bf16_t* __restrict__ x, const bf16_t* __restrict__ G,
+                                                    double* __restrict__ alpha, int N2, int K2) {
+  __shared__ double red[3][64][4];
+  const int mt = (M + 15) / 16, nt = (N1 + 15) / 16, t = (int)blockIdx.x - mt;
+  if (t < 0) gemm_nt_tile_split<4>(x, G, alpha, M, N2, K2, 0, blockIdx.x, red);
+  else gemm_nt_tile_split<4>(q, Uq, y, M, N1, K1, t % nt, t / nt, red);
 }
 
 // Few rows (decode): every workgroup owns 2 rows of B and streams them once for all M rows of A.

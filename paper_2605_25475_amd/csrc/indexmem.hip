@@ -220,13 +220,17 @@ void launch_tail(const DecArgs& a, int units, hipStream_t s) {
   }
 }
 
-// C[m][n] = sum_k A[m][k] B[n][k] in fp64: matrix cores when the contraction length allows, one
-// tile per wave for small products (more waves), 2 x 2 tiles per wave for large ones (less L2 traffic)
+// C[m][n] = sum_k A[m][k] B[n][k] in fp64: matrix cores when the contraction length allows; the contraction
+// split over 16 or 4 waves for small products (more waves, shorter chains), 2 x 2 tiles per wave for large ones
+// (less L2 traffic)
+long long gemm_tiles(long long M, long long N) { return ((M + 15) / 16) * ((N + 15) / 16); }
 void gemm_nt(hipStream_t s, const bf16_t* A, const bf16_t* B, double* Cm, int M, int N, int Kd) {
   if (Kd % 32 != 0) {
     k_gemm_nt_f64<<<dim3((N + 63) / 64, (M + 63) / 64), 256, 0, s>>>(A, B, Cm, M, N, Kd);
-  } else if (Kd % 128 == 0 && (long long)((M + 15) / 16) * ((N + 15) / 16) <= 2048) {
-    k_gemm_nt_mfma_k4<<<dim3((N + 15) / 16, (M + 15) / 16), 256, 0, s>>>(A, B, Cm, M, N, Kd);
+  } else if (Kd % 512 == 0 && gemm_tiles(M, N) <= 512) {
+    k_gemm_nt_mfma_split<16><<<dim3((N + 15) / 16, (M + 15) / 16), 1024, 0, s>>>(A, B, Cm, M, N, Kd);
+  } else if (Kd % 128 == 0 && (N <= 16 || gemm_tiles(M, N) <= 2048)) {
+    k_gemm_nt_mfma_split<4><<<dim3((N + 15) / 16, (M + 15) / 16), 256, 0, s>>>(A, B, Cm, M, N, Kd);
   } else if ((long long)M * N <= (1ll << 21) || N <= 16) {
     k_gemm_nt_mfma<1, 1><<<dim3((N + 31) / 32, (M + 31) / 32), 256, 0, s>>>(A, B, Cm, M, N, Kd);
   } else {
@@ -492,9 +496,15 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
       k_project_keys<<<dim3((h->max_live + 63) / 64, units), 256, 0, s>>>(
           (const bf16_t*)st->K, (bf16_t*)st->Kidx, st->len, st->n_projected, (const bf16_t*)p->Uk,
           (const bf16_t*)p->norm_k_w, c.capacity, h->max_live, c.rms_eps, status_ptr(h));
-    if (n_q >= c.n_idx_heads && exact_fits(&c, M)) exact_project(h, s, (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M);
-    else gemm_nt(s, (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M, Nq, Kq);
-    gemm_nt(s, (const bf16_t*)x_gate, (const bf16_t*)p->G, al, M, c.n_idx_heads, c.gate_in_dim);
+    if (c.gate_in_dim % 128 == 0 && gemm_tiles(M, Nq) <= 2048) {
+      k_query_side<<<(M + 15) / 16 + gemm_tiles(M, Nq), 256, 0, s>>>(
+          (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M, Nq, Kq, (const bf16_t*)x_gate, (const bf16_t*)p->G, al,
+          c.n_idx_heads, c.gate_in_dim);
+    } else {
+      if (n_q >= c.n_idx_heads && exact_fits(&c, M)) exact_project(h, s, (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M);
+      else gemm_nt(s, (const bf16_t*)q_new, (const bf16_t*)p->Uq, qy, M, Nq, Kq);
+      gemm_nt(s, (const bf16_t*)x_gate, (const bf16_t*)p->G, al, M, c.n_idx_heads, c.gate_in_dim);
+    }
   }
   // fewer queries than indexer heads (a decode step): the heads of a query are the scoring product's columns
   if (n_q < c.n_idx_heads) {
