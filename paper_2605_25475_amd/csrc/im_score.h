@@ -378,18 +378,21 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_scan(const bf16_
   }
 }
 
-// grid (ceil(max_live / 64), units), 4 waves of 16 keys each.  A candidate is a record's block: its 4 queries are
-// evaluated in fp64 by the whole wave (lane (query r = lane / 16, p): dims 4 p .. of every head), the heads' terms
-// added in head order.  A second candidate block inside one record is not known by name: the key goes to the list.
+// grid (ceil(max_live / (4 KPW)), units), 4 waves of KPW keys each (16, or 4).  A candidate is a record's block: its 4 queries are
+// evaluated in fp64 by the whole wave (lane (query r = lane / 16, p): dims 4 p .. of every head).  Bound by the vector
+// ALU: half of it conversions and products, half the sums over 16 lanes, which is why the heads' sums are taken together.  A second candidate block inside one record is not known by name: the key goes to the list.
 template <int DI, int HM>
 __device__ __forceinline__ float score_exact4(const float* __restrict__ qrow, const float* __restrict__ al, int H_idx,
                                               const float* kd, int p) {
   constexpr int PD = DI / 16;
+  const bool b3 = p & 8, b2 = p & 4, b1 = p & 2;
+  const int head = p >> 1;   // of 8, whose sum ends in this lane
+  auto pick = [](bool b, double lo, double hi) { return b ? hi : lo; };   // (of values: of array elements it is an indexed load)
   double acc = 0.0;
 #pragma unroll
   for (int j0 = 0; j0 < HM; j0 += 8) {
     if (j0 >= H_idx) break;
-    float qv[8][PD], av[8];   // (heads past the last repeat it, unused)
+    float qv[8][PD];   // (heads past the last repeat it, unused)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int j = min(j0 + i, H_idx - 1);
@@ -400,20 +403,28 @@ __device__ __forceinline__ float score_exact4(const float* __restrict__ qrow, co
         qv[i][0] = qrow[j * DI + p];
       }
     }
-#pragma unroll
-    for (int i = 0; i < 8; i += 4) {
-      const float4 a4 = *(const float4*)(al + j0 + i);
-      av[i] = a4.x; av[i + 1] = a4.y; av[i + 2] = a4.z; av[i + 3] = a4.w;
-    }
+    const float av = al[j0 + head];
+    double z[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      double z = 0.0;
+      z[i] = 0.0;
 #pragma unroll
-      for (int m = 0; m < PD; ++m) z = fma((double)qv[i][m], (double)kd[m], z);
-      z = row16_sum_d(z);
-      if (j0 + i < H_idx) acc = fma((double)av[i], fmax(z, 0.0), acc);
+      for (int m = 0; m < PD; ++m) z[i] = fma((double)qv[i][m], (double)kd[m], z[i]);
     }
+    // the 8 heads' sums over the 16 lanes: after each step a lane goes on with half of the heads
+#pragma unroll
+    for (int i = 0; i < 8; ++i) z[i] += dpp_zero_d<0x128, 0xF>(z[i]);                                    // lane ^ 8
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { z[i] = pick(b3, z[i], z[i + 4]); z[i] += dpp_zero_d<0x141, 0xF>(z[i]); }   // lane ^ 7
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { z[i] = pick(b2, z[i], z[i + 2]); z[i] += dpp_zero_d<0x4E, 0xF>(z[i]); }    // lane ^ 2
+    z[0] = pick(b1, z[0], z[1]);
+    z[0] += dpp_zero_d<0xB1, 0xF>(z[0]);                                                                 // lane ^ 1
+    if (j0 + head < H_idx) acc = fma((double)av, fmax(z[0], 0.0), acc);
   }
+  acc += dpp_zero_d<0x4E, 0xF>(acc);     // over the heads
+  acc += dpp_zero_d<0x141, 0xF>(acc);
+  acc += dpp_zero_d<0x128, 0xF>(acc);
   return (float)acc;
 }
 // this lane's share (dims PD p ..) of a key
@@ -427,7 +438,7 @@ __device__ __forceinline__ void score_exact_key(const bf16_t* __restrict__ krow,
   }
 }
 
-template <int DI, int HM>
+template <int DI, int HM, int KPW>
 __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ Kidx, const int32_t* __restrict__ pos,
                                                      const int32_t* __restrict__ len, const char* __restrict__ blocks,
                                                      const float* __restrict__ qf, const float* __restrict__ al16,
@@ -441,9 +452,10 @@ __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ 
   const int unit = blockIdx.y, units = gridDim.y, b = unit / sets_per_b;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
   const int n = min(len[unit], max_live);
-  const int kbase = blockIdx.x * 64 + 16 * w;
+  const int kbase = (blockIdx.x * 4 + w) * KPW;
   if (kbase >= n) return;
-  const int key = min(kbase + l16, n - 1), nblk = (n_q + 15) / 16;
+  const bool mine = l16 < KPW && kbase + l16 < n;
+  const int key = mine ? kbase + l16 : kbase, nblk = (n_q + 15) / 16;
   const int pk = pos[(size_t)unit * C + key];
   float u1[IM_SCORE_GROUPS], u2[IM_SCORE_GROUPS], lmax = -INFINITY;
   int i1[IM_SCORE_GROUPS], ib = 0;
@@ -474,7 +486,7 @@ __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ 
   for (int g = 0; g < IM_SCORE_GROUPS; ++g) {
     if (g >= groups) break;
     more = more || (u2[g] >= low && u2[g] > -INFINITY);
-    unsigned long long cand = __ballot(kbase + l16 < n && u1[g] >= low && u1[g] > -INFINITY);
+    unsigned long long cand = __ballot(mine && u1[g] >= low && u1[g] > -INFINITY);
     while (cand) {
       const int ln = __builtin_ctzll(cand);
       cand &= cand - 1;
@@ -490,8 +502,8 @@ __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ 
       if (l16 == kk) best = fmaxf(best, m);
     }
   }
-  more = rows_max_f(more ? 1.f : 0.f) > 0.f && kbase + l16 < n;
-  if (kq == 0 && kbase + l16 < n) scores[(size_t)unit * C + key] = best;
+  more = rows_max_f(more ? 1.f : 0.f) > 0.f && mine;
+  if (kq == 0 && mine) scores[(size_t)unit * C + key] = best;
   const unsigned long long lst = __ballot(more && kq == 0);
   if (lst) {
     int base = 0;
@@ -506,7 +518,7 @@ __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ 
 // segment of its query blocks; the segments are as short as fills the grid, and not below IM_LIST_BLOCKS.
 // scores[key] rises by atomic maxima; reading an older value only costs work.
 #define IM_LIST_WGS 1024
-#define IM_LIST_BLOCKS 8
+#define IM_LIST_BLOCKS 2
 template <int DI, int HM>
 __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_listed(const bf16_t* __restrict__ Kidx,
                                                                        const int32_t* __restrict__ pos,

@@ -107,6 +107,8 @@ size_t score_rec_keys(size_t sets, size_t capacity) {
   return all < few ? all : few;
 }
 
+// up to this many keys a wave of k_score_exact takes 4 instead of 16: 12000 keys 27 -> 17 us, 65536 keys 54 -> 58
+#define IM_EXACT_FEW 32768
 // The query projection of M rows goes through the exact int8 product (im_exact.h) where it has more than 2048 tiles
 // of 16 x 16: below, its 64 x 128 tiles leave most of the chip idle and the fp64 kernel that splits the contraction is
 // faster (512 rows x 512: 32 us against 80).
@@ -288,9 +290,15 @@ void score_many(im_handle* h, const im_state* st, const bf16_t* norm_q_w, const 
   else
     k_score_scan<DI, HM, 4><<<grid, 256, 0, s>>>(Kidx, st->pos, st->len, st->n_projected, blocks, q_pos, n_q, per_b,
                                                  c.capacity, c.n_idx_heads, live, units, per_group, live, rec_u, rec_i);
-  k_score_exact<DI, HM><<<dim3((live + 63) / 64, units), 256, 0, s>>>(
-      Kidx, st->pos, st->len, blocks, qf, al16, q_pos, n_q, per_b, c.capacity, c.n_idx_heads, live, groups, live, rec_u,
-      rec_i, scores, n_listed, listed);
+  // the wave's keys are evaluated in turn, 1.5 us each
+  if ((long long)live * units <= IM_EXACT_FEW)
+    k_score_exact<DI, HM, 4><<<dim3((live + 15) / 16, units), 256, 0, s>>>(
+        Kidx, st->pos, st->len, blocks, qf, al16, q_pos, n_q, per_b, c.capacity, c.n_idx_heads, live, groups, live, rec_u,
+        rec_i, scores, n_listed, listed);
+  else
+    k_score_exact<DI, HM, 16><<<dim3((live + 63) / 64, units), 256, 0, s>>>(
+        Kidx, st->pos, st->len, blocks, qf, al16, q_pos, n_q, per_b, c.capacity, c.n_idx_heads, live, groups, live, rec_u,
+        rec_i, scores, n_listed, listed);
   k_score_listed<DI, HM><<<IM_LIST_WGS, 256, 0, s>>>(Kidx, st->pos, blocks, qf, al16, c.batch, n_q, per_b, c.capacity,
                                              c.n_idx_heads, scores, n_listed, listed);
 }
