@@ -437,8 +437,8 @@ int32_t im_append_kv(im_handle* h, const im_state* st, const void* k_new, const 
   dim3 grid((n_new * 16 + 255) / 256, units);
   k_append_rows<<<grid, 256, 0, s>>>((bf16_t*)st->K, (bf16_t*)st->V, st->pos, st->len,
                                      (const bf16_t*)k_new, (const bf16_t*)v_new, pos_new, n_new,
-                                     c.n_kv_heads, 1, c.capacity);
-  k_append_len<<<(units + 255) / 256, 256, 0, s>>>(st->len, units, n_new, c.capacity, status_ptr(h));
+                                     c.n_kv_heads, 1, c.capacity, n_new <= 16 ? status_ptr(h) : nullptr);
+  if (n_new > 16) k_append_len<<<(units + 255) / 256, 256, 0, s>>>(st->len, units, n_new, c.capacity, status_ptr(h));
   return launch_check(h, "im_append_kv");
 }
 
@@ -460,7 +460,7 @@ int32_t im_append_kv_hidden(im_handle* h, const im_params* p, const im_state* st
   dim3 grid((n_new * 16 + 255) / 256, units);
   k_append_rows<<<grid, 256, 0, s>>>((bf16_t*)st->K, (bf16_t*)st->V, st->pos, st->len,
                                      (const bf16_t*)k_new, (const bf16_t*)v_new, pos_new, n_new,
-                                     c.n_kv_heads, c.n_kv_heads, c.capacity);
+                                     c.n_kv_heads, c.n_kv_heads, c.capacity, nullptr);
   double* xk = (double*)(h->ws + h->off_xk);
   const int M = c.batch * n_new;
   if (M <= 32)
@@ -516,18 +516,19 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
   }
   // fewer queries than indexer heads (a decode step): the heads of a query are the scoring product's columns
   if (n_q < c.n_idx_heads) {
+    const bool raw = n_q <= 4;   // (every wave normalises them; more queries take a launch for it)
     const int rows = M * c.n_idx_heads;
-    k_qnorm_alpha<<<(rows + 3) / 4 + (rows + 255) / 256, 256, 0, s>>>(qy, rows, di, (const bf16_t*)p->norm_q_w,
-                                                                     c.rms_eps, al, rows, alpha_denom);
+    if (!raw)
+      k_qnorm_alpha<<<(rows + 3) / 4 + (rows + 255) / 256, 256, 0, s>>>(qy, rows, di, (const bf16_t*)p->norm_q_w,
+                                                                       c.rms_eps, al, rows, alpha_denom);
     const dim3 grid((h->max_live + 63) / 64, units);
-    if (c.head_shared)
-      k_score_few<IM_DI_SHARED><<<grid, 256, 0, s>>>((const bf16_t*)st->Kidx, st->pos, st->len, st->n_projected, qy, al,
-                                                     q_pos, n_q, c.n_kv_heads / heads_per_set(c), c.capacity,
-                                                     c.n_idx_heads, h->max_live, scores_out);
-    else
-      k_score_few<IM_DI><<<grid, 256, 0, s>>>((const bf16_t*)st->Kidx, st->pos, st->len, st->n_projected, qy, al,
-                                              q_pos, n_q, c.n_kv_heads / heads_per_set(c), c.capacity,
-                                              c.n_idx_heads, h->max_live, scores_out);
+#define IM_SCORE_FEW(DI, RAW)                                                                                       \
+  k_score_few<DI, RAW><<<grid, 256, 0, s>>>((const bf16_t*)st->Kidx, st->pos, st->len, st->n_projected, qy, al, q_pos, \
+                                            n_q, c.n_kv_heads / heads_per_set(c), c.capacity, c.n_idx_heads,        \
+                                            h->max_live, (const bf16_t*)p->norm_q_w, c.rms_eps, alpha_denom, scores_out)
+    if (c.head_shared) { if (raw) IM_SCORE_FEW(IM_DI_SHARED, true); else IM_SCORE_FEW(IM_DI_SHARED, false); }
+    else { if (raw) IM_SCORE_FEW(IM_DI, true); else IM_SCORE_FEW(IM_DI, false); }
+#undef IM_SCORE_FEW
     return launch_check(h, "im_index_score");
   }
   const bf16_t* nqw = (const bf16_t*)p->norm_q_w;
