@@ -757,7 +757,10 @@ __device__ __forceinline__ void select_pick_bin(const unsigned* hist, unsigned r
   __syncthreads();
 }
 
-// grid (units), 1024 threads
+// grid (units), 1024 threads.  R > 0: at most 1024 R entries, whose keys and positions a thread holds in registers (entry
+// tid + 1024 r): loaded again in each of the 5 passes they were a chain of dependent loads of 1 us each, 46 us for
+// 8192 entries.  The lists then follow from one scan over the (r, wave) counts.  R = 0: any number of entries.
+template <int R>
 __global__ __launch_bounds__(1024) void k_select(const float* __restrict__ scores,
                                                  const int32_t* __restrict__ pos,
                                                  const int32_t* __restrict__ len, int C, int max_live,
@@ -785,10 +788,29 @@ __global__ __launch_bounds__(1024) void k_select(const float* __restrict__ score
   if (over && tid == 0) atomicOr(status, IM_STATUS_LIVE_EXCEEDED_BIT);
   const int k = over ? n : min(budget, n);
 
+  constexpr int RR = R > 0 ? R : 1;
+  uint32_t kr[RR];
+  int pr[RR];
+  if constexpr (R > 0) {   // (past the end: the last entry again, unused)
+    float sv[RR];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = max(min(tid + 1024 * r, n - 1), 0);
+      sv[r] = sc[i];
+      pr[r] = ps[i];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) kr[r] = __float_as_uint(sv[r]);
+  }
   int maxpos = INT_MIN;
   if (n_recent > 0) {
     int m = INT_MIN;
-    for (int i = tid; i < n; i += 1024) m = max(m, ps[i]);
+    if constexpr (R > 0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) m = max(m, n > 0 ? pr[r] : INT_MIN);
+    } else {
+      for (int i = tid; i < n; i += 1024) m = max(m, ps[i]);
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
     if ((tid & 63) == 0) sh_red[tid >> 6] = m;
@@ -796,10 +818,38 @@ __global__ __launch_bounds__(1024) void k_select(const float* __restrict__ score
     for (int i = 0; i < 16; ++i) maxpos = max(maxpos, sh_red[i]);
     __syncthreads();
   }
-  auto key_of = [&](int i) -> uint32_t {
-    const int p = ps[i];
+  auto key_from = [&](float score, int p) -> uint32_t {
     const bool forced = (p < n_sink) || (n_recent > 0 && (long long)p > (long long)maxpos - n_recent);
-    return forced ? IM_KEY_PINF : score_key(sc[i]);
+    return forced ? IM_KEY_PINF : score_key(score);
+  };
+  if constexpr (R > 0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) kr[r] = key_from(__uint_as_float(kr[r]), pr[r]);
+  }
+  // f(slot, key, position) for this thread's entries, ascending
+  auto entries = [&](auto f) {
+    if constexpr (R > 0) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (tid + 1024 * r < n) f(tid + 1024 * r, kr[r], pr[r]);
+    } else {
+      for (int i = tid; i < n; i += 1024) {
+        const int p = ps[i];
+        f(i, key_from(sc[i], p), p);
+      }
+    }
+  };
+
+  // one more in a bin; the lanes that share the first one's bin add together (scores of one size share their upper bits:
+  // 64 atomics to one address otherwise)
+  auto count = [&](bool on, unsigned bin) {
+    const unsigned long long act = __ballot(on);
+    if (act == 0) return;
+    const int first = __builtin_ctzll(act);
+    const unsigned b0 = __builtin_amdgcn_readlane(bin, first);
+    const unsigned long long same = __ballot(on && bin == b0);
+    if ((int)(threadIdx.x & 63) == first) atomicAdd(&hist[b0], (unsigned)__popcll(same));
+    else if (on && bin != b0) atomicAdd(&hist[bin], 1u);
   };
 
   if (k == n - 1 && n >= 2) {
@@ -807,10 +857,10 @@ __global__ __launch_bounds__(1024) void k_select(const float* __restrict__ score
     // position, then largest slot.  One reduction instead of the radix passes; the lists follow from it.
     unsigned long long best = ~0ull;   // (key << 32) | ~position key: its minimum is the last-ranked (score, position)
     int bslot = -1;
-    for (int i = tid; i < n; i += 1024) {
-      const unsigned long long c = ((unsigned long long)key_of(i) << 32) | (uint32_t)(~((uint32_t)ps[i] ^ 0x80000000u));
+    entries([&](int i, uint32_t key, int p) {
+      const unsigned long long c = ((unsigned long long)key << 32) | (uint32_t)(~((uint32_t)p ^ 0x80000000u));
       if (c <= best) { best = c; bslot = i; }   // ascending slots: <= keeps the largest
-    }
+    });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       const unsigned long long ob = __shfl_xor(best, o, 64);
@@ -843,10 +893,9 @@ __global__ __launch_bounds__(1024) void k_select(const float* __restrict__ score
       if (tid < 256) hist[tid] = 0;
       __syncthreads();
       const uint32_t prefix = sh_prefix;
-      for (int i = tid; i < n; i += 1024) {
-        const uint32_t key = key_of(i);
-        if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-      }
+      entries([&](int, uint32_t key, int) {
+        count((key & mask) == prefix, (key >> shift) & 255u);
+      });
       __syncthreads();
       const unsigned rem = sh_rem;
       select_pick_bin<true>(hist, rem, wsum, sh_pick);
@@ -870,11 +919,10 @@ __global__ __launch_bounds__(1024) void k_select(const float* __restrict__ score
         if (tid < 256) hist[tid] = 0;
         __syncthreads();
         const uint32_t prefix = sh_prefix;
-        for (int i = tid; i < n; i += 1024) {
-          if (key_of(i) != T) continue;
-          const uint32_t pk = (uint32_t)ps[i] ^ 0x80000000u;
-          if ((pk & mask) == prefix) atomicAdd(&hist[(pk >> shift) & 255u], 1u);
-        }
+        entries([&](int, uint32_t key, int p) {
+          const uint32_t pk = (uint32_t)p ^ 0x80000000u;
+          count(key == T && (pk & mask) == prefix, (pk >> shift) & 255u);
+        });
         __syncthreads();
         const unsigned r = sh_rem;
         select_pick_bin<false>(hist, r, wsum, sh_pick);
@@ -891,6 +939,44 @@ __global__ __launch_bounds__(1024) void k_select(const float* __restrict__ score
     }
   }
 
+  if constexpr (R > 0) {
+    if (all_ties) {   // (uniform) keep = key >= T: the counts of all (r, wave) at once, then every list entry's place
+      const int lane = tid & 63, w = tid >> 6;
+      auto kept = [&](int r) { return tid + 1024 * r < n && (mode == 0 || (mode == 2 && kr[r] >= T)); };
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const unsigned cnt = __popcll(__ballot(kept(r)));
+        if (lane == 0) hist[r * 16 + w] = cnt;
+      }
+      __syncthreads();
+      unsigned v = 0, incl = 0;
+      if (tid < R * 16) {
+        incl = v = hist[tid];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const unsigned t = __shfl_up(incl, o, 64);
+          if (lane >= o) incl += t;
+        }
+        if (lane == 63) wsum[w] = incl;
+      }
+      __syncthreads();
+      if (tid < R * 16) {
+        for (int i = 0; i < w; ++i) incl += wsum[i];
+        hist[tid] = incl - v;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int i = tid + 1024 * r;
+        const bool f = kept(r);
+        const unsigned before = hist[r * 16 + w] + __popcll(__ballot(f) & ((1ull << lane) - 1ull));
+        if (f) keep[before] = i;
+        else if (i < n) evict[(unsigned)i - before] = i;
+      }
+      if (tid == 0) { n_keep[unit] = k; n_evict[unit] = n - k; }
+      return;
+    }
+  }
   // ordered emission
   unsigned kb = 0, eb = 0, qb = 0;
   for (int base = 0; base < n; base += 1024) {
@@ -900,7 +986,7 @@ __global__ __launch_bounds__(1024) void k_select(const float* __restrict__ score
     if (in) {
       if (mode == 0) f = true;
       else if (mode == 2) {
-        const uint32_t key = key_of(i);
+        const uint32_t key = key_from(sc[i], ps[i]);
         if (key > T) f = true;
         else if (key == T) {
           if (all_ties) f = true;

@@ -554,9 +554,15 @@ int32_t im_topb_select(im_handle* h, const float* scores, const im_state* st, in
   int rc = ensure_ws(h, s);
   if (rc) return rc;
   const im_config& c = h->cfg;
-  k_select<<<n_sets(c), 1024, 0, s>>>(scores, st->pos, st->len, c.capacity, h->max_live,
-                                                  budget, c.n_sink, c.n_recent, keep_idx, evict_idx,
-                                                  n_keep, n_evict, status_ptr(h));
+  const int live = h->max_live;
+#define IM_SELECT(R)                                                                                               \
+  k_select<R><<<n_sets(c), 1024, 0, s>>>(scores, st->pos, st->len, c.capacity, live, budget, c.n_sink, c.n_recent, \
+                                         keep_idx, evict_idx, n_keep, n_evict, status_ptr(h))
+  if (live <= 4 * 1024) IM_SELECT(4);
+  else if (live <= 8 * 1024) IM_SELECT(8);
+  else if (live <= 16 * 1024) IM_SELECT(16);
+  else IM_SELECT(0);
+#undef IM_SELECT
   return launch_check(h, "im_topb_select");
 }
 
