@@ -27,7 +27,7 @@ struct im_handle {
   size_t off_status, off_qy, off_alpha, off_mem, off_attn, off_dpart, off_dcand, off_dqm, off_xk, off_hspart, total;
   size_t off_xcount, off_xexp, off_xplanes, off_xlist;              // exact products
   size_t off_qf, off_al16, off_qblk, off_recu, off_reci, off_nlist, off_list;   // scores of many queries
-  int mem_split, attn_chunks, dec_splits;
+  int attn_chunks, dec_splits;
   size_t rec_keys;   // (group, key) records of a scan that the workspace holds
   // optional kernel timing (im_profile_start / im_profile_stop)
   hipEvent_t* prof_ev;
@@ -125,15 +125,15 @@ size_t n_sets_of(const im_config* c) { return (size_t)c->batch * (c->head_shared
 // rows x 8 heads: 99 us with 256 workgroups, 105 with 384, 86 with 768).  A tile of 32 rows
 // takes a workgroup 5 us per head, a partial of 64 KB far less.  8 units x 1167 rows: 2 splits 79 us, 24 splits 14 us;
 // 8 units x 4096 rows: 8 splits 68 us, 64 splits 23 us.
-int mem_splits(const im_config* c, long long live) {
-  const long long sets = n_sets_of(c), rows = c->head_shared ? 32 : 64;
-  const long long n = (live + rows - 1) / rows, most = ((c->head_shared ? 1024 : 512) + sets - 1) / sets;
+int splits_of(long long live, long long rows, long long wgs, long long sets) {
+  const long long n = (live + rows - 1) / rows, most = (wgs + sets - 1) / sets;
   return (int)(n < most ? n : most);
 }
-
+int mem_splits(const im_config* c, long long live) {
+  return c->head_shared ? splits_of(live, 32, 1024, n_sets_of(c)) : splits_of(live, 64, 512, n_sets_of(c));
+}
 void layout(const im_config* c, im_handle* h) {
   const size_t B = c->batch, Hi = c->n_idx_heads, units = (size_t)c->batch * c->n_kv_heads;
-  h->mem_split = mem_splits(c, c->capacity);
   h->attn_chunks = (c->capacity + IM_ATT_CHUNK - 1) / IM_ATT_CHUNK;
   size_t off = 0;
   // status word (in a 32-word slot of its own), then one newest-position word per unit
@@ -141,7 +141,7 @@ void layout(const im_config* c, im_handle* h) {
   h->dec_splits = (c->capacity + DEC_KEYS - 1) / DEC_KEYS + 1;   // + the last-slot record
   h->off_qy = off;     off = align256(off + B * c->max_queries * Hi * IM_DI * sizeof(double));
   h->off_alpha = off;  off = align256(off + B * c->max_queries * Hi * sizeof(double));
-  h->off_mem = off;    off = align256(off + (size_t)n_sets_of(c) * h->mem_split * (IM_DM * IM_D + IM_DM) * sizeof(float));
+  h->off_mem = off;    off = align256(off + n_sets_of(c) * mem_splits(c, c->capacity) * (IM_DM * IM_D + IM_DM) * sizeof(float));
   h->off_attn = off;   off = align256(off + B * c->n_q_heads * h->attn_chunks * IM_ATT_REC * sizeof(float));
   h->off_dpart = off;  off = align256(off + units * h->dec_splits * DEC_GMAX * DEC_REC * sizeof(float));  // upper bound: G <= 8
   h->off_dcand = off;  off = align256(off + units * h->dec_splits * DEC_CAND * sizeof(uint32_t));
@@ -164,9 +164,18 @@ void layout(const im_config* c, im_handle* h) {
   h->off_xplanes = off; off = align256(off + (exact ? np * xk * 4 : 0));
   h->off_xlist = off;  off = align256(off + (exact ? (XG_LIST_A + XG_LIST_B) * sizeof(int2) : 0));
   // head_shared: U_k X of the rows of one append, fp64
+  const size_t common = off;
   h->off_xk = off;     off = align256(off + (c->head_shared ? B * c->capacity * IM_DI_SHARED * sizeof(double) : 0));
   h->off_hspart = off; off = align256(off + (c->head_shared ? B * HS_NSC * sizeof(uint4) : 0));
   h->total = off;
+  if (c->head_shared) {   // (a head-shared workspace is at least what the per-unit layout of the shape takes, and its own part)
+    im_config u = *c;
+    u.head_shared = 0;
+    u.idx_dim = IM_DI;
+    im_handle t;
+    layout(&u, &t);
+    if (common < t.total) h->total += t.total - common;
+  }
 }
 
 int launch_check(im_handle* h, const char* what) {
@@ -516,7 +525,9 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
   }
   // fewer queries than indexer heads (a decode step): the heads of a query are the scoring product's columns
   if (n_q < c.n_idx_heads) {
-    const bool raw = n_q <= 4;   // (every wave normalises them; more queries take a launch for it)
+    // every wave normalises for itself (0.7 us a query) where few share a SIMD: 1176 waves 4.7 -> 6.9 us and a launch of 3.7
+    // less, 4224 waves 8.5 -> 14.1; more queries or keys take k_qnorm_alpha
+    const bool raw = n_q <= 4 && (long long)((h->max_live + 15) / 16) * units <= 2048;
     const int rows = M * c.n_idx_heads;
     if (!raw)
       k_qnorm_alpha<<<(rows + 3) / 4 + (rows + 255) / 256, 256, 0, s>>>(qy, rows, di, (const bf16_t*)p->norm_q_w,
