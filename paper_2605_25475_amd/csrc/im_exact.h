@@ -145,7 +145,8 @@ __global__ __launch_bounds__(256) void k_exact_prep(const bf16_t* __restrict__ A
 // that copied 8 values of A turns them into digits one step ahead, between the products.  A step has two halves of 16
 // products; the operands of a half are read from LDS during the half before it (read at the top of a step, by all
 // waves at once, they took 1024 cycles of the LDS in which no product ran), so the step's barrier lies between
-// its halves.
+// its halves.  65536 x 512 x 4096: 1563 us (1737 with the operands read at the top of a step and 8 rows per wave's copy); the
+// clock is 2.04 GHz under it.  fp64 matrix cores: 4441 us.
 __global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict__ A, const char* __restrict__ planes,
                                                        const int32_t* __restrict__ expA,
                                                        const int32_t* __restrict__ expB, double* __restrict__ C, int M,

@@ -107,7 +107,9 @@ size_t score_rec_keys(size_t sets, size_t capacity) {
   return all < few ? all : few;
 }
 
-// up to this many keys a wave of k_score_exact takes 4 instead of 16: 12000 keys 27 -> 17 us, 65536 keys 54 -> 58
+// Up to this many keys a wave of k_score_exact takes 4 instead of 16, which it evaluates in turn: 12000 keys 27 -> 17 us,
+// 32768 of the head-shared layout 28 -> 28, 65536 keys 54 -> 58 (before the heads' sums were taken together; with
+// that 13, 22 and 39 us).
 #define IM_EXACT_FEW 32768
 // The query projection of M rows goes through the exact int8 product (im_exact.h) where it has more than 2048 tiles
 // of 16 x 16: below, its 64 x 128 tiles leave most of the chip idle and the fp64 kernel that splits the contraction is
@@ -239,6 +241,7 @@ void gemm_nt(hipStream_t s, const bf16_t* A, const bf16_t* B, double* Cm, int M,
   if (Kd % 32 != 0) {
     k_gemm_nt_f64<<<dim3((N + 63) / 64, (M + 63) / 64), 256, 0, s>>>(A, B, Cm, M, N, Kd);
   } else if (Kd % 512 == 0 && gemm_tiles(M, N) <= 512) {
+    // (the gates of 4096 queries: 20 us with 4 waves a tile, 15 with 16; of 32768: 95 with 4 or 8)
     k_gemm_nt_mfma_split<16><<<dim3((N + 15) / 16, (M + 15) / 16), 1024, 0, s>>>(A, B, Cm, M, N, Kd);
   } else if (Kd % 128 == 0 && (N <= 16 || gemm_tiles(M, N) <= 2048)) {
     k_gemm_nt_mfma_split<4><<<dim3((N + 15) / 16, (M + 15) / 16), 256, 0, s>>>(A, B, Cm, M, N, Kd);
