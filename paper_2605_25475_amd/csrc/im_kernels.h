@@ -1381,15 +1381,21 @@ __global__ __launch_bounds__(256) void k_mem_finalize(float* __restrict__ M, flo
   if (e >= IM_DM * IM_D + IM_DM) return;
   const int bps = im_mem_blocks_per_split(ne, fold_block, n_split);
   const int active = ((ne + fold_block - 1) / fold_block + bps - 1) / bps;
-  float s = 0.f;
+  // 8 partials in flight (one past the end repeats the last, unused), added as a tree, and 8 of these sums in one of their own:
+  // the error grows with the length of the chain (3072 rows in 96 partials: that of b is 1.4e-7 added one after
+  // another, in 24 partials of 128 rows 7.5e-8, as here 5.0e-8)
+  float s = 0.f, s64 = 0.f;
   const float* src = part + (size_t)unit * n_split * (IM_DM * IM_D + IM_DM) + e;
-  for (int s0 = 0; s0 < active; s0 += 8) {   // 8 partials in flight (one past the end repeats the last, unused)
+  for (int s0 = 0; s0 < active; s0 += 8) {
     float v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = src[(size_t)min(s0 + i, active - 1) * (IM_DM * IM_D + IM_DM)];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s += (s0 + i < active) ? v[i] : 0.f;
+    for (int i = 0; i < 8; ++i) v[i] = (s0 + i < active) ? v[i] : 0.f;
+    s64 += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+    if ((s0 & 56) == 56) { s += s64; s64 = 0.f; }
   }
+  s += s64;
   float* dst = (e < IM_DM * IM_D) ? (M + (size_t)unit * IM_DM * IM_D + e)
                                   : (bvec + (size_t)unit * IM_DM + (e - IM_DM * IM_D));
   *dst = fmaf(lambda, *dst, eta * s);
