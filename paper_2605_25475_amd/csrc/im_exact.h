@@ -5,10 +5,13 @@
 // integers of a common unit, x = X 2^(E - 149) with E the row's largest (biased) exponent, so |X| <= 255 2^22, in four
 // signed base-256 digits, and the 16 products of digits, accumulated exactly in 7 int32 sums (one per power of
 // 256), give the exact sum of X W: a third of the time of the fp64 cores.  Elements more than 2^22 below their
-// row's largest lose bits in X: they are listed with their remainder (1 in 2.6 million for Gaussian values) and
-// added in fp64 afterwards; should a list overflow, the fp64 kernel computes the product instead.
-// (A matrix with an infinity or a NaN counts as an overflowed list.)
-//   k_exact_prep : row exponents of A; exponents and digit planes of B
+// row's largest lose bits in X: a row lists up to XG_ROOM of them (1 in 2.6 million values, for Gaussian ones), and their
+// remainders' products are added in fp64 afterwards, in a fixed order.  So an element of C is the exact sum rounded
+// once, where neither its row nor its column lists anything; else, one fp64 sum of the remainders is added to that.
+// A row with more of them, an infinity or a NaN is full: the 64 x 64 tiles of C that it is part of are computed
+// on the fp64 cores instead.
+// Every row writes its count and its exponent anew: nothing is kept from one product to the next.
+//   k_exact_prep : row exponents and lists; digit planes of B
 //   k_exact_gemm : the product
 //   k_exact_fix  : remainders
 #pragma once
@@ -21,18 +24,14 @@ typedef int im_i16 __attribute__((ext_vector_type(16)));
 #define XG_BN 128
 #define XG_BK 64
 #define XG_MAX_K 8192       // sums of 4 digit products stay below 2^29, and the two halves of the result below 2^53
-#define XG_LIST_A 65536     // listed elements
-#define XG_LIST_B 4096
-// counters: [0] listed elements of A, [1] of B.  Entries: (row, k).  k_score_features clears the counters for
-// the next product.
+#define XG_ROOM 8           // listed elements of a row
+#define XG_FULL (XG_ROOM + 1)
+// Rows of A, then of B: the number of listed elements (or XG_FULL), and their k, ascending.
 struct ExactLists {
-  int32_t* count;
-  int2 *a, *b;
+  int32_t *countA, *countB;
+  uint16_t *a, *b;   // [row][XG_ROOM]
 };
 
-__device__ __forceinline__ bool exact_overflow(const ExactLists& l) {
-  return l.count[0] > XG_LIST_A || l.count[1] > XG_LIST_B;
-}
 // the scale 2^(149 - E) that makes a row's elements integers; rows of very small numbers take a larger unit
 __device__ __forceinline__ int exact_clamp_exp(int e) { return max(e, 40); }
 __device__ __forceinline__ float exact_scale(int e) { return __uint_as_float((uint32_t)(127 + 156 - e) << 23); }
@@ -46,8 +45,8 @@ __device__ __forceinline__ int exact_max_exp(const uint4& u, int e) {
   return e;
 }
 
-// lists those of 8 values (row, k ..) that X truncates
-__device__ __forceinline__ void exact_list(const uint4& u, float scale, int row, int k, int32_t* count, int2* list, int room) {
+// which of 8 values X truncates
+__device__ __forceinline__ uint32_t exact_lost(const uint4& u, float scale) {
   const uint32_t v[4] = {u.x, u.y, u.z, u.w};
   uint32_t lost = 0;
 #pragma unroll
@@ -55,12 +54,7 @@ __device__ __forceinline__ void exact_list(const uint4& u, float scale, int row,
     const float f = ((i & 1) ? bf_hi(v[i >> 1]) : bf_lo(v[i >> 1])) * scale;
     lost |= (f != truncf(f)) ? 1u << i : 0u;
   }
-  while (lost) {   // (in practice a handful in the whole matrix)
-    const int i = __builtin_ctz(lost);
-    lost &= lost - 1;
-    const int at = atomicAdd(count, 1);
-    if (at < room) list[at] = make_int2(row, k + i);
-  }
+  return lost;
 }
 
 // 8 values -> their 4 digit planes (8 bytes each, lowest digit first)
@@ -117,26 +111,40 @@ __global__ __launch_bounds__(256) void k_exact_prep(const bf16_t* __restrict__ A
   for (int i = 0; i < XG_MAX_K / 512; ++i)
     if (i * 512 < K) e = exact_max_exp(v[i], e);
   e = exact_clamp_exp((int)wave_max_u((uint32_t)e));
-  if (lane == 0) {
-    (isb ? expB : expA)[row] = e;
-    if (e == 255) atomicOr(lists.count + (isb ? 1 : 0), 1 << 30);   // an infinity or a NaN: the fp64 kernel's case
-  }
+  if (lane == 0) (isb ? expB : expA)[row] = e;
   const float scale = row < N || !isb ? exact_scale(e) : 0.f;
+  unsigned long long lost[2] = {0ull, 0ull};   // of this lane's values: 8 bits per piece
 #pragma unroll
   for (int i = 0; i < XG_MAX_K / 512; ++i) {
     const int k = i * 512 + lane * 8;
     if (i * 512 >= K || k >= K) continue;
-    if (!isb) {
-      exact_list(v[i], scale, row, k, lists.count, lists.a, XG_LIST_A);
-      continue;
-    }
-    exact_list(v[i], scale, row, k, lists.count + 1, lists.b, XG_LIST_B);
+    lost[i / 8] |= (unsigned long long)exact_lost(v[i], scale) << (8 * (i % 8));
+    if (!isb) continue;
     uint2 pl[4];
     exact_digits(v[i], scale, pl);
     char* dst = planes + ((size_t)(row / 32) * (K / 32) + k / 32) * 4096 + exact_place(row, (k / 8) & 3);
 #pragma unroll
     for (int d = 0; d < 4; ++d) *(uint2*)(dst + d * 1024) = pl[d];
   }
+  int count = e == 255 ? XG_FULL : 0;
+  if (__any((lost[0] | lost[1]) != 0ull)) {   // (in practice a handful of rows in the whole matrix)
+    uint16_t* list = (isb ? lists.b : lists.a) + (size_t)row * XG_ROOM;
+    for (int i = 0; i * 512 < K && count < XG_FULL; ++i) {
+      const uint32_t bits = (uint32_t)((i < 8 ? lost[0] : lost[1]) >> (8 * (i & 7))) & 255u;
+      unsigned long long lanes = __ballot(bits != 0u);
+      while (lanes && count < XG_FULL) {
+        const int ln = __builtin_ctzll(lanes);
+        lanes &= lanes - 1;
+        uint32_t of = (uint32_t)__builtin_amdgcn_readlane((int)bits, ln);
+        while (of && count < XG_FULL) {
+          if (count < XG_ROOM && lane == 0) list[count] = (uint16_t)(i * 512 + ln * 8 + __builtin_ctz(of));
+          of &= of - 1;
+          ++count;
+        }
+      }
+    }
+  }
+  if (lane == 0) (isb ? lists.countB : lists.countA)[row] = count;
 }
 
 // grid (ceil(M / XG_BM) * Np / XG_BN), 8 waves as 2 x 4; a wave owns a 32 x 32 tile of C in 7 int32 accumulators.
@@ -267,29 +275,37 @@ __global__ __launch_bounds__(512, 2) void k_exact_gemm(const bf16_t* __restrict_
   }
 }
 
-// remainders of the listed elements: of A against the whole of B, then of B against the integers of A.
-// Grid-stride over the lists (usually a few entries); with an overflowed list, over the tiles of the fp64 product.
+// remainders: grid (ceil(N / 64) * ceil(M / 64)), a workgroup per 64 x 64 tile of C, which returns at once where nothing is
+// listed.  One thread owns an element: those of its row of A against the whole of B, then those of its row of B
+// against the integers of A, each in ascending order of k.
 __global__ __launch_bounds__(256) void k_exact_fix(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B, int M, int N, int K,
                                                    const int32_t* __restrict__ expA, const int32_t* __restrict__ expB,
                                                    double* __restrict__ C, ExactLists lists) {
-  if (exact_overflow(lists)) {
-    const int tx = (N + 63) / 64, tiles = tx * ((M + 63) / 64);
-    for (int t = blockIdx.x; t < tiles; t += gridDim.x) gemm_nt_tile<2, 2>(A, B, C, M, N, K, t % tx, t / tx);
+  __shared__ int counts[128];
+  const int tx = (N + 63) / 64, bx = blockIdx.x % tx, by = blockIdx.x / tx, m0 = by * 64, n0 = bx * 64, tid = threadIdx.x;
+  int mine = 0;
+  if (tid < 64) mine = (m0 + tid < M) ? lists.countA[m0 + tid] : 0;
+  else if (tid < 128) mine = (n0 + tid - 64 < N) ? lists.countB[n0 + tid - 64] : 0;
+  if (tid < 128) counts[tid] = mine;
+  if (!__syncthreads_or(mine)) return;
+  if (__syncthreads_or(mine > XG_ROOM)) {
+    gemm_nt_tile<2, 2>(A, B, C, M, N, K, bx, by);
     return;
   }
-  const int na = lists.count[0], nb = lists.count[1];
-  for (int i = blockIdx.x; i < na; i += gridDim.x) {
-    const int2 mk = lists.a[i];
-    const double r = exact_rest(A[(size_t)mk.x * K + mk.y], expA[mk.x]);
-    for (int n = threadIdx.x; n < N; n += 256)
-      atomicAdd(C + (size_t)mk.x * N + n, r * (double)bf2f(B[(size_t)n * K + mk.y]));
-  }
-  for (int i = 0; i < nb; ++i) {
-    const int2 nk = lists.b[i];
-    const double r = exact_rest(B[(size_t)nk.x * K + nk.y], expB[nk.x]);
-    for (int m = blockIdx.x * 256 + threadIdx.x; m < M; m += gridDim.x * 256) {
-      const bf16_t x = A[(size_t)m * K + nk.y];
-      atomicAdd(C + (size_t)m * N + nk.x, r * ((double)bf2f(x) - exact_rest(x, expA[m])));
+  for (int i = tid; i < 64 * 64; i += 256) {
+    const int m = m0 + (i >> 6), n = n0 + (i & 63), ca = counts[i >> 6], cb = counts[64 + (i & 63)];
+    if (ca + cb == 0 || m >= M || n >= N) continue;
+    const bf16_t *ar = A + (size_t)m * K, *br = B + (size_t)n * K;
+    const int ea = expA[m], eb = expB[n];
+    double sum = 0.0;
+    for (int j = 0; j < ca; ++j) {
+      const int k = lists.a[(size_t)m * XG_ROOM + j];
+      sum = fma(exact_rest(ar[k], ea), (double)bf2f(br[k]), sum);
     }
+    for (int j = 0; j < cb; ++j) {
+      const int k = lists.b[(size_t)n * XG_ROOM + j];
+      sum = fma(exact_rest(br[k], eb), (double)bf2f(ar[k]) - exact_rest(ar[k], ea), sum);
+    }
+    C[(size_t)m * N + n] += sum;
   }
 }

@@ -66,8 +66,7 @@ __global__ __launch_bounds__(1024) void k_score_features(const double* __restric
                                                          const bf16_t* __restrict__ norm_w, float rms_eps,
                                                          double alpha_denom, int n_q, int H_idx,
                                                          float* __restrict__ qf, float* __restrict__ al16,
-                                                         char* __restrict__ blocks, int32_t* __restrict__ n_listed,
-                                                         int32_t* __restrict__ exact_count) {
+                                                         char* __restrict__ blocks, int32_t* __restrict__ n_listed) {
   using SB = ScoreBlock<DI, HM>;
   constexpr int HP = 64 / DI, NP = HM / HP;   // heads per pass of a wave, passes
   __shared__ __attribute__((aligned(16))) char sb[SB::BYTES];
@@ -82,7 +81,6 @@ __global__ __launch_bounds__(1024) void k_score_features(const double* __restric
   const float nw = norm_w ? bf2f(norm_w[d]) : 1.f;
   const int my_pos = q_pos[row];
   if (blockIdx.x == 0 && tid == 0) n_listed[b] = 0;
-  if (blockIdx.x == 0 && b == 0 && tid < 2) exact_count[tid] = 0;   // (the product's lists have been used)
   for (int i = tid; i < SB::BYTES / 4; i += 1024) ((uint32_t*)sb)[i] = 0;
   __syncthreads();
   float* rows = (float*)(sb + SB::OFF);

@@ -25,7 +25,7 @@ struct im_handle {
   bool ws_ready;
   // workspace layout (byte offsets)
   size_t off_status, off_qy, off_alpha, off_mem, off_attn, off_dpart, off_dcand, off_dqm, off_xk, off_hspart, total;
-  size_t off_xcount, off_xexp, off_xplanes, off_xlist;              // exact products
+  size_t off_xexp, off_xcount, off_xplanes, off_xlist;              // exact products
   size_t off_qf, off_al16, off_qblk, off_recu, off_reci, off_nlist, off_list;   // scores of many queries
   int attn_chunks, dec_splits;
   size_t rec_keys;   // (group, key) records of a scan that the workspace holds
@@ -160,11 +160,12 @@ void layout(const im_config* c, im_handle* h) {
   h->off_list = off;   off = align256(off + sets * c->capacity * sizeof(int2));
   // exact products: the largest one is the query projection
   const size_t np = exact_np(c), xk = (size_t)c->n_q_heads * IM_D;
-  const bool exact = exact_fits(c, c->batch * c->max_queries);
-  h->off_xcount = off; off = align256(off + 2 * sizeof(int32_t));
-  h->off_xexp = off;   off = align256(off + (exact ? (rows + np) * sizeof(int32_t) : 0));
+  const bool exact = exact_fits(c, (long long)c->batch * c->max_queries);
+  const size_t xrows = exact ? rows + np : 0;
+  h->off_xexp = off;   off = align256(off + xrows * sizeof(int32_t));
+  h->off_xcount = off; off = align256(off + xrows * sizeof(int32_t));
+  h->off_xlist = off;  off = align256(off + xrows * XG_ROOM * sizeof(uint16_t));
   h->off_xplanes = off; off = align256(off + (exact ? np * xk * 4 : 0));
-  h->off_xlist = off;  off = align256(off + (exact ? (XG_LIST_A + XG_LIST_B) * sizeof(int2) : 0));
   // head_shared: U_k X of the rows of one append, fp64
   const size_t common = off;
   h->off_xk = off;     off = align256(off + (c->head_shared ? B * c->capacity * IM_DI_SHARED * sizeof(double) : 0));
@@ -190,7 +191,6 @@ int ensure_ws(im_handle* h, hipStream_t s) {
   if (h->ws_ready) return IM_OK;
   const int n_words = 32 + h->cfg.batch * h->cfg.n_kv_heads;
   k_fill_i32<<<(n_words + 255) / 256, 256, 0, s>>>((int32_t*)(h->ws + h->off_status), n_words, 0);
-  k_fill_i32<<<1, 64, 0, s>>>((int32_t*)(h->ws + h->off_xcount), 2, 0);
   int rc = launch_check(h, "workspace clear");
   if (rc == IM_OK) h->ws_ready = true;
   return rc;
@@ -257,14 +257,15 @@ void exact_project(im_handle* h, hipStream_t s, const bf16_t* q, const bf16_t* U
   const im_config& c = h->cfg;
   const int N = c.n_idx_heads * c.idx_dim, K = c.n_q_heads * IM_D, np = (int)exact_np(&c);
   int32_t* expA = (int32_t*)(h->ws + h->off_xexp);
-  int32_t* expB = expA + (size_t)c.batch * c.max_queries;
+  const size_t rows = (size_t)c.batch * c.max_queries;   // (the rows of B come behind those of A)
+  int32_t *expB = expA + rows, *count = (int32_t*)(h->ws + h->off_xcount);
+  uint16_t* list = (uint16_t*)(h->ws + h->off_xlist);
   char* planes = h->ws + h->off_xplanes;
-  const ExactLists lists = {(int32_t*)(h->ws + h->off_xcount), (int2*)(h->ws + h->off_xlist),
-                            (int2*)(h->ws + h->off_xlist) + XG_LIST_A};
+  const ExactLists lists = {count, count + rows, list, list + rows * XG_ROOM};
   k_exact_prep<<<(M + 3) / 4 + (np + 3) / 4, 256, 0, s>>>(q, Uq, M, N, np, K, expA, expB, planes, lists);
   const int nt = np / XG_BN, mt = (M + XG_BM - 1) / XG_BM, per = 8 % nt == 0 ? 8 / nt : 1;
   k_exact_gemm<<<(mt + per - 1) / per * per * nt, 512, 0, s>>>(q, planes, expA, expB, y, M, N, np, K);
-  k_exact_fix<<<512, 256, 0, s>>>(q, Uq, M, N, K, expA, expB, y, lists);
+  k_exact_fix<<<(N + 63) / 64 * ((M + 63) / 64), 256, 0, s>>>(q, Uq, M, N, K, expA, expB, y, lists);
 }
 
 // the scores of n_q >= H_idx queries from their raw projections in the workspace
@@ -284,7 +285,7 @@ void score_many(im_handle* h, const im_state* st, const bf16_t* norm_q_w, const 
   const bf16_t* Kidx = (const bf16_t*)st->Kidx;
   k_score_features<DI, HM><<<dim3(nblk, c.batch), 1024, 0, s>>>((const double*)(ws + h->off_qy),
       (const double*)(ws + h->off_alpha), q_pos, norm_q_w, c.rms_eps, alpha_denom, n_q, c.n_idx_heads, qf, al16, blocks,
-      n_listed, (int32_t*)(ws + h->off_xcount));
+      n_listed);
   // a scan over a short cache has few (256-key tile, unit) workgroups: its query blocks then go in up to
   // IM_SCORE_GROUPS groups with workgroups of their own; a very short one also drops to 16 keys per wave
   const long long tiles4 = (long long)((live + 255) / 256) * units;

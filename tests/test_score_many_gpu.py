@@ -77,10 +77,14 @@ def _shrink(t, share, seed):
     return torch.where(small, (t.float() * 2.0 ** -26).to(torch.bfloat16), t)
 
 
-@pytest.mark.parametrize("share_q,share_u", [(0.0, 0.0), (0.002, 0.0), (0.002, 0.0005), (0.0, 0.01), (0.05, 0.0)],
-                         ids=["plain", "lists-q", "lists-both", "overflow-u", "overflow-q"])
-@pytest.mark.parametrize("heads,n_q,shared", [((32, 8), 1089, False), ((28, 4), 1207, False), ((32, 8), 2081, True)],
-                         ids=["512", "448", "128"])   # columns of the query projection
+# (a row lists 8 values at most: 1 to 2 a row stay below that, 8 a row put most tiles on the fp64 cores)
+@pytest.mark.parametrize("share_q,share_u", [(0.0, 0.0), (0.0003, 0.0), (0.0, 0.0003), (0.0003, 0.0003), (0.002, 0.0), (0.002, 0.0005),
+                                             (0.0, 0.01), (0.05, 0.0)],
+                         ids=["plain", "few-q", "few-u", "few-both", "lists-q", "lists-both", "overflow-u", "overflow-q"])
+@pytest.mark.parametrize("heads,n_q,shared", [((32, 8), 1089, False), ((28, 4), 1207, False), ((32, 8), 2081, True),
+                                              ((24, 8), 701, False), ((40, 8), 430, False), ((64, 8), 270, False),
+                                              ((26, 13), 700, False)],
+                         ids=["512", "448", "128", "384", "640", "1024", "384-k3328"])   # columns of the query projection
 def test_query_projection_as_an_exact_product(heads, n_q, shared, share_q, share_u):
     # row counts that are no multiple of the product's 64-row tiles; 448 columns are no multiple of its 128
     n = 40
