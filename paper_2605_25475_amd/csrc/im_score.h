@@ -592,7 +592,8 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_listed(const bf1
 #pragma unroll
           for (int r = 0; r < 4; ++r) acc[r] = fmaf(a4[i][r], fabsf(zz[i][r]), acc[r]);
       }
-      const float bar = best * key.scale;
+      // (a finite score may be infinite in the bounds' units: an infinite bound stays above it)
+      const float bar = (best == INFINITY) ? INFINITY : fminf(best * key.scale, 3.402823466e38f);
       // (negated: a key without bounds is a hit)
       const bool hit = (qp.x >= pk && !(acc[0] <= bar)) || (qp.y >= pk && !(acc[1] <= bar)) ||
                        (qp.z >= pk && !(acc[2] <= bar)) || (qp.w >= pk && !(acc[3] <= bar));

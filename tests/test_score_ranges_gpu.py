@@ -1,0 +1,49 @@
+"""im_index_score of many queries at the ends of the number range: bounds that are infinite.  The scores must be the oracle's fp32 numbers."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_25475_amd as im
+from helpers import f64
+from parity import LockStep, LockStepShared
+from workloads import WORKLOADS
+
+pytestmark = pytest.mark.gpu
+
+
+def _high(p):
+    # bounds of infinity, and keys whose scale takes a score in the bounds' units beyond fp32
+    p["G"] = (p["G"].float() * 2.0 ** 60).to(torch.bfloat16)
+    p["norm_q_w"] = (p["norm_q_w"].float() * 2.0 ** 66).to(torch.bfloat16)
+    p["norm_k_w"] = (p["norm_k_w"].float() * 2.0 ** -60).to(torch.bfloat16)
+
+
+MODES = {"high": _high}
+
+
+@pytest.mark.parametrize("mode", sorted(MODES))
+@pytest.mark.parametrize("heads", [(32, 8), (28, 4)], ids=["8", "7"])   # indexer heads
+@pytest.mark.parametrize("shared", [False, True], ids=["per-unit", "head-shared"])
+def test_scores_at_the_ends_of_the_range(mode, heads, shared):
+    n_q, n = 400, 100   # 25 blocks of queries in 8 groups: most candidates come from the list
+    kw = dict(context=n_q, budget=n, decode_steps=0, batch=2, n_layers=1, n_q_heads=heads[0], n_kv_heads=heads[1])
+    w = WORKLOADS["cfg1"].shared(**kw) if shared else WORKLOADS["cfg1"].scaled(**kw)
+    ls = (LockStepShared if shared else LockStep)(w, params_mod=MODES[mode])
+    g, ref, d = ls.gpu, ls.ref, (lambda t: t.contiguous().cuda())
+    pos = torch.arange(n, dtype=torch.int32).repeat(w.batch, 1).contiguous()
+    q = ls.Q[:, :n_q].contiguous()
+    xg = q.view(w.batch, n_q, -1).clone()
+    if shared:
+        im.im_append_kv_hidden(ls.handle, ls.params, g.st, d(ls.K[:, :, :n]), d(ls.V[:, :, :n]), d(ls.X[:, :n]), d(pos))
+        ref.append_kv_hidden(f64(ls.K[:, :, :n]), f64(ls.V[:, :, :n]), f64(ls.X[:, :n]), pos.numpy())
+    else:
+        im.im_append_kv(ls.handle, g.st, d(ls.K[:, :, :n]), d(ls.V[:, :, :n]), d(pos))
+        ref.append_kv(f64(ls.K[:, :, :n]), f64(ls.V[:, :, :n]), pos.numpy())
+    qpos = torch.full((w.batch, n_q), n, dtype=torch.int32)
+    want = ref.index_score(f64(q), f64(xg), qpos.numpy())[..., :n]
+    im.im_index_score(ls.handle, ls.params, g.st, d(q), d(xg), d(qpos), g.scores)
+    torch.cuda.synchronize()
+    got = g.scores[..., :n].cpu().numpy().astype(np.float64)
+    assert np.isfinite(want).all()
+    wrong = int((got != want).sum())
+    assert wrong == 0, f"{wrong} of {want.size} scores differ"
