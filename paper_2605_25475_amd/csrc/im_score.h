@@ -177,7 +177,9 @@ __global__ __launch_bounds__(1024) void k_score_features(const double* __restric
     if constexpr (DI == 64) r2 = wave_sum_f(r2); else r2 = row16_sum_f(r2);
     sane = sane && score_sane(cn);
     err += (1.001f * sqrtf(r2) + 0x1p-16f * cn * f) / f;
-    sane = __all(sane && isfinite(err));
+    // (err is at least 2^-16 of what the sum of the heads' terms can reach: below 2^80 no part of that sum is infinite, and an
+    // infinity of either sign cannot meet one of the other)
+    sane = __all(sane && err < 0x1p80f);
     if (lane < DI) *(_Float16*)(sb + HM * SB::HEAD + place) = sane ? hv : (_Float16)0.f;
     if (!sane) {   // (operands of zero: infinities and NaN stay out of the sum, whose bound is then infinite)
       for (int j = hl; j < H_idx; j += HP) {

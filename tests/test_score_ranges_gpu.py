@@ -1,4 +1,5 @@
-"""im_index_score of many queries at the ends of the number range: bounds that are infinite.  The scores must be the oracle's fp32 numbers."""
+"""im_index_score of many queries at the ends of the number range: bounds that are infinite, or
+would be.  The scores must be the oracle's fp32 numbers."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +12,12 @@ from workloads import WORKLOADS
 pytestmark = pytest.mark.gpu
 
 
+def _first_column(p, rows):
+    """Gates that read the first value of the gate input alone: alpha_j = rows[j] x_0 / sqrt(H_idx d_idx)."""
+    p["G"].zero_()
+    p["G"][:, 0] = torch.tensor(rows, dtype=torch.float64).to(torch.bfloat16)
+
+
 def _high(p):
     # bounds of infinity, and keys whose scale takes a score in the bounds' units beyond fp32
     p["G"] = (p["G"].float() * 2.0 ** 60).to(torch.bfloat16)
@@ -18,7 +25,21 @@ def _high(p):
     p["norm_k_w"] = (p["norm_k_w"].float() * 2.0 ** -60).to(torch.bfloat16)
 
 
-MODES = {"high": _high}
+def _opposite(p):
+    # heads (u, -u, w, -w) with gates (a, a, -a, -a): the linear part of the bound vanishes, S = a |u k| - a |w k|, and
+    # the two parts are beyond fp32 in the bounds' units although every single factor is inside them
+    U, Hi, di = p["Uq"], p["G"].shape[0], p["norm_q_w"].shape[0]
+    rows = [0.0] * Hi
+    for j in range(0, Hi - 3, 4):
+        for s in (0, 2):
+            U[(j + s + 1) * di:(j + s + 2) * di] = -U[(j + s) * di:(j + s + 1) * di]
+            rows[j + s] = rows[j + s + 1] = (1.1e18 if s == 0 else -1.1e18) * (Hi * di) ** 0.5
+    _first_column(p, rows)
+    p["norm_q_w"].fill_(1.12e18 / di ** 0.5)
+    p["norm_k_w"].fill_(15.9 / di ** 0.5)
+
+
+MODES = {"high": _high, "opposite": _opposite}
 
 
 @pytest.mark.parametrize("mode", sorted(MODES))
@@ -33,6 +54,9 @@ def test_scores_at_the_ends_of_the_range(mode, heads, shared):
     pos = torch.arange(n, dtype=torch.int32).repeat(w.batch, 1).contiguous()
     q = ls.Q[:, :n_q].contiguous()
     xg = q.view(w.batch, n_q, -1).clone()
+    if mode != "high":
+        xg[:] = 0
+        xg[:, :, 0] = 1.0
     if shared:
         im.im_append_kv_hidden(ls.handle, ls.params, g.st, d(ls.K[:, :, :n]), d(ls.V[:, :, :n]), d(ls.X[:, :n]), d(pos))
         ref.append_kv_hidden(f64(ls.K[:, :, :n]), f64(ls.V[:, :, :n]), f64(ls.X[:, :n]), pos.numpy())
