@@ -659,8 +659,9 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_listed(const bf1
       best = fmaxf(best, rows_max_f(m));
     }
     if (kq == 0 && k0 + l16 < cnt && best > start) {
-      // fp32 maximum by integer atomics: the bit patterns of non-negative numbers ascend, of negative ones descend
-      if (best >= 0.f) atomicMax((int*)(scores + at), __float_as_int(best));
+      // fp32 maximum by integer atomics: the bit patterns of positive numbers ascend, of negative ones descend (-0.0 is one
+      // of these, the least: a score of -1e-50 rounds to it)
+      if (__float_as_int(best) >= 0) atomicMax((int*)(scores + at), __float_as_int(best));
       else atomicMin((unsigned*)(scores + at), __float_as_uint(best));
     }
   }

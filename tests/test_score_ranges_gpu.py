@@ -1,5 +1,5 @@
-"""im_index_score of many queries at the ends of the number range: bounds that are infinite, or
-would be.  The scores must be the oracle's fp32 numbers."""
+"""im_index_score of many queries at the ends of the number range: bounds that are infinite, or would be, and scores
+that round to a negative zero.  The scores must be the oracle's fp32 numbers."""
 import numpy as np
 import pytest
 import torch
@@ -39,7 +39,14 @@ def _opposite(p):
     p["norm_k_w"].fill_(15.9 / di ** 0.5)
 
 
-MODES = {"high": _high, "opposite": _opposite}
+def _negative_zero(p):
+    # scores of the first 16 queries round to -0.0, the others are large and negative
+    _first_column(p, [-1.0] * p["G"].shape[0])
+    p["norm_q_w"].fill_(2.0 ** -40)
+    p["norm_k_w"].fill_(2.0 ** -40)
+
+
+MODES = {"high": _high, "opposite": _opposite, "negative-zero": _negative_zero}
 
 
 @pytest.mark.parametrize("mode", sorted(MODES))
@@ -57,6 +64,8 @@ def test_scores_at_the_ends_of_the_range(mode, heads, shared):
     if mode != "high":
         xg[:] = 0
         xg[:, :, 0] = 1.0
+    if mode == "negative-zero":
+        xg[:, :16, 0], xg[:, 16:, 0] = 2.0 ** -100, 2.0 ** 100
     if shared:
         im.im_append_kv_hidden(ls.handle, ls.params, g.st, d(ls.K[:, :, :n]), d(ls.V[:, :, :n]), d(ls.X[:, :n]), d(pos))
         ref.append_kv_hidden(f64(ls.K[:, :, :n]), f64(ls.V[:, :, :n]), f64(ls.X[:, :n]), pos.numpy())
@@ -68,6 +77,6 @@ def test_scores_at_the_ends_of_the_range(mode, heads, shared):
     im.im_index_score(ls.handle, ls.params, g.st, d(q), d(xg), d(qpos), g.scores)
     torch.cuda.synchronize()
     got = g.scores[..., :n].cpu().numpy().astype(np.float64)
-    assert np.isfinite(want).all()
+    assert np.isfinite(want).all() and (mode == "negative-zero") == bool((want == 0).all())
     wrong = int((got != want).sum())
     assert wrong == 0, f"{wrong} of {want.size} scores differ"
