@@ -612,6 +612,178 @@ __global__ __launch_bounds__(256) void k_qnorm_alpha(double* __restrict__ y, int
   if (on) y[(size_t)row * di + lane] = (double)(float)(v / rr * w);
 }
 
+// ------------------------------------------------------------------------------------------
+// a1 (iii) for a short window of queries: all pairs on the fp64 matrix cores.  imp[key] = max over the queries that may
+// see the key of sum_j alpha[s][j] ReLU(q[s][j] . k[key]).
+// ------------------------------------------------------------------------------------------
+// grid (ceil(max_live / (64 TPW)), units) read as one list of (tile, unit) pairs, 4 waves; a wave owns
+// TPW tiles of 16 rows (4, or 1 when that gives too few workgroups; the A operand, kept in
+// registers as packed bf16) and walks over the queries 16 at a time.  One pass of the
+// 16x16x4 product (DI / 4 steps over the DI dims) takes ONE indexer head of 16 queries as its 16
+// columns, so a lane's result registers belong to one query and the gated ReLU terms of the heads
+// are added in place, head after head, with no cross-lane step; after the last head the block's
+// scores go into the running maximum under the position mask.  The maxima of the 16 query columns
+// meet once, at the end.  Bound by the fp64 matrix cores: 16 queries x 8 heads of 64 dims against 524288
+// keys 172 us, 50 TFLOP/s.
+// grid z: groups of q_per_group queries (a multiple of 16) with workgroups of their own, group g writing row g * units + unit
+// (of out_stride floats) of `out`: the scores themselves, or partial maxima that k_score_max folds.
+// DI (64 or 16) is the indexer head dim: a lane holds DI / 4 dims of its row, packed in DI / 8 words.
+template <int TPW, int DI>
+__global__ __launch_bounds__(256) void k_score(const bf16_t* __restrict__ Kidx,
+                                               const int32_t* __restrict__ pos,
+                                               const int32_t* __restrict__ len,
+                                               int32_t* __restrict__ n_projected,
+                                               const double* __restrict__ qhat,
+                                               const double* __restrict__ alpha,
+                                               const int32_t* __restrict__ q_pos, int n_q, int H_kv,
+                                               int C, int H_idx, int max_live,
+                                               float* __restrict__ out, int out_stride, int q_per_group) {
+  __shared__ int s_min[4];
+  __shared__ int s_first[4];
+  const int units = gridDim.y, bid = blockIdx.y * gridDim.x + blockIdx.x;
+  const int unit = bid % units, tile = bid / units;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int l16 = lane & 15, kq = lane >> 4;
+  const int b = unit / H_kv;
+  const int n = min(len[unit], max_live);
+  if (tile == 0 && blockIdx.z == 0 && tid == 0) n_projected[unit] = n;  // the projection kernel ran before
+  const int t0 = tile * (64 * TPW);
+  if (t0 >= n) return;
+  const int kbase = t0 + 16 * TPW * w;
+  // A operands: lane (row l16, kq) holds dims 16 kq .. 16 kq + 15 of its row in each of the tiles
+  // (rows past the end repeat the last live one; their scores are never written)
+  constexpr int WPL = DI / 8, DPL = DI / 4;
+  uint32_t ka[TPW][WPL];
+  int posk[TPW][4];
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const size_t row = (size_t)unit * C + min(kbase + 16 * t + l16, n - 1);
+    if constexpr (DI == 64) {
+      const uint4 u0 = *(const uint4*)(Kidx + row * DI + DPL * kq);
+      const uint4 u1 = *(const uint4*)(Kidx + row * DI + DPL * kq + 8);
+      ka[t][0] = u0.x; ka[t][1] = u0.y; ka[t][2] = u0.z; ka[t][3] = u0.w;
+      ka[t][4] = u1.x; ka[t][5] = u1.y; ka[t][6] = u1.z; ka[t][7] = u1.w;
+    } else {
+      static_assert(DI == 16, "indexer head dim 64 or 16");
+      const uint2 u0 = *(const uint2*)(Kidx + row * DI + DPL * kq);
+      ka[t][0] = u0.x; ka[t][1] = u0.y;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {   // positions of the keys of this lane's result registers
+      const int key = kbase + 16 * t + 4 * r + kq;
+      const int p = pos[(size_t)unit * C + min(key, n - 1)];
+      posk[t][r] = (key < n) ? p : INT_MAX;
+    }
+  }
+  // smallest key position of the workgroup's tile, and the first query that sees it: the walk over
+  // the queries starts there (visibility is decided per key further down)
+  int mn = INT_MAX;
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) mn = min(mn, posk[t][r]);
+  mn = (int)(wave_min_u((uint32_t)mn ^ 0x80000000u) ^ 0x80000000u);
+  if (lane == 0) s_min[w] = mn;
+  __syncthreads();
+  const int tile_min = min(min(s_min[0], s_min[1]), min(s_min[2], s_min[3]));
+  const int32_t* qp_b = q_pos + (size_t)b * n_q;
+  int first = n_q;
+  for (int i = tid; i < n_q; i += 256)
+    if (qp_b[i] >= tile_min) { first = i; break; }
+  first = (int)wave_min_u((uint32_t)first);
+  if (lane == 0) s_first[w] = first;
+  __syncthreads();
+  first = min(min(s_first[0], s_first[1]), min(s_first[2], s_first[3]));
+  float imp[TPW][4];
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) imp[t][r] = -INFINITY;
+  const int q_lo = blockIdx.z * q_per_group, q_hi = min(n_q, q_lo + q_per_group);
+  out += ((size_t)blockIdx.z * units + unit) * out_stride;
+#pragma unroll 1
+  for (int s0 = max(first & ~15, q_lo); s0 < q_hi; s0 += 16) {
+    // this lane's query column; columns past the end repeat the last query and are masked
+    const int s = min(s0 + l16, n_q - 1);
+    const bool sv = s0 + l16 < q_hi;
+    const int qp = qp_b[s];
+    double acc[TPW][4];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[t][r] = 0.0;
+#pragma unroll 1
+    for (int j = 0; j < H_idx; ++j) {
+      // B operand: lane (column l16 = query s, kq) holds dims DPL kq .. DPL kq + DPL - 1 of head j
+      double qd[DPL];
+      {
+        const uint4* src = (const uint4*)(qhat + (((size_t)b * n_q + s) * H_idx + j) * DI + DPL * kq);
+#pragma unroll
+        for (int m = 0; m < DPL / 2; ++m) {
+          const uint4 u = src[m];
+          qd[2 * m] = __longlong_as_double(((long long)u.y << 32) | u.x);
+          qd[2 * m + 1] = __longlong_as_double(((long long)u.w << 32) | u.z);
+        }
+      }
+      const double al = alpha[((size_t)b * n_q + s) * H_idx + j];
+      // keep the A operand packed: converted to fp64 ahead of the loop it would take 32 registers
+      // per tile and halve the occupancy; the conversions hide under the matrix cores
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int i = 0; i < WPL; ++i) __asm__ volatile("" : "+v"(ka[t][i]));
+      im_v4d z[TPW];
+#pragma unroll
+      for (int t = 0; t < TPW; ++t) z[t] = im_v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int m = 0; m < DPL; ++m) {
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+          const uint32_t wd = ka[t][m >> 1];
+          const float f = (m & 1) ? bf_hi(wd) : bf_lo(wd);
+          z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)f, qd[m], z[t], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[t][r] = fma(al, fmax(z[t][r], 0.0), acc[t][r]);
+    }
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool vis = sv && posk[t][r] <= qp;     // key row 4 r + kq of tile t, query s
+        imp[t][r] = vis ? fmaxf(imp[t][r], (float)acc[t][r]) : imp[t][r];
+      }
+  }
+  // the 16 query columns' maxima meet in lane 15 of each row, which writes the keys of its register rows
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float v = imp[t][r];
+      v = fmaxf(v, dpp_keep_f<0x111, 0xF>(v));
+      v = fmaxf(v, dpp_keep_f<0x112, 0xF>(v));
+      v = fmaxf(v, dpp_keep_f<0x114, 0xF>(v));
+      v = fmaxf(v, dpp_keep_f<0x118, 0xF>(v));
+      const int key = kbase + 16 * t + 4 * r + kq;
+      if (l16 == 15 && key < n) out[key] = v;
+    }
+  }
+}
+
+// scores[unit][key] = max over the query groups' partial maxima [group][unit][max_live].  grid (ceil(max_live/256), units)
+__global__ __launch_bounds__(256) void k_score_max(const float* __restrict__ part, int groups,
+                                                   const int32_t* __restrict__ len, int C, int max_live,
+                                                   float* __restrict__ scores) {
+  const int unit = blockIdx.y, units = gridDim.y, key = blockIdx.x * 256 + threadIdx.x;
+  if (key >= min(len[unit], max_live)) return;
+  float v = -INFINITY;
+  for (int g = 0; g < groups; ++g) v = fmaxf(v, part[((size_t)g * units + unit) * max_live + key]);
+  scores[(size_t)unit * C + key] = v;
+}
+
 // a1 (iii) for a few queries (a decode step: fewer queries than indexer heads; Section 3.1, Eq. (5)).
 // Here the 16 columns of the 16x16x4 product are the indexer HEADS of one query (H_idx <= 16; absent
 // heads carry a zero gate), so one pass over the DI dims gives a tile of 16 keys its similarities to

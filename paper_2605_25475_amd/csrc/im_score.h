@@ -1,4 +1,4 @@
-// Scores of many queries against a cache (im_index_score with at least as many queries as indexer heads; Section
+// Scores of many queries against a cache (im_index_score with more queries than score_short takes; Section
 // 3.1, Eq. (5)): imp[key] = max over the queries that may see the key of S = sum_j alpha_j ReLU(q_j . k), in fp64.
 //
 // The fp64 value is needed for ONE query per key, the maximal one.  So the scores of all (query, key) pairs are

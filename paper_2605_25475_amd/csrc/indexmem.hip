@@ -268,7 +268,21 @@ void exact_project(im_handle* h, hipStream_t s, const bf16_t* q, const bf16_t* U
   k_exact_fix<<<(N + 63) / 64 * ((M + 63) / 64), 256, 0, s>>>(q, Uq, M, N, K, expA, expB, y, lists);
 }
 
-// the scores of n_q >= H_idx queries from their raw projections in the workspace
+// A short window of queries (n_q >= H_idx) is scored in fp64 against all keys: per key that takes, for 16 queries,
+// H_idx d_idx operations, and up to 512 of them cost less than the bounds and their candidates; over a short cache, whose
+// queries go in groups, more of them do.  Scoring calls, fp64 against bounds, in us:
+//   16 queries x 8 heads of 64 dims: 65536 keys 49 / 73, 524288 keys 188 / 250; 24 queries 70 / 77 and 330 / 271
+//   16 queries x 16 heads of 64, 131072 keys: 144 / 183; 24 queries 196 / 166
+//   64 queries x 8 heads of 16, 512 keys 29 / 35, 8192 keys 31 / 37, 131072 keys 68 / 87
+//   32 queries x 8 heads of 64, 4096 keys 42 / 46, 22400 keys 59 / 58; 64 queries 37 / 42 and 93 / 75
+bool score_few_tiles(const im_handle* h) { return (long long)((h->max_live + 255) / 256) * n_sets_of(&h->cfg) < 128; }
+bool score_short(const im_handle* h, int n_q) {
+  const im_config& c = h->cfg;
+  const long long ops = (long long)((n_q + 15) / 16) * c.n_idx_heads * c.idx_dim, keys = (long long)h->max_live * n_sets_of(&c);
+  return n_q <= 16 || ops <= 512 || (score_few_tiles(h) && n_q <= 128 && ops * keys <= 24000000);
+}
+
+// the scores of longer windows from their raw projections in the workspace
 template <int DI, int HM>
 void score_many(im_handle* h, const im_state* st, const bf16_t* norm_q_w, const int32_t* q_pos, int n_q,
                 double alpha_denom, float* scores, hipStream_t s) {
@@ -547,6 +561,25 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
     return launch_check(h, "im_index_score");
   }
   const bf16_t* nqw = (const bf16_t*)p->norm_q_w;
+  if (score_short(h, n_q)) {
+    const int rows = M * c.n_idx_heads;
+    k_qnorm_alpha<<<(rows + 3) / 4 + (rows + 255) / 256, 256, 0, s>>>(qy, rows, di, nqw, c.rms_eps, al, rows, alpha_denom);
+    // few (256-key tile, unit) workgroups: 16 keys per wave instead of 64, and a group of queries per workgroup
+    const bool small = score_few_tiles(h);
+    const int nblk = (n_q + 15) / 16, per_group = small ? (nblk + IM_SCORE_GROUPS - 1) / IM_SCORE_GROUPS * 16 : n_q;
+    const int groups = (n_q + per_group - 1) / per_group, live = h->max_live;
+    float* out = groups > 1 ? (float*)(h->ws + h->off_recu) : scores_out;   // (a scan's records take 8 times as much)
+#define IM_SCORE(TPW, DI)                                                                                          \
+  k_score<TPW, DI><<<dim3((live + 64 * TPW - 1) / (64 * TPW), units, groups), 256, 0, s>>>(                        \
+      (const bf16_t*)st->Kidx, st->pos, st->len, st->n_projected, qy, al, q_pos, n_q, c.n_kv_heads / heads_per_set(c), \
+      c.capacity, c.n_idx_heads, live, out, groups > 1 ? live : c.capacity, per_group)
+    if (c.head_shared) { if (small) IM_SCORE(1, IM_DI_SHARED); else IM_SCORE(4, IM_DI_SHARED); }
+    else { if (small) IM_SCORE(1, IM_DI); else IM_SCORE(4, IM_DI); }
+#undef IM_SCORE
+    if (groups > 1)
+      k_score_max<<<dim3((live + 255) / 256, units), 256, 0, s>>>(out, groups, st->len, c.capacity, live, scores_out);
+    return launch_check(h, "im_index_score");
+  }
   if (c.head_shared) {
     if (c.n_idx_heads <= 8) score_many<IM_DI_SHARED, 8>(h, st, nqw, q_pos, n_q, alpha_denom, scores_out, s);
     else score_many<IM_DI_SHARED, 16>(h, st, nqw, q_pos, n_q, alpha_denom, scores_out, s);
