@@ -113,11 +113,13 @@ size_t score_rec_keys(size_t sets, size_t capacity) {
 #define IM_EXACT_FEW 32768
 // The query projection of M rows goes through the exact int8 product (im_exact.h) where it has more than 2048 tiles
 // of 16 x 16: below, its 64 x 128 tiles leave most of the chip idle and the fp64 kernel that splits the contraction is
-// faster (512 rows x 512: 32 us against 80).
+// faster (512 rows x 512: 32 us against 80).  Up to 32 columns stay there too: the exact product has 128 of them in any case
+// (scoring calls of 65536 rows x 4096, exact against fp64: 16 columns 793 / 459 us, 32 columns 752 / 618, 48
+// columns 753 / 860).
 size_t exact_np(const im_config* c) { return ((size_t)c->n_idx_heads * c->idx_dim + XG_BN - 1) / XG_BN * XG_BN; }
 bool exact_fits(const im_config* c, long long M) {
   const long long N = c->n_idx_heads * c->idx_dim, K = (long long)c->n_q_heads * IM_D;
-  return K <= XG_MAX_K && M < (1 << 30) && ((M + 15) / 16) * ((N + 15) / 16) > 2048;
+  return N > 32 && K <= XG_MAX_K && M < (1 << 30) && ((M + 15) / 16) * ((N + 15) / 16) > 2048;
 }
 
 size_t n_sets_of(const im_config* c) { return (size_t)c->batch * (c->head_shared ? 1 : c->n_kv_heads); }

@@ -71,3 +71,9 @@ def test_short_windows(shared, H, Hk, batch, n, n_q):
     for mode in ("plain", "equal-queries", "non-finite"):
         if mode != "non-finite" or (n >= 3 and n_q >= 7):
             _check(shared, H, Hk, batch, n, n_q, mode)
+
+
+@pytest.mark.parametrize("H,n_q", [(4, 33000), (8, 16500)])
+def test_many_queries_with_one_or_two_indexer_heads(H, n_q):
+    # (their projection has 16 and 32 columns and more than 2048 tiles)
+    _check(True, H, H, 1, 70, n_q)
