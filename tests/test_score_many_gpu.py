@@ -1,7 +1,8 @@
 """im_index_score with at least as many queries as indexer heads: bounds of all pairs on the fp16 matrix cores, fp64
-for the pairs that can be a key's maximum.  The scores must be the oracle's fp32 numbers bit for bit, at the edges
-of its tiles (16 queries, 64 and 256 keys) and where the bounds decide nothing: equal queries, gates of zero, and
-values outside the range in which bounds are formed."""
+for the pairs that can be a key's maximum (short windows: fp64 for all pairs).  The scores must be the oracle's fp32
+numbers bit for bit, at the edges of the tiles of the form for small caches (16 queries, 64 keys) and where the
+bounds decide nothing: equal queries, gates of zero, and values outside the range in which bounds are formed.
+(Large caches: test_score_shapes_gpu.py.)"""
 import numpy as np
 import pytest
 import torch

@@ -77,3 +77,23 @@ def test_short_windows(shared, H, Hk, batch, n, n_q):
 def test_many_queries_with_one_or_two_indexer_heads(H, n_q):
     # (their projection has 16 and 32 columns and more than 2048 tiles)
     _check(True, H, H, 1, 70, n_q)
+
+
+# Past both thresholds of the form for large caches (from 128 tiles of 256 keys on a wave scans 64 keys instead of 16; above 32768
+# keys it evaluates 16 instead of 4), one key around whole tiles.  Per unit 32 units of 1023 .. keys, head-shared 16
+# sequences of 2047 .. keys: 32736 to 36000 keys.
+LARGE = [(shared, H, n, n_q) for shared, ns in ((False, (1023, 1024, 1025, 1100)), (True, (2047, 2048, 2049, 2200)))
+         for H in (32, 64) for n in ns for n_q in ((33,) if not shared else (81 if H == 32 else 49,))]
+
+
+@pytest.mark.parametrize("shared,H,n,n_q", LARGE, ids=["-".join(map(str, c)) for c in LARGE])
+def test_many_queries_over_large_caches(shared, H, n, n_q):
+    for mode in ("plain", "equal-queries", "non-finite"):
+        _check(shared, H, 8, 16 if shared else 4, n, n_q, mode)
+
+
+@pytest.mark.parametrize("shared,H,n,n_q", [(False, 32, 1025, 140), (False, 64, 1100, 260), (True, 32, 2049, 300), (True, 64, 2200, 150)])
+def test_query_groups_over_large_caches(shared, H, n, n_q):
+    # more blocks of 16 queries than groups: records name one block of several
+    for mode in ("plain", "equal-queries", "non-finite"):
+        _check(shared, H, 8, 16 if shared else 4, n, n_q, mode)
