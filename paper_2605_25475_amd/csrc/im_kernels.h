@@ -461,12 +461,12 @@ __device__ __forceinline__ void gemm_nt_tile_split(const bf16_t* __restrict__ A,
   }
 }
 
-// grid (ceil(N / 16), ceil(M / 16))
+// grid (ceil(M / 16), ceil(N / 16)): the rows, of which a prompt has a million and more, in x
 template <int W>
 __global__ __launch_bounds__(64 * W) void k_gemm_nt_mfma_split(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                                double* __restrict__ Cm, int M, int N, int Kd) {
   __shared__ double red[W - 1][64][4];
-  gemm_nt_tile_split<W>(A, B, Cm, M, N, Kd, blockIdx.x, blockIdx.y, red);
+  gemm_nt_tile_split<W>(A, B, Cm, M, N, Kd, blockIdx.y, blockIdx.x, red);
 }
 
 // Both query-side products of up to a few hundred queries in one launch: y = q U_q^T and alpha = x G^T (N2 <= 16).  The

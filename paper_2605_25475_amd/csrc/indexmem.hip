@@ -244,9 +244,9 @@ void gemm_nt(hipStream_t s, const bf16_t* A, const bf16_t* B, double* Cm, int M,
     k_gemm_nt_f64<<<dim3((N + 63) / 64, (M + 63) / 64), 256, 0, s>>>(A, B, Cm, M, N, Kd);
   } else if (Kd % 512 == 0 && gemm_tiles(M, N) <= 512) {
     // (the gates of 4096 queries: 20 us with 4 waves a tile, 15 with 16; of 32768: 95 with 4 or 8)
-    k_gemm_nt_mfma_split<16><<<dim3((N + 15) / 16, (M + 15) / 16), 1024, 0, s>>>(A, B, Cm, M, N, Kd);
+    k_gemm_nt_mfma_split<16><<<dim3((M + 15) / 16, (N + 15) / 16), 1024, 0, s>>>(A, B, Cm, M, N, Kd);
   } else if (Kd % 128 == 0 && (N <= 16 || gemm_tiles(M, N) <= 2048)) {
-    k_gemm_nt_mfma_split<4><<<dim3((N + 15) / 16, (M + 15) / 16), 256, 0, s>>>(A, B, Cm, M, N, Kd);
+    k_gemm_nt_mfma_split<4><<<dim3((M + 15) / 16, (N + 15) / 16), 256, 0, s>>>(A, B, Cm, M, N, Kd);
   } else if ((long long)M * N <= (1ll << 21) || N <= 16) {
     k_gemm_nt_mfma<1, 1><<<dim3((N + 31) / 32, (M + 31) / 32), 256, 0, s>>>(A, B, Cm, M, N, Kd);
   } else {
