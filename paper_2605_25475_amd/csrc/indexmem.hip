@@ -26,9 +26,8 @@ struct im_handle {
   // workspace layout (byte offsets)
   size_t off_status, off_qy, off_alpha, off_mem, off_attn, off_dpart, off_dcand, off_dqm, off_xk, off_hspart, total;
   size_t off_xexp, off_xcount, off_xplanes, off_xlist;              // exact products
-  size_t off_qf, off_al16, off_qblk, off_recu, off_reci, off_nlist, off_list;   // scores of many queries
+  size_t off_spart, off_qf, off_al16, off_qblk, off_recu, off_reci, off_nlist, off_list;   // scores of several queries
   int attn_chunks, dec_splits;
-  size_t rec_keys;   // (group, key) records of a scan that the workspace holds
   // optional kernel timing (im_profile_start / im_profile_stop)
   hipEvent_t* prof_ev;
   int prof_max, prof_n, prof_span;
@@ -136,51 +135,65 @@ int splits_of(long long live, long long rows, long long wgs, long long sets) {
 int mem_splits(const im_config* c, long long live) {
   return c->head_shared ? splits_of(live, 32, 1024, n_sets_of(c)) : splits_of(live, 64, 512, n_sets_of(c));
 }
+// most 16-query blocks' worth of a call's window (score_short): a longer one may go through the bounds
+bool score_may_scan(const im_config* c) {
+  return c->max_queries > 16 && (long long)((c->max_queries + 15) / 16) * c->n_idx_heads * c->idx_dim > 512;
+}
+
+// The status words stay from call to call.  Everything else is written and read inside one call, and calls on one handle
+// do not overlap: what grows with the queries comes first, and behind it scoring, memory write, attention and the
+// fused steps use the same memory, one after another.
 void layout(const im_config* c, im_handle* h) {
-  const size_t B = c->batch, Hi = c->n_idx_heads, units = (size_t)c->batch * c->n_kv_heads;
-  h->attn_chunks = (c->capacity + IM_ATT_CHUNK - 1) / IM_ATT_CHUNK;
-  size_t off = 0;
+  const size_t B = c->batch, Hi = c->n_idx_heads, units = (size_t)c->batch * c->n_kv_heads, sets = n_sets_of(c);
+  auto take = [](size_t& off, size_t bytes) {
+    const size_t at = off;
+    off = align256(off + bytes);
+    return at;
+  };
+  size_t base = 0;
   // status word (in a 32-word slot of its own), then one newest-position word per unit
-  h->off_status = off; off = align256(off + (32 + units) * sizeof(int32_t));
-  h->dec_splits = (c->capacity + DEC_KEYS - 1) / DEC_KEYS + 1;   // + the last-slot record
-  h->off_qy = off;     off = align256(off + B * c->max_queries * Hi * IM_DI * sizeof(double));
-  h->off_alpha = off;  off = align256(off + B * c->max_queries * Hi * sizeof(double));
-  h->off_mem = off;    off = align256(off + n_sets_of(c) * mem_splits(c, c->capacity) * (IM_DM * IM_D + IM_DM) * sizeof(float));
-  h->off_attn = off;   off = align256(off + B * c->n_q_heads * h->attn_chunks * IM_ATT_REC * sizeof(float));
-  h->off_dpart = off;  off = align256(off + units * h->dec_splits * DEC_GMAX * DEC_REC * sizeof(float));  // upper bound: G <= 8
-  h->off_dcand = off;  off = align256(off + units * h->dec_splits * DEC_CAND * sizeof(uint32_t));
-  h->off_dqm = off;    off = align256(off + units * DEC_GMAX * DEC_QM * sizeof(float));
-  // scores of many queries: normalised features, gates, operand blocks of 16 queries, the scan's records, listed keys
-  const size_t rows = B * c->max_queries, sets = c->head_shared ? B : units, qblk = (c->max_queries + 15) / 16;
-  h->off_qf = off;     off = align256(off + rows * Hi * c->idx_dim * sizeof(float));
-  h->off_al16 = off;   off = align256(off + rows * 16 * sizeof(float));
-  h->off_qblk = off;   off = align256(off + B * qblk * score_block_bytes(c));
-  h->rec_keys = score_rec_keys(sets, c->capacity);
-  h->off_recu = off;   off = align256(off + h->rec_keys * 4 * sizeof(float2));
-  h->off_reci = off;   off = align256(off + h->rec_keys * 4 * sizeof(int32_t));
-  h->off_nlist = off;  off = align256(off + B * sizeof(int32_t));
-  h->off_list = off;   off = align256(off + sets * c->capacity * sizeof(int2));
-  // exact products: the largest one is the query projection
+  h->off_status = take(base, (32 + units) * sizeof(int32_t));
+  // raw query projections and gates (of the fused steps, too)
+  const size_t rows = B * c->max_queries, qblk = (c->max_queries + 15) / 16;
+  h->off_qy = take(base, rows * Hi * c->idx_dim * sizeof(double));
+  h->off_alpha = take(base, rows * Hi * sizeof(double));
+  // the query projection as an exact product
   const size_t np = exact_np(c), xk = (size_t)c->n_q_heads * IM_D;
   const bool exact = exact_fits(c, (long long)c->batch * c->max_queries);
   const size_t xrows = exact ? rows + np : 0;
-  h->off_xexp = off;   off = align256(off + xrows * sizeof(int32_t));
-  h->off_xcount = off; off = align256(off + xrows * sizeof(int32_t));
-  h->off_xlist = off;  off = align256(off + xrows * XG_ROOM * sizeof(uint16_t));
-  h->off_xplanes = off; off = align256(off + (exact ? np * xk * 4 : 0));
-  // head_shared: U_k X of the rows of one append, fp64
-  const size_t common = off;
-  h->off_xk = off;     off = align256(off + (c->head_shared ? B * c->capacity * IM_DI_SHARED * sizeof(double) : 0));
-  h->off_hspart = off; off = align256(off + (c->head_shared ? B * HS_NSC * sizeof(uint4) : 0));
-  h->total = off;
-  if (c->head_shared) {   // (a head-shared workspace is at least what the per-unit layout of the shape takes, and its own part)
-    im_config u = *c;
-    u.head_shared = 0;
-    u.idx_dim = IM_DI;
-    im_handle t;
-    layout(&u, &t);
-    if (common < t.total) h->total += t.total - common;
-  }
+  h->off_xexp = take(base, xrows * sizeof(int32_t));
+  h->off_xcount = take(base, xrows * sizeof(int32_t));
+  h->off_xlist = take(base, xrows * XG_ROOM * sizeof(uint16_t));
+  h->off_xplanes = take(base, exact ? np * xk * 4 : 0);
+  // scores by bounds: normalised features, gates, operand blocks of 16 queries, counts of listed keys
+  const bool scan = score_may_scan(c);
+  h->off_qf = take(base, scan ? rows * Hi * c->idx_dim * sizeof(float) : 0);
+  h->off_al16 = take(base, scan ? rows * 16 * sizeof(float) : 0);
+  h->off_qblk = take(base, scan ? B * qblk * score_block_bytes(c) : 0);
+  h->off_nlist = take(base, scan ? B * sizeof(int32_t) : 0);
+  size_t score = base, mem = base, attn = base, step = base;
+  // ... the scan's records, listed keys
+  const size_t rec_keys = scan ? score_rec_keys(sets, c->capacity) : 0;
+  h->off_recu = take(score, rec_keys * 4 * sizeof(float2));
+  h->off_reci = take(score, rec_keys * 4 * sizeof(int32_t));
+  h->off_list = take(score, scan ? sets * c->capacity * sizeof(int2) : 0);
+  // short windows: the query groups' maxima over a short cache (score_few_tiles: fewer than 128 tiles of 256 keys)
+  const size_t few_keys = sets * c->capacity < 128 * 256 ? sets * c->capacity : 128 * 256;
+  h->off_spart = take(score, c->max_queries > 16 ? IM_SCORE_GROUPS * few_keys * sizeof(float) : 0);
+  // memory write: partial sums (at most 34 MB, 68 MB with sets of several heads)
+  h->off_mem = take(mem, sets * mem_splits(c, c->capacity) * (IM_DM * IM_D + IM_DM) * sizeof(float));
+  // attention
+  h->attn_chunks = (c->capacity + IM_ATT_CHUNK - 1) / IM_ATT_CHUNK;
+  h->off_attn = take(attn, B * c->n_q_heads * h->attn_chunks * IM_ATT_REC * sizeof(float));
+  // the fused steps; head_shared: U_k X of the rows of one append or step, fp64
+  h->dec_splits = (c->capacity + DEC_KEYS - 1) / DEC_KEYS + 1;   // + the last-slot record
+  h->off_dpart = take(step, units * h->dec_splits * DEC_GMAX * DEC_REC * sizeof(float));  // upper bound: G <= 8
+  h->off_dcand = take(step, units * h->dec_splits * DEC_CAND * sizeof(uint32_t));
+  h->off_dqm = take(step, units * DEC_GMAX * DEC_QM * sizeof(float));
+  h->off_xk = take(step, c->head_shared ? B * c->capacity * IM_DI_SHARED * sizeof(double) : 0);
+  h->off_hspart = take(step, c->head_shared ? B * HS_NSC * sizeof(uint4) : 0);
+  h->total = score;
+  for (size_t end : {mem, attn, step}) h->total = end > h->total ? end : h->total;
 }
 
 int launch_check(im_handle* h, const char* what) {
@@ -570,7 +583,7 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
     const bool small = score_few_tiles(h);
     const int nblk = (n_q + 15) / 16, per_group = small ? (nblk + IM_SCORE_GROUPS - 1) / IM_SCORE_GROUPS * 16 : n_q;
     const int groups = (n_q + per_group - 1) / per_group, live = h->max_live;
-    float* out = groups > 1 ? (float*)(h->ws + h->off_recu) : scores_out;   // (a scan's records take 8 times as much)
+    float* out = groups > 1 ? (float*)(h->ws + h->off_spart) : scores_out;
 #define IM_SCORE(TPW, DI)                                                                                          \
   k_score<TPW, DI><<<dim3((live + 64 * TPW - 1) / (64 * TPW), units, groups), 256, 0, s>>>(                        \
       (const bf16_t*)st->Kidx, st->pos, st->len, st->n_projected, qy, al, q_pos, n_q, c.n_kv_heads / heads_per_set(c), \

@@ -125,7 +125,11 @@ def test_calls_validate_before_enqueuing(lib):
 
 def test_head_shared_layout_validation(lib):
     ok = good_cfg(head_shared=1, idx_dim=16)
-    assert lib.im_workspace_bytes(C.byref(ok.c_struct())) > lib.im_workspace_bytes(C.byref(good_cfg().c_struct()))
+    n = lib.im_workspace_bytes(C.byref(ok.c_struct()))
+    h = C.c_void_p()
+    assert lib.im_create(C.byref(ok.c_struct()), 1 << 20, n - 1, C.byref(h)) == im.IM_ERR_INVALID_ARG
+    for more in (dict(capacity=4096), dict(batch=4), dict(max_queries=4096)):
+        assert lib.im_workspace_bytes(C.byref(good_cfg(head_shared=1, idx_dim=16, **more).c_struct())) > n, more
     h = C.c_void_p()
     assert lib.im_create(C.byref(good_cfg(head_shared=2, idx_dim=16).c_struct()), 1 << 20, 1 << 40, C.byref(h)) == im.IM_ERR_INVALID_ARG
     assert lib.im_create(C.byref(good_cfg(head_shared=1).c_struct()), 1 << 20, 1 << 40, C.byref(h)) == im.IM_ERR_UNSUPPORTED   # idx_dim 64
@@ -145,6 +149,21 @@ def test_head_shared_layout_validation(lib):
     assert lib.im_append_kv_hidden(h, C.byref(pr), C.byref(st), X, X, X, X, 0, None) == im.IM_ERR_INVALID_ARG
     assert b"head_shared" in lib.im_last_error(h) or b"n_new" in lib.im_last_error(h)
     lib.im_destroy(h)
+
+
+def test_workspace_holds_what_the_calls_of_a_shape_can_use(lib):
+    mb = lambda **kw: lib.im_workspace_bytes(C.byref(good_cfg(**kw).c_struct())) / 1e6
+    shared = dict(head_shared=1, idx_dim=16)
+    # one query per call never takes the records of a scan: what is left are the memory write's partial sums, at most 512 (in
+    # sets of several heads 1024) of 66 KB and one more per set
+    assert mb(batch=4, capacity=2049, max_queries=1) < (512 + 32) * 0.0661 + 0.2
+    assert mb(batch=4, capacity=2049, max_queries=1, **shared) < (1024 + 4) * 0.0661 + 0.2
+    # a prompt: raw and normalised features (12 bytes per value), 36 KB of operands per 16 queries and 48 bytes per record
+    # fill it; a quarter of the feature values in the head-shared layout, and records per sequence
+    prompt = dict(batch=4, capacity=16384, max_queries=16384)
+    feats, keys = 65536 * 8 * 64 * 12, 32 * 16384
+    assert mb(**prompt) < (1.1 * feats + 36864 * 4096 / 2 + 48 * (keys + 2048 * 256) + 8 * keys + 4 * 512 * 4096 + 544 * 66100) / 1e6
+    assert mb(**prompt, **shared) < 0.7 * mb(**prompt)
 
 
 def test_binding_fails_loudly_on_invalid_config():
