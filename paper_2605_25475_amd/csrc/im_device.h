@@ -228,10 +228,13 @@ __device__ __forceinline__ uint4 load_stream16(const void* p) {
 // 1 KB from global memory straight into LDS: 16 bytes per lane, from src (this lane's address) to dst + 16 * lane (dst
 // uniform per wave).  Written as assembly on purpose: behind the compiler's own form of this instruction every LDS
 // read waits for all copies in flight (it cannot tell the buffers apart), so nothing is fetched ahead.
-// (M0 holds the LDS address; the compiler keeps nothing in it.)  The caller waits: copy_wait<N>() leaves the N youngest vector memory operations of the wave outstanding.
+// M0 holds the LDS address, and gets back what it held: it is a reserved register, which a clobber list cannot name.
+// The caller waits: copy_wait<N>() leaves the N youngest vector memory operations of the wave outstanding.
 __device__ __forceinline__ void copy_to_lds_1k(const char* src, char* dst) {
   const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)dst);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(src) : "memory");
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0) : "s"(at), "v"(src) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void copy_wait() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory"); }
