@@ -71,8 +71,9 @@ typedef struct im_config {
   int32_t gate_in_dim;  /* width of the gate input X_s (multiple of 16)                       */
   int32_t n_sink;       /* first token positions always kept (4 in the paper, Section 4)      */
   int32_t n_recent;     /* newest positions always kept (0: none)                             */
-  int32_t fold_block;   /* evicted rows are folded into the memory in blocks of this (64;
-                           a multiple of 32)                                                   */
+  int32_t fold_block;   /* evicted rows are folded into the memory in blocks of this (64; a multiple
+                           of 32): a partial sum covers whole blocks.  head_shared = 1: whole
+                           tiles of 32 tokens (of every head), whatever it says                 */
   int32_t max_queries;  /* largest n_q a call to im_index_score will pass                     */
   int32_t head_shared;  /* 0: state per (batch, KV head); 1: one set per sequence (see above);
                            then gate_in_dim is also d_model, the width of the hidden states     */

@@ -469,8 +469,8 @@ __global__ __launch_bounds__(64 * W) void k_gemm_nt_mfma_split(const bf16_t* __r
   gemm_nt_tile_split<W>(A, B, Cm, M, N, Kd, blockIdx.y, blockIdx.x, red);
 }
 
-// Both query-side products of up to a few hundred queries in one launch: y = q U_q^T and alpha = x G^T (N2 <= 16).  The
-// gate's ceil(M / 16) tiles come first: a chain of loads of 10 to 20 us each, that hides behind the projection's.
+// Both query-side products of up to 2048 tiles of y (1024 rows of 512 columns, 4096 of 128) in one launch: y = q U_q^T and
+// alpha = x G^T (N2 <= 16).  The gate's ceil(M / 16) tiles come first: a chain of loads of 10 to 20 us each, that hides behind the projection's.
 __global__ __launch_bounds__(256) void k_query_side(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Uq,
                                                     double* __restrict__ y, int M, int N1, int K1,
                                                     const bf16_t* __restrict__ x, const bf16_t* __restrict__ G,

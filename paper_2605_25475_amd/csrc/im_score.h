@@ -37,7 +37,6 @@ struct ScoreBlock {
   static constexpr int T = HM, ERR = HM + 1, POS = HM + 2, ROWS = HM + 3;
   static constexpr int BYTES = (OFF + ROWS * 64 + 1023) / 1024 * 1024;   // whole 1 KB wave copies
 };
-#define IM_SCORE_BLOCK_MAX (ScoreBlock<64, 16>::BYTES)
 
 // power of two that brings a norm into [2^11, 2^12); 1 for a zero or non-finite one
 __device__ __forceinline__ float score_scale(float norm) {
