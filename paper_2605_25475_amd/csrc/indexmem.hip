@@ -106,9 +106,9 @@ size_t score_rec_keys(size_t sets, size_t capacity) {
   return all < few ? all : few;
 }
 
-// Up to this many keys a wave of k_score_exact takes 4 instead of 16, which it evaluates in turn: 12000 keys 27 -> 17 us,
-// 32768 of the head-shared layout 28 -> 28, 65536 keys 54 -> 58 (before the heads' sums were taken together; with
-// that 13, 22 and 39 us).
+// Up to this many keys a wave of k_score_exact takes 4 instead of 16, which it evaluates in turn.  Scoring calls of 2000 queries, 4
+// keys a wave against 16, in us: 12000 keys 190 / 200, 24000 keys 207 / 213, 32768 keys 220 / 224 (head-shared 252 /
+// 247), 48000 keys 267 / 262, 65536 keys 298 / 290.
 #define IM_EXACT_FEW 32768
 // The query projection of M rows goes through the exact int8 product (im_exact.h) where it has more than 2048 tiles
 // of 16 x 16: below, its 64 x 128 tiles leave most of the chip idle and the fp64 kernel that splits the contraction is
