@@ -851,159 +851,8 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
     // Five groups of 4 loads per lane (K tile 0, K tile 1, Q, V tile 0, V tile 1), paced: a group goes out
     // when all but the last 4 loads before it have arrived, so a lane has at most 8 in flight.  With every
     // workgroup of the launch resident at once, issuing all 20 at the start oversubscribes the memory queues where a
-    // launch has many splits: with the waits and without, 4 tokens x 8 layers of 16 x 512 entries 829 and 837 us, of 8 x 1024
-    // with index reuse 661 and 676; of 4 x 2048 and 1 x 4096 the same; one layer of 1 x 256 19.1 and 18.7.
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      const int kr = min(16 * (2 * wl + tt) + l16, nk - 1);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        kif[tt][i] = load_stream16(a.Kidx + (base + kr) * IM_DI + 16 * kq + 8 * i);
-    }
-    const int kk = 32 * wl + (lane & 31);       // the key this lane ranks (both half-waves hold it)
-    mypos = a.pos[base + min(kk, nk - 1)];
-    const int qpos = a.q_pos[b];
-    const int mxp = (a.n_recent > 0) ? a.maxpos[u] : 0;
-    // split 0 also looks after the one key beyond the splits, when there is one
-    const bool do_x = do_x_any;
-    // (its attention logits: wave wl takes dims 32 wl .. 32 wl + 31, lane (head l16, kq) 8 of them)
-    uint4 xk = make_uint4(0, 0, 0, 0), xq = xk, xkv = xk, xki0 = xk, xki1 = xk;
-    int xpos = 0;
-    if (do_x) {
-      const size_t last = (size_t)u * a.C + (n - 1);
-      xki0 = *(const uint4*)(a.Kidx + last * IM_DI + 16 * kq);
-      xki1 = *(const uint4*)(a.Kidx + last * IM_DI + 16 * kq + 8);
-      xk = *(const uint4*)(a.K + last * IM_D + 32 * wl + 8 * kq);
-      xq = *(const uint4*)(a.q + ((size_t)b * a.H + h * G + min(l16, G - 1)) * IM_D + 32 * wl + 8 * kq);
-      // rows for the record: lanes 0-15 the K row, lanes 16-31 the V row (8 elements each)
-      xkv = *(const uint4*)(((lane & 16) ? a.V : a.K) + last * IM_D + 8 * l16);
-      xpos = a.pos[last];
-    }
-    __asm__ volatile("" ::: "memory");   // every load above is issued before the arithmetic below
-    // ---- QK-Norm of the query features (per head over its 64 dims), head gate
-    double alj;
-    {
-      double ss = 0.0;
-#pragma unroll
-      for (int m = 0; m < 16; ++m) ss = fma(qd[m], qd[m], ss);
-      ss = rows_sum_d(ss);
-      const double rr = sqrt(ss / (double)IM_DI + (double)a.rms_eps);
-      const double inv = 1.0 / rr;
-      float wf[16];
-      unpack8(nw[0], wf);
-      unpack8(nw[1], wf + 8);
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        // y / rr, correctly rounded, without 16 division sequences per lane: inv is the correctly
-        // rounded reciprocal; the first residual step leaves a quotient within one ulp, and a residual
-        // step on such a quotient yields the correctly rounded one (Markstein's theorem on
-        // FMA-based division).  The step-by-step path and the oracle divide; all three then round the
-        // same fp64 value to fp32.
-        double qq = qd[m] * inv;
-        qq = fma(fma(-qq, rr, qd[m]), inv, qq);
-        qq = fma(fma(-qq, rr, qd[m]), inv, qq);
-        // (lanes past the last indexer head hold head 0's values: finite, and never used: their columns of
-        // the similarity product are not stored and their gate is zero)
-        qd[m] = (double)(float)(qq * (double)wf[m]);
-      }
-      alj = hv ? (double)(float)(araw / sqrt((double)(a.H_idx * IM_DI))) : 0.0;
-    }
-    if (do_x) {   // uniform per workgroup; every scoring wave computes, the first writes
-      float fx[16];
-      unpack8(xki0, fx);
-      unpack8(xki1, fx + 8);
-      double zp = 0.0;
-#pragma unroll
-      for (int m = 0; m < 16; ++m) zp = fma(qd[m], (double)fx[m], zp);
-      zp = rows_sum_d(zp);                                   // q_j . k over the 64 dims, in all 4 rows
-      const double asum = wave_sum_d((kq == 0) ? alj * fmax(zp, 0.0) : 0.0);
-      float lp = 0.f;
-      {
-        float qv[8], kv[8];
-        unpack8(xq, qv);
-        unpack8(xk, kv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) lp = fmaf(qv[e], kv[e], lp);
-      }
-      lp = rows_sum_f(lp);
-      if (kq == 0 && l16 < 8) sm.xlp[wl][l16] = lp;   // summed over the 4 waves after the barrier
-      if (wl == 0) {
-        if (l16 == 0) {
-          *(uint4*)(lrec + DEC_CAND_KI + 8 * kq) = xki0;
-          *(uint4*)(lrec + DEC_CAND_KI + 8 * kq + 4) = xki1;
-        }
-        if (lane < 32) *(uint4*)(lrec + ((lane & 16) ? DEC_CAND_V : DEC_CAND_K) + 4 * l16) = xkv;
-        if (lane == 0) {
-          const float sc = (xpos <= qpos) ? (float)asum : -INFINITY;
-          if (a.scores) a.scores[(size_t)u * a.C + (n - 1)] = sc;
-          const bool forced = (xpos < a.n_sink) || (a.n_recent > 0 && (long long)xpos > (long long)mxp - a.n_recent);
-          const uint32_t skey = forced ? IM_KEY_PINF : score_key(sc);
-          lrec[0] = skey;
-          lrec[1] = (uint32_t)(~((uint32_t)xpos ^ 0x80000000u));
-          lrec[2] = (uint32_t)(n - 1);
-          lrec[3] = (uint32_t)n;
-          lrec[12] = (uint32_t)xpos;
-        }
-      }
-    }
-    // ---- gated similarities of the 2 tiles of this wave: Z[key][head] = Kidx_tile . q^T (fp64 MFMA)
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      float f[16];
-      unpack8(kif[tt][0], f);
-      unpack8(kif[tt][1], f + 8);
-      v4d z = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int m = 0; m < 16; ++m) z = __builtin_amdgcn_mfma_f64_16x16x4f64((double)f[m], qd[m], z, 0, 0, 0);
-      const int T = 2 * wl + tt;
-      if (hv) {
-#pragma unroll
-        // fp64 16x16x4 result layout: register r of lane (l16, kq) is row 4 r + kq, column l16
-        for (int r = 0; r < 4; ++r) sm.zs[16 * T + 4 * r + kq][l16] = alj * fmax(z[r], 0.0);
-      }
-    }
-    if (own_last) {   // the last live slot's indexer key and position go to the last-slot record
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-        if (16 * (2 * wl + tt) + l16 == ll) {
-          *(uint4*)(lrec + DEC_CAND_KI + 8 * kq) = kif[tt][0];
-          *(uint4*)(lrec + DEC_CAND_KI + 8 * kq + 4) = kif[tt][1];
-        }
-      }
-      if (lane < 32 && kk == ll) { lrec[2] = (uint32_t)(n - 1); lrec[3] = (uint32_t)n; lrec[12] = (uint32_t)mypos; }
-    }
-    // the rows just written belong to this wave's own keys: it reads them back without a
-    // workgroup barrier (LDS operations of one wave complete in order)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // ---- score, forced flag, and the wave's last-ranked entry: smallest rank key; on equal
-    // (score, position) the largest slot
-    const bool valid = lane < 32 && kk < nk;
-    uint32_t khi = 0xffffffffu, klo = 0xffffffffu;
-    if (valid) {
-      double asum = 0.0;
-      for (int j = 0; j < a.H_idx; ++j) asum += sm.zs[kk][j];
-      const float sc = (mypos <= qpos) ? (float)asum : -INFINITY;
-      if (a.scores) a.scores[base + kk] = sc;
-      const bool forced = (mypos < a.n_sink) || (a.n_recent > 0 && (long long)mypos > (long long)mxp - a.n_recent);
-      khi = forced ? IM_KEY_PINF : score_key(sc);
-      klo = (uint32_t)(~((uint32_t)mypos ^ 0x80000000u));
-    }
-    const uint32_t mh = wave_min_u(khi);
-    const uint32_t ml = wave_min_u(khi == mh ? klo : 0xffffffffu);
-    const int win = (int)wave_max_u((valid && khi == mh && klo == ml) ? (uint32_t)(lane + 1) : 0u) - 1;
-    if (lane == 0) {
-      sm.c64[wl] = ((unsigned long long)mh << 32) | ml;
-      sm.cslot[wl] = (win >= 0) ? 32 * wl + win : -1;
-    }
-  } else {
-    // ================= attention waves: issue the K, Q and V loads =================
-    // Five groups of 4 loads per lane (K tile 0, K tile 1, Q, V tile 0, V tile 1), paced: a group goes out
-    // when all but the last 4 loads before it have arrived, so a lane has at most 8 in flight.  With every
-    // workgroup of the launch resident at once, issuing all 20 at the start oversubscribes the memory queues.
-    // (With P V on the matrix cores the order hardly matters any more: 13.2 us per launch at 32 units x 2048 entries with
-    // all waits or none, 11.7 without scoring waves.)
+    // launch has many splits: with the waits and without, 4 tokens x 8 layers of 16 x 512 entries 829 and 837 us, of
+    // 8 x 1024 with index reuse 661 and 676; of 4 x 2048 and 1 x 4096 the same; one layer of 1 x 256 19.1 and 18.7.
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
       const int kr = min(16 * (2 * wl + tt) + l16, nk - 1);
