@@ -383,10 +383,10 @@ __global__ __launch_bounds__(256, HM == 8 ? 4 : 2) void k_score_scan(const bf16_
 // grid (ceil(max_live / (4 KPW)), units), 4 waves of KPW keys each (16, or 4).  A candidate is a record's block: its 4 queries are
 // evaluated in fp64 by the whole wave (lane (query r = lane / 16, p): dims 4 p .. of every head).  Bound by the vector
 // ALU: half of it conversions and products, half the sums over 16 lanes, which is why the heads' sums are taken together.  A
-// second candidate block inside one record is not known by name: the key goes to the list.  So do all keys of a wave that has
-// more than IM_EXACT_NAMED candidates per key (queries that are equal, or gates of zero): the list takes whole blocks
-// through the fp64 matrix cores (64 equal queries x 65536 keys x 8 heads, the call: 449 us without this, 2 candidates 219, 4 240,
-// 8 285; 4 x 16384 tokens of the benchmark's kind: 6486, 6574, 6530 and 6509).
+// second candidate block inside one record is not known by name: the key goes to the list.  So do all keys of a wave whose
+// candidates number more than IM_EXACT_NAMED per key (queries that are equal, or gates of zero): the list takes whole blocks
+// through the fp64 matrix cores, from the best of what was evaluated.  64 equal queries x 65536 keys x 8 heads, the call: 449 us
+// without this, with 2, 3 and 4 candidates 253, 261 and 281; with gates of zero 429, 180, 164 and 182.
 #define IM_EXACT_NAMED 4
 template <int DI, int HM>
 __device__ __forceinline__ float score_exact4(const float* __restrict__ qrow, const float* __restrict__ al, int H_idx,
@@ -489,20 +489,14 @@ __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ 
   const float low = (top == INFINITY) ? -INFINITY : top - 2.001f * err - 0x1p-18f * fabsf(top);
   float best = -INFINITY;
   bool more = false;
-  int named = 0;
+  int room = IM_EXACT_NAMED * KPW;   // (uniform)
 #pragma unroll
   for (int g = 0; g < IM_SCORE_GROUPS; ++g) {
     if (g >= groups) break;
     more = more || (u2[g] >= low && u2[g] > -INFINITY);
-    named += __popcll(__ballot(mine && u1[g] >= low && u1[g] > -INFINITY));
-  }
-  const bool all = named > IM_EXACT_NAMED * KPW;
-  more = more || (all && lmax > -INFINITY);
-#pragma unroll
-  for (int g = 0; g < IM_SCORE_GROUPS; ++g) {
-    if (g >= groups || all) break;
     unsigned long long cand = __ballot(mine && u1[g] >= low && u1[g] > -INFINITY);
     while (cand) {
+      if (--room < 0) break;
       const int ln = __builtin_ctzll(cand);
       cand &= cand - 1;
       const int blk = __builtin_amdgcn_readlane(i1[g], ln), kk = ln & 15;
@@ -517,7 +511,7 @@ __global__ __launch_bounds__(256) void k_score_exact(const bf16_t* __restrict__ 
       if (l16 == kk) best = fmaxf(best, m);
     }
   }
-  more = rows_max_f(more ? 1.f : 0.f) > 0.f && mine;
+  more = rows_max_f(more || (room < 0 && lmax > -INFINITY) ? 1.f : 0.f) > 0.f && mine;
   if (kq == 0 && mine) scores[(size_t)unit * C + key] = best;
   const unsigned long long lst = __ballot(more && kq == 0);
   if (lst) {
