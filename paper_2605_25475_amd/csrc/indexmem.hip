@@ -135,7 +135,7 @@ int splits_of(long long live, long long rows, long long wgs, long long sets) {
 int mem_splits(const im_config* c, long long live) {
   return c->head_shared ? splits_of(live, 32, 1024, n_sets_of(c)) : splits_of(live, 64, 512, n_sets_of(c));
 }
-// most 16-query blocks' worth of a call's window (score_short): a longer one may go through the bounds
+// whether a call may go through the bounds: shorter windows never do (score_short)
 bool score_may_scan(const im_config* c) {
   return c->max_queries > 16 && (long long)((c->max_queries + 15) / 16) * c->n_idx_heads * c->idx_dim > 512;
 }
@@ -294,6 +294,7 @@ bool score_few_tiles(const im_handle* h) { return (long long)((h->max_live + 255
 bool score_short(const im_handle* h, int n_q) {
   const im_config& c = h->cfg;
   const long long ops = (long long)((n_q + 15) / 16) * c.n_idx_heads * c.idx_dim, keys = (long long)h->max_live * n_sets_of(&c);
+  if (!score_may_scan(&c)) return true;   // (the workspace holds nothing for the bounds)
   return n_q <= 16 || ops <= 512 || (score_few_tiles(h) && n_q <= 128 && ops * keys <= 24000000);
 }
 
