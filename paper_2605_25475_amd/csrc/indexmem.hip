@@ -101,6 +101,7 @@ size_t score_block_bytes(const im_config* c) {
 // workgroups a scan aims at: with query groups it has at most this many (rounded up by one group), and a
 // workgroup covers at most 256 keys, which bounds its records
 #define IM_SCORE_WGS 2048
+#define IM_SCORE_GROUP_TILES 512   // fewer tiles of 256 keys: a short window's queries go in groups
 size_t score_rec_keys(size_t sets, size_t capacity) {
   const size_t all = IM_SCORE_GROUPS * sets * capacity, few = (size_t)IM_SCORE_WGS * 256 + sets * capacity;
   return all < few ? all : few;
@@ -177,8 +178,8 @@ void layout(const im_config* c, im_handle* h) {
   h->off_recu = take(score, rec_keys * 4 * sizeof(float2));
   h->off_reci = take(score, rec_keys * 4 * sizeof(int32_t));
   h->off_list = take(score, scan ? sets * c->capacity * sizeof(int2) : 0);
-  // short windows: the query groups' maxima over a short cache (score_few_tiles: fewer than 128 tiles of 256 keys)
-  const size_t few_keys = sets * c->capacity < 128 * 256 ? sets * c->capacity : 128 * 256;
+  // short windows: the query groups' maxima over a short cache (fewer than IM_SCORE_GROUP_TILES tiles of 256 keys)
+  const size_t most = (size_t)IM_SCORE_GROUP_TILES * 256, few_keys = sets * c->capacity < most ? sets * c->capacity : most;
   h->off_spart = take(score, c->max_queries > 16 ? IM_SCORE_GROUPS * few_keys * sizeof(float) : 0);
   // memory write: partial sums (at most 34 MB, 68 MB with sets of several heads)
   h->off_mem = take(mem, sets * mem_splits(c, c->capacity) * (IM_DM * IM_D + IM_DM) * sizeof(float));
@@ -290,12 +291,14 @@ void exact_project(im_handle* h, hipStream_t s, const bf16_t* q, const bf16_t* U
 //   16 queries x 16 heads of 64, 131072 keys: 144 / 183; 24 queries 196 / 166
 //   64 queries x 8 heads of 16, 512 keys 29 / 35, 8192 keys 31 / 37, 131072 keys 68 / 87
 //   32 queries x 8 heads of 64, 4096 keys 42 / 46, 22400 keys 59 / 58; 64 queries 37 / 42 and 93 / 75
-bool score_few_tiles(const im_handle* h) { return (long long)((h->max_live + 255) / 256) * n_sets_of(&h->cfg) < 128; }
+//   24 queries x 8 heads of 64: 32768 keys 51 / 56, 65536 keys 70 / 77, 96000 keys 87 / 91; 40 queries 67 / 58, 99 / 86, 126 / 101
+long long score_tiles(const im_handle* h) { return (long long)((h->max_live + 255) / 256) * n_sets_of(&h->cfg); }
 bool score_short(const im_handle* h, int n_q) {
   const im_config& c = h->cfg;
   const long long ops = (long long)((n_q + 15) / 16) * c.n_idx_heads * c.idx_dim, keys = (long long)h->max_live * n_sets_of(&c);
   if (!score_may_scan(&c)) return true;   // (the workspace holds nothing for the bounds)
-  return n_q <= 16 || ops <= 512 || (score_few_tiles(h) && n_q <= 128 && ops * keys <= 24000000);
+  return n_q <= 16 || ops <= 512 || (score_tiles(h) < 128 && n_q <= 128 && ops * keys <= 24000000) ||
+         (score_tiles(h) < IM_SCORE_GROUP_TILES && n_q <= 32 && ops <= 1024);
 }
 
 // the scores of longer windows from their raw projections in the workspace
@@ -580,9 +583,9 @@ int32_t im_index_score(im_handle* h, const im_params* p, const im_state* st, con
   if (score_short(h, n_q)) {
     const int rows = M * c.n_idx_heads;
     k_qnorm_alpha<<<(rows + 3) / 4 + (rows + 255) / 256, 256, 0, s>>>(qy, rows, di, nqw, c.rms_eps, al, rows, alpha_denom);
-    // few (256-key tile, unit) workgroups: 16 keys per wave instead of 64, and a group of queries per workgroup
-    const bool small = score_few_tiles(h);
-    const int nblk = (n_q + 15) / 16, per_group = small ? (nblk + IM_SCORE_GROUPS - 1) / IM_SCORE_GROUPS * 16 : n_q;
+    // few (256-key tile, unit) workgroups: a group of queries per workgroup; very few: 16 keys per wave instead of 64, too
+    const bool small = score_tiles(h) < 128;
+    const int nblk = (n_q + 15) / 16, per_group = score_tiles(h) < IM_SCORE_GROUP_TILES ? (nblk + IM_SCORE_GROUPS - 1) / IM_SCORE_GROUPS * 16 : n_q;
     const int groups = (n_q + per_group - 1) / per_group, live = h->max_live;
     float* out = groups > 1 ? (float*)(h->ws + h->off_spart) : scores_out;
 #define IM_SCORE(TPW, DI)                                                                                          \

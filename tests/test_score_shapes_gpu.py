@@ -58,9 +58,10 @@ def _check(shared, H, Hk, batch, n, n_q, mode="plain"):
             assert wrong == 0, f"sequence {b}, set {u}: {wrong} of {n} scores differ"
 
 
-SHORT = [   # windows that are scored in fp64: 16 keys per wave and groups of queries over short caches, 64 keys over long ones
+SHORT = [   # windows that are scored in fp64: 16 keys per wave over short caches, groups of queries below 512 tiles of 256 keys
     (False, 32, 8, 1, 1, 16), (False, 32, 8, 2, 63, 17), (False, 32, 8, 1, 300, 64), (False, 28, 4, 1, 129, 128),
     (False, 64, 8, 1, 65, 33), (False, 32, 8, 4, 1025, 9), (False, 64, 8, 4, 1025, 16), (False, 16, 4, 8, 1100, 31),
+    (False, 32, 8, 4, 1025, 31), (False, 28, 4, 16, 511, 32), (False, 32, 8, 4, 4097, 17),
     (True, 32, 8, 2, 64, 49), (True, 32, 8, 2, 257, 64), (True, 28, 4, 16, 2049, 33), (True, 64, 8, 16, 2100, 32),
     (True, 4, 4, 3, 70, 511),
 ]
