@@ -69,8 +69,8 @@ def algorithmic_bytes(w: Workload) -> dict:
     }
     unit_total = sum(per_unit.values())
     layer_total = units * unit_total + sum(per_layer.values())
-    # the main kernel of the fused step (k_dec_main) streams the retained cache: the indexer key and
-    # the K / V rows of the B entries its 128-key splits cover (the newest entry is the tail kernel's)
+    # the main kernel of the fused step (k_dec_score) streams the retained cache: the indexer keys and
+    # the K / V rows of the B entries its 128-key splits cover (the newest entry is the last kernel's)
     main_kernel = units * (2 * w.idx_dim * Bg + per_unit["kv"])
     return {"per_unit": unit_total, "per_layer_step": layer_total, "main_kernel_per_launch": main_kernel,
             "attention_kv_per_layer": units * per_unit["kv"], "detail": {**per_unit, **per_layer}}
@@ -427,13 +427,13 @@ def main() -> None:
         d_p = im.im_profile_stop(job.handle)
         k_ms = float(np.mean(d_pm)) - float(np.mean(d_p))
         durs = d_pm
-        kname = "k_att_main" if w.head_shared else "k_dec_main"   # the launch that streams the cache
+        kname = "k_dec_score"   # the launch that streams the cache
         achieved = ab["main_kernel_per_launch"] / (k_ms * 1e-3) / 1e9
         traffic = None
         tpath = os.path.join(ROOT, "profiles", f"hbm_traffic_{w.name}.json")
         if os.path.exists(tpath):   # HBM bytes per launch from the committed rocprofv3 --pmc summary
             with open(tpath) as f:
-                traffic = json.load(f)["kernels"].get(f"{kname}<{w.group}>", {}).get("total_bytes")
+                traffic = next((v.get("total_bytes") for k, v in json.load(f)["kernels"].items() if k.startswith(kname + "<")), None)
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kname,
                 "avg_launch_us": k_ms * 1e3, "launches_timed": len(durs),

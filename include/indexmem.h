@@ -258,7 +258,7 @@ int32_t im_decode_attn_with_readout_static(const im_config* cfg, int32_t max_liv
  * scores_dbg [B, H_kv, C] fp32 (as im_index_score writes them).
  * batch <= 64.  n_sink + n_recent <= budget <= capacity - 1 is not required, but a unit with
  * len = capacity cannot take the new token (IM_STATUS_APPEND_OVERFLOW).
- * head_shared = 1: the same step as im_append_kv_hidden(n_new = 1) -> ... in four launches; x_gate
+ * head_shared = 1: the same step as im_append_kv_hidden(n_new = 1) -> ..., in three launches, too; x_gate
  * [B, gate_in_dim] is the new token's hidden state (it feeds the head gate and the token's indexer
  * key); evicted_slot is [B], scores_dbg [B, C]; at most 16 KV heads and max_live <= 8193. */
 int32_t im_decode_step(im_handle* h, const im_params* p, const im_state* st, const void* q,
@@ -285,7 +285,7 @@ int32_t im_attend_step_hidden(im_handle* h, const im_params* p, const im_state* 
 
 /* Index reuse across neighbouring layers (Appendix "From Running Mean to IndexCache": the indexer
  * runs once per group of layers and the other layers of the group reuse its decision).  The step
- * of a FOLLOWER layer for one new token per sequence, three launches, nothing scored: exactly
+ * of a FOLLOWER layer for one new token per sequence, two launches, nothing scored: exactly
  *   im_append_kv(n_new = 1) -> im_memory_update + im_compact_kv with the single entry in slot
  *   evict_slot[b, h] (as the cache stands after the append; -1 or >= len: nothing leaves) ->
  *   im_decode_attn_with_readout.
@@ -314,14 +314,14 @@ int32_t im_decode_step_shared_hidden(im_handle* h, const im_params* p, const im_
 int32_t im_stream_read(const void* src, size_t bytes, uint32_t never, void* sink, void* stream);
 
 /* Kernel timing for benchmarks (not part of the method).  After im_profile_start, every
- * im_decode_step on this handle brackets part of its launch sequence (prep kernel, main kernel,
- * tail kernel) with a pair of HIP events on the launch stream, for at most max_records calls:
- *   IM_PROFILE_MAIN           the main kernel alone (scoring and attention partials of every
+ * im_decode_step on this handle brackets part of its launch sequence (projections; scores and attention
+ * partials; the rest) with a pair of HIP events on the launch stream, for at most max_records calls:
+ *   IM_PROFILE_MAIN           the second launch alone (scores, and attention partials of every
  *                             128-key split: the launch that streams the cache);
- *   IM_PROFILE_PREP           the prep kernel alone;
+ *   IM_PROFILE_PREP           the first launch alone;
  *   IM_PROFILE_PREP_AND_MAIN  both, with no event between them.
  * An event pair around one launch also spans the hand-over between the event and the dispatch;
- * mean(PREP_AND_MAIN) - mean(PREP) is the main kernel as it runs behind the prep kernel.
+ * mean(PREP_AND_MAIN) - mean(PREP) is the second launch as it runs behind the first.
  * im_profile_stop WAITS for `stream`, writes the elapsed milliseconds of the recorded spans to
  * ms_host[0 .. *n_records) (host pointers; ms_host holds max_records floats) and releases the
  * events.  Do not use while the stream is being captured into a graph. */

@@ -322,9 +322,8 @@ __device__ __forceinline__ void att_pv(const float (&pr)[2][4], const uint4 (&vf
   }
 }
 
-// leaves o in LDS: dst[head * IM_D + dim] of this wave
-template <int G>
-__device__ __forceinline__ void att_store(const im_c4 (&o)[8], float* dst, int l16, int kq) {
+// leaves o of G heads in LDS: dst[head * IM_D + dim] of this wave
+__device__ __forceinline__ void att_store(const im_c4 (&o)[8], float* dst, int l16, int kq, int G) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     if (4 * kq + r < G) {

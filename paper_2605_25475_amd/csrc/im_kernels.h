@@ -1765,7 +1765,7 @@ __global__ __launch_bounds__(256) void k_attn_partial(const bf16_t* __restrict__
   if (kq == 0 && l16 < G) { s_ml[w][l16][0] = mw; s_ml[w][l16][1] = lsum; }
   im_c4 o[8];
   att_pv(sreg, vf, o);
-  att_store<G>(o, &s_acc[w][0][0], l16, kq);
+  att_store(o, &s_acc[w][0][0], l16, kq, G);
   __syncthreads();
   for (int idx = tid; idx < G * IM_D; idx += 256) {
     const int j = idx >> 7, d = idx & 127;

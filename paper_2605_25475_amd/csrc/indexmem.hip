@@ -24,10 +24,10 @@ struct im_handle {
   int max_live;
   bool ws_ready;
   // workspace layout (byte offsets)
-  size_t off_status, off_qy, off_alpha, off_mem, off_attn, off_dpart, off_dcand, off_dqm, off_xk, off_hspart, total;
+  size_t off_status, off_qy, off_alpha, off_mem, off_attn, off_dpart, off_dml, off_dqm, off_xk, off_dpick, off_darrived, total;
   size_t off_xexp, off_xcount, off_xplanes, off_xlist;              // exact products
   size_t off_spart, off_qf, off_al16, off_qblk, off_recu, off_reci, off_nlist, off_list;   // scores of several queries
-  int attn_chunks, dec_splits;
+  int attn_chunks;
   // optional kernel timing (im_profile_start / im_profile_stop)
   hipEvent_t* prof_ev;
   int prof_max, prof_n, prof_span;
@@ -187,12 +187,13 @@ void layout(const im_config* c, im_handle* h) {
   h->attn_chunks = (c->capacity + IM_ATT_CHUNK - 1) / IM_ATT_CHUNK;
   h->off_attn = take(attn, B * c->n_q_heads * h->attn_chunks * IM_ATT_REC * sizeof(float));
   // the fused steps; head_shared: U_k X of the rows of one append or step, fp64
-  h->dec_splits = (c->capacity + DEC_KEYS - 1) / DEC_KEYS + 1;   // + the last-slot record
-  h->off_dpart = take(step, units * h->dec_splits * DEC_GMAX * DEC_REC * sizeof(float));  // upper bound: G <= 8
-  h->off_dcand = take(step, units * h->dec_splits * DEC_CAND * sizeof(uint32_t));
-  h->off_dqm = take(step, units * DEC_GMAX * DEC_QM * sizeof(float));
+  const size_t splits = (c->capacity + DEC_KEYS - 1) / DEC_KEYS, G = c->n_q_heads / c->n_kv_heads;
+  h->off_dpart = take(step, units * splits * G * IM_D * sizeof(float));
+  h->off_dml = take(step, units * splits * G * sizeof(float2));
+  h->off_dqm = take(step, units * G * DEC_QM * sizeof(float));
   h->off_xk = take(step, c->head_shared ? B * c->capacity * IM_DI_SHARED * sizeof(double) : 0);
-  h->off_hspart = take(step, c->head_shared ? B * HS_NSC * sizeof(uint4) : 0);
+  h->off_dpick = take(step, sets * ((c->capacity + 15) / 16) * sizeof(uint4));
+  h->off_darrived = take(step, sets * sizeof(int32_t));
   h->total = score;
   for (size_t end : {mem, attn, step}) h->total = end > h->total ? end : h->total;
 }
@@ -226,27 +227,48 @@ int n_sets(const im_config& c) { return c.batch * c.n_kv_heads / heads_per_set(c
 #define IM_REQUIRE(cond, msg) \
   do { if (!(cond)) return set_err(h, IM_ERR_INVALID_ARG, "%s: %s", __func__, msg); } while (0)
 
-// the tail kernel stages CHW split records per round: the smallest variant that holds the launch's
-// splits (more splits than the largest variant are merged in several rounds)
-template <int G>
-void launch_tail(const DecArgs& a, int units, hipStream_t s) {
-  // one workgroup per (unit, head) when those fit the chip once and one staging round holds the splits
-  if (units * G <= 256 && a.S <= 64) {
-    if (a.S <= 8) k_dec_tail_head<G, 8><<<units * G, DEC_TT, 0, s>>>(a);
-    else if (a.S <= 16) k_dec_tail_head<G, 16><<<units * G, DEC_TT, 0, s>>>(a);
-    else if (a.S <= 32) k_dec_tail_head<G, 32><<<units * G, DEC_TT, 0, s>>>(a);
-    else k_dec_tail_head<G, 64><<<units * G, DEC_TT, 0, s>>>(a);
-    return;
-  }
-  if constexpr (G <= 4) {
-    if (a.S <= 8) k_dec_tail<G, 8><<<units, DEC_TT, 0, s>>>(a);
-    else if (a.S <= 16) k_dec_tail<G, 16><<<units, DEC_TT, 0, s>>>(a);
-    else k_dec_tail<G, 24><<<units, DEC_TT, 0, s>>>(a);
+// The last launch of a fused step: a workgroup of 16 waves fills a CU, so it takes the fewest query heads with which the
+// launch fits the chip once.
+template <int HPW, int DI>
+void launch_finish_as(const DecArgs& a, hipStream_t s) {
+  const int units = a.B * a.H_kv, x = units % 8 == 0 ? 8 : 1;
+  k_dec_finish<HPW, DI><<<dim3(x, (a.G + HPW - 1) / HPW, units / x), DEC_FT, 0, s>>>(a);
+}
+template <int DI>
+void launch_finish(const DecArgs& a, hipStream_t s) {
+  const int units = a.B * a.H_kv, G = a.G;
+  if (units * G <= 256 || G == 1) launch_finish_as<1, DI>(a, s);
+  else if (units * ((G + 1) / 2) <= 256 || G == 2) launch_finish_as<2, DI>(a, s);
+  else if (units * ((G + 3) / 4) <= 256 || G <= 4) launch_finish_as<4, DI>(a, s);
+  else launch_finish_as<8, DI>(a, s);
+}
+
+// The launches of a fused step; begin and end (events, or NULL) are recorded behind the first and behind the one that streams the cache
+template <int DI, int HG>
+void launch_score(const DecArgs& a, int tiles, hipStream_t s) {
+  const int units = a.B * a.H_kv, sets = units / a.H_set, n_score = (sets * ((a.n_pick + 3) / 4) + 7) / 8 * 8;
+  const int blocks = n_score + units * a.S;
+  if (tiles == 4) k_dec_score<DI, 4, HG><<<blocks, 256, 0, s>>>(a, n_score);
+  else if (tiles == 2) k_dec_score<DI, 2, HG><<<blocks, 256, 0, s>>>(a, n_score);
+  else k_dec_score<DI, 1, HG><<<blocks, 256, 0, s>>>(a, n_score);
+}
+void launch_step(const DecArgs& a, int n_roles, int prep_rows, int tiles, hipEvent_t begin, hipEvent_t end, hipStream_t s) {
+  const int units = a.B * a.H_kv;
+  if (!a.score) {
+    k_dec_attend<<<n_roles + units * a.S, 256, 0, s>>>(a, n_roles);
   } else {
-    if (a.S <= 4) k_dec_tail<G, 4><<<units, DEC_TT, 0, s>>>(a);
-    else if (a.S <= 8) k_dec_tail<G, 8><<<units, DEC_TT, 0, s>>>(a);
-    else k_dec_tail<G, 16><<<units, DEC_TT, 0, s>>>(a);
+    if (prep_rows == 4) k_dec_prep<4><<<n_roles, 256, 0, s>>>(a);
+    else k_dec_prep<8><<<n_roles, 256, 0, s>>>(a);
+    if (begin) (void)hipEventRecord(begin, s);
+    if (a.hs) {
+      if (a.H_idx <= 8) launch_score<IM_DI_SHARED, 2>(a, tiles, s); else launch_score<IM_DI_SHARED, 4>(a, tiles, s);
+    } else {
+      if (a.H_idx <= 8) launch_score<IM_DI, 2>(a, tiles, s); else launch_score<IM_DI, 4>(a, tiles, s);
+    }
   }
+  if (end) (void)hipEventRecord(end, s);
+  if (a.hs) launch_finish<IM_DI_SHARED>(a, s);
+  else launch_finish<IM_DI>(a, s);
 }
 
 // C[m][n] = sum_k A[m][k] B[n][k] in fp64: matrix cores when the contraction length allows; the contraction
@@ -825,6 +847,8 @@ static int32_t decode_launch(im_handle* h, const im_params* p, const im_state* s
   hipStream_t s = (hipStream_t)stream;
   int rc = ensure_ws(h, s);
   if (rc) return rc;
+  if (c.head_shared && c.n_kv_heads > 16)
+    return set_err(h, IM_ERR_UNSUPPORTED, "%s: head_shared = 1 with more than 16 KV heads", what);
   const int units = c.batch * c.n_kv_heads, G = c.n_q_heads / c.n_kv_heads;
   int32_t* words = (int32_t*)(h->ws + h->off_status);
   DecArgs a = {};
@@ -834,100 +858,43 @@ static int32_t decode_launch(im_handle* h, const im_params* p, const im_state* s
   a.nqw = (const bf16_t*)p->norm_q_w; a.nkw = (const bf16_t*)p->norm_k_w;
   a.Wt = (const bf16_t*)p->Wtheta; a.wg = (const bf16_t*)p->wg; a.cg = p->cg;
   a.q = (const bf16_t*)q; a.xg = (const bf16_t*)x_gate; a.k_new = (const bf16_t*)k_new;
-  a.v_new = (const bf16_t*)v_new; a.pos_new = pos_new; a.q_pos = q_pos; a.ext_evict = ext_evict;
+  a.v_new = (const bf16_t*)v_new; a.pos_new = pos_new; a.q_pos = q_pos; a.named = ext_evict;
   a.out = (bf16_t*)out; a.readout = readout_dbg; a.scores = scores_dbg; a.evicted = evicted_slot;
   a.qy = (double*)(h->ws + h->off_qy); a.alpha = (double*)(h->ws + h->off_alpha);
-  a.status = words; a.maxpos = words + 32;
-  a.part = (float*)(h->ws + h->off_dpart); a.cand = (uint32_t*)(h->ws + h->off_dcand);
-  a.qm = (float*)(h->ws + h->off_dqm);
+  a.status = words; a.maxpos = words + 32; a.arrived = (int32_t*)(h->ws + h->off_darrived);
+  a.part = (float*)(h->ws + h->off_dpart); a.part_ml = (float2*)(h->ws + h->off_dml);
+  a.qm = (float*)(h->ws + h->off_dqm); a.pick = (uint4*)(h->ws + h->off_dpick);
+  a.xk = (double*)(h->ws + h->off_xk);
   a.B = c.batch; a.H = c.n_q_heads; a.H_kv = c.n_kv_heads; a.C = c.capacity; a.H_idx = c.n_idx_heads;
   a.gate_in = c.gate_in_dim; a.n_sink = c.n_sink; a.n_recent = c.n_recent; a.budget = budget;
-  // 128-key splits for the main kernel; a single key beyond a multiple of 128 (the steady state with
-  // a budget that is a multiple of 128) is left to the tail kernel instead of a one-key split
-  a.S = (h->max_live % DEC_KEYS == 1 && h->max_live > 1) ? h->max_live / DEC_KEYS
-                                                         : (h->max_live + DEC_KEYS - 1) / DEC_KEYS;
-  a.S_alloc = h->dec_splits; a.max_live = h->max_live;
+  // 128-key splits over all live entries but the last, which the second launch takes
+  a.S = h->max_live > 1 ? (h->max_live - 1 + DEC_KEYS - 1) / DEC_KEYS : 1;
+  a.max_live = h->max_live;
   a.rms_eps = c.rms_eps; a.mem_eps = c.mem_eps; a.scale = c.softmax_scale; a.lambda = lambda; a.eta = eta;
-  a.hs = c.head_shared; a.H_set = heads_per_set(c); a.di = c.idx_dim; a.xk = (double*)(h->ws + h->off_xk);
-  if (c.head_shared) {
-    // four launches: projections + append + readout terms; the sequence's scores and decision; the
-    // attention partials with that slot named; the per-(unit, head) tail
-    a.hs_part = (uint4*)(h->ws + h->off_hspart);
-    a.hs_evict = words + 32;   // [units]
-    a.hs_named = ext_evict;    // a follower step: one slot per sequence from the caller
-    a.ext_evict = a.hs_evict;
-    if (c.n_kv_heads > 16) return set_err(h, IM_ERR_UNSUPPORTED, "%s: head_shared = 1 with more than 16 KV heads", what);
-    a.attend = no_score ? 1 : 0;   // attend-only: U_k alone in the prep launch, no scoring launch
-    const int hs_prep_blocks = (1 + DEC_MP) * units + IM_DI_SHARED / 2 +
-                               (no_score ? 0 : c.n_idx_heads * IM_DI_SHARED / 2 + (c.n_idx_heads + 1) / 2);
-    const int hs_main_blocks = units * (a.S > 0 ? a.S : 1);
-    const bool hprof = h->prof_ev && h->prof_n < h->prof_max;
-    hipEvent_t hev0 = hprof ? h->prof_ev[2 * h->prof_n] : nullptr, hev1 = hprof ? h->prof_ev[2 * h->prof_n + 1] : nullptr;
-    // an attend-only or follower step has nothing between its projections and its attention: the prep
-    // roles ride in the attention launch (two launches in all)
-    const bool merged = no_score;
-    if (hprof && (merged || h->prof_span != IM_PROFILE_MAIN)) (void)hipEventRecord(hev0, s);
-    if (!merged) {
-      k_hs_prep<<<hs_prep_blocks, 256, 0, s>>>(a);
-      k_hs_score<<<c.batch * HS_NSC, HS_ST, 0, s>>>(a);
-      if (hprof && h->prof_span == IM_PROFILE_MAIN) (void)hipEventRecord(hev0, s);
-      if (hprof && h->prof_span == IM_PROFILE_PREP) (void)hipEventRecord(hev1, s);
-    }
-#define IM_HS_CASE(g)                                                                  \
-  case g:                                                                              \
-    if (merged) k_att_merged<g><<<hs_prep_blocks + hs_main_blocks, DEC_MT / 2, 0, s>>>(a, hs_prep_blocks); \
-    else k_att_main<g><<<hs_main_blocks, DEC_MT / 2, 0, s>>>(a);                       \
-    if (hprof && (merged || h->prof_span != IM_PROFILE_PREP)) (void)hipEventRecord(hev1, s); \
-    if (a.S <= 8) k_dec_tail_head<g, 8><<<units * g, DEC_TT, 0, s>>>(a);               \
-    else if (a.S <= 16) k_dec_tail_head<g, 16><<<units * g, DEC_TT, 0, s>>>(a);        \
-    else if (a.S <= 32) k_dec_tail_head<g, 32><<<units * g, DEC_TT, 0, s>>>(a);        \
-    else k_dec_tail_head<g, 64><<<units * g, DEC_TT, 0, s>>>(a);                       \
-    break;
-    switch (G) {
-      IM_HS_CASE(1) IM_HS_CASE(2) IM_HS_CASE(3) IM_HS_CASE(4)
-      IM_HS_CASE(5) IM_HS_CASE(6) IM_HS_CASE(7) IM_HS_CASE(8)
-      default: return set_err(h, IM_ERR_UNSUPPORTED, "group size %d", G);
-    }
-#undef IM_HS_CASE
-    if (hprof) h->prof_n++;
-    return launch_check(h, what);
-  }
-  // the per-unit blocks come first in the prep kernel's block order: an attend-only step launches
-  // just those (no query-side indexer projections)
-  const int row_pairs = c.n_idx_heads * IM_DI / 2 + (c.n_idx_heads + 1) / 2;
-  // projection blocks take 4 batch rows each (a shorter chain per block) while the grid then still is
-  // one generation of workgroups (4 per CU), else 8
-  const int prep_rows = (row_pairs * ((c.batch + 3) / 4) + (1 + DEC_MP) * units <= 4 * 256) ? 4 : 8;
-  const int prep_blocks = (no_score ? 0 : row_pairs * ((c.batch + prep_rows - 1) / prep_rows)) + (1 + DEC_MP) * units;
-  const int main_blocks = units * (a.S > 0 ? a.S : 1);
+  a.G = G; a.kv_magic = (uint32_t)((1ull << 32) / (unsigned)c.n_kv_heads) + 1u;
+  a.alpha_denom = sqrt((double)(c.n_idx_heads * c.idx_dim));
+  a.hs = c.head_shared; a.H_set = heads_per_set(c); a.di = c.idx_dim; a.score = no_score ? 0 : 1;
+  // projection blocks take two weight rows (U_q and G where the step scores, U_k in the head-shared layout) and 4 batch rows each (a
+  // shorter chain per block) while the roles then still are one generation of workgroups (4 per CU), else 8
+  const int row_pairs = (a.score ? c.n_idx_heads * c.idx_dim / 2 + (c.n_idx_heads + 1) / 2 : 0) + (a.hs ? IM_DI_SHARED / 2 : 0);
+  const int prep_rows = a.score && row_pairs * ((c.batch + 3) / 4) + (1 + DEC_MP) * units > 4 * 256 ? 8 : 4;
+  a.n_proj = row_pairs * ((c.batch + prep_rows - 1) / prep_rows);
+  const int n_roles = ((1 + DEC_MP) * units + a.n_proj + 7) / 8 * 8;
+  // 16-key tiles per wave of the scoring launch: about one wave per SIMD (1024) where there are so many keys
+  const long long key_tiles = (long long)n_sets(c) * ((h->max_live + 15) / 16);
+  const int tiles = key_tiles > 2048 ? 4 : key_tiles > 1024 ? 2 : 1;
+  a.n_pick = a.score ? (a.max_live + 16 * tiles - 1) / (16 * tiles) : 0;
   const bool prof = h->prof_ev && h->prof_n < h->prof_max;
   hipEvent_t ev0 = prof ? h->prof_ev[2 * h->prof_n] : nullptr, ev1 = prof ? h->prof_ev[2 * h->prof_n + 1] : nullptr;
-  // a step that scores nothing has nothing between its prep roles and its attention: they share a
-  // launch (a follower's tail then takes the moved entry's indexer key from the cache, where the
-  // launch's unit block has put the new token's, instead of from the last-slot record)
-  const bool merged = no_score;
-  a.kidx_in_cache = (merged && ext_evict) ? 1 : 0;
-  if (prof && (merged || h->prof_span != IM_PROFILE_MAIN)) (void)hipEventRecord(ev0, s);
-  if (!merged) {
-    if (prep_rows == 4) k_dec_prep<4><<<prep_blocks, 256, 0, s>>>(a);
-    else k_dec_prep<8><<<prep_blocks, 256, 0, s>>>(a);
-    if (prof && h->prof_span == IM_PROFILE_MAIN) (void)hipEventRecord(ev0, s);
-    if (prof && h->prof_span == IM_PROFILE_PREP) (void)hipEventRecord(ev1, s);
+  // what a step of three launches brackets: the first, the second, or both; of two launches the first
+  hipEvent_t mid = nullptr, end = nullptr;
+  if (prof) {
+    const bool three = a.score != 0;
+    if (!three || h->prof_span != IM_PROFILE_MAIN) (void)hipEventRecord(ev0, s);
+    if (three && h->prof_span == IM_PROFILE_MAIN) mid = ev0;
+    if (three && h->prof_span == IM_PROFILE_PREP) mid = ev1; else end = ev1;
   }
-#define IM_DEC_CASE(g)                                              \
-  case g:                                                           \
-    if (merged) k_att_merged<g><<<prep_blocks + main_blocks, DEC_MT / 2, 0, s>>>(a, prep_blocks); \
-    else if (no_score) k_att_main<g><<<main_blocks, DEC_MT / 2, 0, s>>>(a); \
-    else k_dec_main<g><<<main_blocks, DEC_MT, 0, s>>>(a, a.qy, a.alpha); \
-    if (prof && (merged || h->prof_span != IM_PROFILE_PREP)) (void)hipEventRecord(ev1, s); \
-    launch_tail<g>(a, units, s);                                    \
-    break;
-  switch (G) {
-    IM_DEC_CASE(1) IM_DEC_CASE(2) IM_DEC_CASE(3) IM_DEC_CASE(4)
-    IM_DEC_CASE(5) IM_DEC_CASE(6) IM_DEC_CASE(7) IM_DEC_CASE(8)
-    default: return set_err(h, IM_ERR_UNSUPPORTED, "group size %d", G);
-  }
-#undef IM_DEC_CASE
+  launch_step(a, n_roles, prep_rows, tiles, mid, end, s);
   if (prof) h->prof_n++;
   return launch_check(h, what);
 }
