@@ -11,6 +11,8 @@ LIB_PATH = os.path.join(PKG_DIR, "libindexmem.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    # up to 16 registers of leading scalar arguments are loaded before a wave starts (not by it)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     # packed fp32 instructions are kept out of the generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",

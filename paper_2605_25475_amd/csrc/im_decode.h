@@ -379,19 +379,33 @@ struct DecSplitSmem {
 };
 
 // live entries of a unit as its workgroups treat it, the new token included: at most max_live (n), and the true length
-__device__ __forceinline__ int dec_true_len(const DecArgs& a, int n_old) { return n_old + ((n_old + 1 <= a.C) ? 1 : 0); }
+__device__ __forceinline__ int dec_true_len(int C, int n_old) { return n_old + ((n_old + 1 <= C) ? 1 : 0); }
+
+// What the first loads of a workgroup need, as leading arguments of their own.  The build has leading arguments put into registers before a
+// wave starts, which a struct never is, so the length is on its way while the rest (DecArgs) is read: one round trip of a chain of
+// four (arguments, length, rows, result).  4 x 2048 entries x 8 heads, 32 layer-steps: 747 us with all in the struct, 738 with these
+// arguments read from memory, 722 now; 127 steps without scores and one with, in two layers: 4160, 3976, 3893.
+#define DEC_HEAD \
+  const int32_t *len, const bf16_t *K, const int C, const int max_live, const int H_kv, const uint32_t kv_magic, const int H_set
+struct DecHead {
+  const int32_t* len;
+  const bf16_t* K;
+  int C, max_live, H_kv;
+  uint32_t kv_magic;
+  int H_set;
+};
 
 // One (unit, split) workgroup: the attention partial of its 128 keys.  The splits cover slots [0, n - 1): the last live
 // one, as a rule the new token, which this launch appends, is k_dec_finish's.
-__device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const int s, DecSplitSmem& sm) {
-  const int tid = threadIdx.x, lane = tid & 63, G = a.G;
+__device__ __forceinline__ void dec_split(const DecArgs& a, const DecHead& hd, const int u, const int s, DecSplitSmem& sm) {
+  const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // a scalar, so that branches on it are uniform
-  const int b = u / a.H_kv, h = u % a.H_kv;
-  const int n = min(dec_true_len(a, a.len[u / a.H_set]), a.max_live);
+  const int b = hd.H_kv == 1 ? u : (int)__umulhi((unsigned)u, hd.kv_magic), h = u - b * hd.H_kv;   // u / H_kv, u % H_kv
+  const int n = min(dec_true_len(hd.C, hd.len[hd.H_set == 1 ? u : b]), hd.max_live);
   const int k0 = s * DEC_KEYS;
   const int nk = min(DEC_KEYS, n - 1 - k0);
   if (nk <= 0) return;
-  const size_t base = (size_t)u * a.C + k0;
+  const size_t base = (size_t)u * hd.C + k0;
   const int l16 = lane & 15, kq = lane >> 4;
   // rows past the end of the split are read from its last row instead (finite values, no branches):
   // their logits are masked and their probabilities are zero further down
@@ -403,8 +417,9 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
   for (int tt = 0; tt < 2; ++tt) {
     const int kr = min(16 * (2 * w + tt) + l16, nk - 1);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) kf[tt][c] = load_stream16(a.K + (base + kr) * IM_D + 32 * c + 8 * kq);
+    for (int c = 0; c < 4; ++c) kf[tt][c] = load_stream16(hd.K + (base + kr) * IM_D + 32 * c + 8 * kq);
   }
+  const int G = a.G;
   {
     // lanes past the group repeat its last head (their logits and probabilities are not used)
     const int jq = min(l16, G - 1);
@@ -471,9 +486,8 @@ __device__ __forceinline__ void dec_split(const DecArgs& a, const int u, const i
 }
 
 // The split workgroup at index blk: consecutive ones take different units, the short last splits come last
-__device__ __forceinline__ void dec_split_block(const DecArgs& a, const int blk, DecSplitSmem& sm) {
-  const int U = a.B * a.H_kv;
-  dec_split(a, blk % U, blk / U, sm);
+__device__ __forceinline__ void dec_split_block(const DecArgs& a, const DecHead& hd, const int blk, const int U, DecSplitSmem& sm) {
+  dec_split(a, hd, blk % U, blk / U, sm);
 }
 
 // role block r: units, then DEC_MP per unit, then projections
@@ -499,9 +513,9 @@ __global__ __launch_bounds__(256) void k_dec_prep(const DecArgs a) {
 }
 
 // grid: n_roles role blocks (idle ones up to a multiple of 8), then units * S split workgroups
-__global__ __launch_bounds__(256, 4) void k_dec_attend(const DecArgs a, const int n_roles) {
+__global__ __launch_bounds__(256, 4) void k_dec_attend(DEC_HEAD, const int n_roles, const int U, const DecArgs a) {
   __shared__ __attribute__((aligned(16))) union SM { DecSplitSmem sm; DecPrepSmem ps; __device__ SM() {} } s;
-  if ((int)blockIdx.x >= n_roles) dec_split_block(a, blockIdx.x - n_roles, s.sm);
+  if ((int)blockIdx.x >= n_roles) dec_split_block(a, DecHead{len, K, C, max_live, H_kv, kv_magic, H_set}, blockIdx.x - n_roles, U, s.sm);
   else dec_role<4>(a, blockIdx.x, s.ps);   // (nothing to project but U_k)
 }
 
@@ -578,7 +592,7 @@ __device__ __forceinline__ void dec_score_block(const DecArgs& a, const int su, 
   }
   // (only LDS is shared here: the keys stay in flight)
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  const int n = min(dec_true_len(a, n_old), a.max_live);
+  const int n = min(dec_true_len(a.C, n_old), a.max_live);
   const int n_tiles = (n - key0 + 15) / 16;   // (of the wave that hold live keys; may be <= 0)
   float sc = 0.f;
   if (n_tiles > 0) {
@@ -639,11 +653,14 @@ __device__ __forceinline__ void dec_score_block(const DecArgs& a, const int su, 
 
 // grid: sets * ceil(n_pick / 4) scoring workgroups, idle ones up to a multiple of 8 (n_score in all), then units * S split workgroups
 template <int DI, int T, int HG>
-__global__ __launch_bounds__(256, HG == 2 ? 4 : 2) void k_dec_score(const DecArgs a, const int n_score) {
+__global__ __launch_bounds__(256, HG == 2 ? 4 : 2) void k_dec_score(DEC_HEAD, const int n_score, const int U, const DecArgs a) {
   __shared__ __attribute__((aligned(16))) union SM { DecSplitSmem sm; DecScoreSmem<DI> sc; __device__ SM() {} } s;
-  const int sets = DI == 16 ? a.B : a.B * a.H_kv, part = blockIdx.x / sets;
-  if ((int)blockIdx.x >= n_score) dec_split_block(a, blockIdx.x - n_score, s.sm);
-  else if (4 * part < a.n_pick) dec_score_block<DI, T, HG>(a, blockIdx.x - part * sets, part, s.sc);
+  if ((int)blockIdx.x >= n_score) {
+    dec_split_block(a, DecHead{len, K, C, max_live, H_kv, kv_magic, H_set}, blockIdx.x - n_score, U, s.sm);
+    return;
+  }
+  const int sets = DI == 16 ? a.B : U, part = blockIdx.x / sets;
+  if (4 * part < a.n_pick) dec_score_block<DI, T, HG>(a, blockIdx.x - part * sets, part, s.sc);
 }
 
 // --------------------------------------------------------------------------------------------
@@ -666,19 +683,19 @@ struct DecFinishSmem {
 // has seen its partials and readout terms.  Nobody waits for another: what they read of the cache and one of them has to
 // change (the hole, the length) is changed by the last to arrive at a counter, when all have read it.
 template <int HPW, int DI>
-__global__ __launch_bounds__(DEC_FT) void k_dec_finish(const DecArgs a) {
+__global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a) {
   __shared__ __attribute__((aligned(16))) DecFinishSmem<HPW, DI> sm;
   const int G = a.G, g = blockIdx.y, u = blockIdx.x + gridDim.x * blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int b = a.H_kv == 1 ? u : (int)__umulhi((unsigned)u, a.kv_magic), h = u - b * a.H_kv;   // u / H_kv, u % H_kv
+  const int b = H_kv == 1 ? u : (int)__umulhi((unsigned)u, kv_magic), h = u - b * H_kv;   // u / H_kv, u % H_kv
   const int su = DI == 16 ? b : u;
   const int members = (DI == 16 ? a.H_kv : 1) * gridDim.y, member = (DI == 16 ? h * gridDim.y : 0) + g;   // of the set's workgroups
-  const int n_old = a.len[su];
-  const int n_true = dec_true_len(a, n_old), n = min(n_true, a.max_live);   // n >= 1
+  const int n_old = len[su];
+  const int n_true = dec_true_len(C, n_old), n = min(n_true, max_live);   // n >= 1
   const bool over = n_true > n;   // the live-length promise is broken (flagged): nothing is evicted, the true length stays
   const int n_act = (n - 1 + DEC_KEYS - 1) / DEC_KEYS;   // splits with live keys
-  const bf16_t* Ku = a.K + (size_t)u * a.C * IM_D;
+  const bf16_t* Ku = K + (size_t)u * C * IM_D;
   const bf16_t* Vu = a.V + (size_t)u * a.C * IM_D;
   const bf16_t* qg = a.q + ((size_t)b * a.H + h * G + g * HPW) * IM_D;   // the workgroup's first head
   const int heads = min(HPW, G - g * HPW);

@@ -232,7 +232,7 @@ int n_sets(const im_config& c) { return c.batch * c.n_kv_heads / heads_per_set(c
 template <int HPW, int DI>
 void launch_finish_as(const DecArgs& a, hipStream_t s) {
   const int units = a.B * a.H_kv, x = units % 8 == 0 ? 8 : 1;
-  k_dec_finish<HPW, DI><<<dim3(x, (a.G + HPW - 1) / HPW, units / x), DEC_FT, 0, s>>>(a);
+  k_dec_finish<HPW, DI><<<dim3(x, (a.G + HPW - 1) / HPW, units / x), DEC_FT, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, a);
 }
 template <int DI>
 void launch_finish(const DecArgs& a, hipStream_t s) {
@@ -248,14 +248,14 @@ template <int DI, int HG>
 void launch_score(const DecArgs& a, int tiles, hipStream_t s) {
   const int units = a.B * a.H_kv, sets = units / a.H_set, n_score = (sets * ((a.n_pick + 3) / 4) + 7) / 8 * 8;
   const int blocks = n_score + units * a.S;
-  if (tiles == 4) k_dec_score<DI, 4, HG><<<blocks, 256, 0, s>>>(a, n_score);
-  else if (tiles == 2) k_dec_score<DI, 2, HG><<<blocks, 256, 0, s>>>(a, n_score);
-  else k_dec_score<DI, 1, HG><<<blocks, 256, 0, s>>>(a, n_score);
+  if (tiles == 4) k_dec_score<DI, 4, HG><<<blocks, 256, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, n_score, units, a);
+  else if (tiles == 2) k_dec_score<DI, 2, HG><<<blocks, 256, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, n_score, units, a);
+  else k_dec_score<DI, 1, HG><<<blocks, 256, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, n_score, units, a);
 }
 void launch_step(const DecArgs& a, int n_roles, int prep_rows, int tiles, hipEvent_t begin, hipEvent_t end, hipStream_t s) {
   const int units = a.B * a.H_kv;
   if (!a.score) {
-    k_dec_attend<<<n_roles + units * a.S, 256, 0, s>>>(a, n_roles);
+    k_dec_attend<<<n_roles + units * a.S, 256, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, n_roles, units, a);
   } else {
     if (prep_rows == 4) k_dec_prep<4><<<n_roles, 256, 0, s>>>(a);
     else k_dec_prep<8><<<n_roles, 256, 0, s>>>(a);
