@@ -17,9 +17,9 @@
 // with none, a quarter, half, all of the splits there 746, 780, 795, 810 us, of 1 x 4096 619, 662, 656, 638.
 // Split and scoring workgroups are different ones, so the decision is not known to a partial: it holds all of its keys, and
 // k_dec_finish takes the evicted one out again.  With the roles as waves of one workgroup that met at a barrier, every split left its
-// last-ranked entry out and wrote it to a record, and the last launch staged all records: 23.9 us a layer-step of 4 x 2048 entries x 8 heads,
-// 23.2 now (1 x 4096: 21.4, 19.1; 8 x 1024 with index reuse over four layers: 20.8, 18.7; head-shared 4 x 2048, with a launch
-// of its own for the scores: 26.8, 22.1).
+// last-ranked entry out and wrote it to a record, and the last launch staged all records: 23.9 us a layer-step of 4 x 2048 entries x
+// 8 heads, 22.6 now (1 x 4096: 21.4, 18.4; 8 x 1024 with index reuse over four layers: 20.7, 18.3; head-shared 4 x 2048, with a
+// launch of its own for the scores: 26.8, 21.6).
 // Same results as append -> index_score (n_q = 1) -> topb_select -> memory_update -> compact_kv
 // -> decode_attn_with_readout whenever every unit enters with len <= budget.
 #pragma once
@@ -538,11 +538,11 @@ struct DecScoreSmem {
   bf16_t kn[16];         // head-shared layout: the new token's key
 };
 
-// A scoring workgroup (part `part` of a set's keys): 4 waves of T tiles of 16 keys.  Scores on the fp64 matrix cores, in their 4x4x4 form: four blocks of 4 heads
-// x 4 keys x 4 dims an instruction (16 cycles), so 8 heads take half of the time of the 16x16x4 form, whose columns they would
-// half fill; HG groups of 4 heads.  The
-// wave's entry ranked last by (score, then position, then slot), with sinks and the recent window forced to the top, goes to
-// the workspace, and the scores to the caller, if wanted.  T is chosen for one wave per SIMD where there are so many keys.
+// A scoring workgroup (part `part` of a set's keys): 4 waves of T tiles of 16 keys.  Scores on the fp64 matrix cores, in their 4x4x4
+// form: four blocks of 4 heads x 4 keys x 4 dims an instruction (16 cycles), so that 8 heads waste no columns (4 tiles: 1.75 us, 2.2
+// in the 16x16x4 form, whose columns they half fill); HG groups of 4 heads.  The wave's entry ranked last by (score, then position,
+// then slot), with sinks and the recent window forced to the top, goes to the workspace, and the scores to the caller, if wanted.
+// Bound by its chain (arguments, features, norm, products, rank): 7 us alone, hidden beside the split workgroups (10.8 us alone).
 template <int DI, int T, int HG>
 __device__ __forceinline__ void dec_score_block(const DecArgs& a, const int su, const int part, DecScoreSmem<DI>& sm) {
   constexpr int NH = DI == 64 ? 4 : 1, DPL = DI / 4;   // heads per wave (DI = 16: per row of 16 lanes); dims per lane of an operand
@@ -682,6 +682,8 @@ struct DecFinishSmem {
 // grid: (X, ceil(G / HPW), units / X), a workgroup per (unit, group of HPW query heads); X = 8 puts unit u on XCD u % 8, whose L2
 // has seen its partials and readout terms.  Nobody waits for another: what they read of the cache and one of them has to
 // change (the hole, the length) is changed by the last to arrive at a counter, when all have read it.
+// Bound by its chain: length, partials and ranked entries, the evicted rows, the sums (6.0 us at 4 x 2048 entries x 8 heads; the form
+// that staged a record per split took 6.1 behind a launch of 13.6 instead of 11.0).
 template <int HPW, int DI>
 __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a) {
   __shared__ __attribute__((aligned(16))) DecFinishSmem<HPW, DI> sm;
@@ -781,7 +783,10 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       if (mine) {
         m_all = m;
         l_all = lane < n_act ? ml[jj].y * __expf(ml[jj].x - m) : 0.f;
-        for (int sp = lane + 64; sp < n_act; sp += 64) l_all = fmaf(mlu[sp * G + g * HPW + jj].y, __expf(mlu[sp * G + g * HPW + jj].x - m), l_all);
+        for (int sp = lane + 64; sp < n_act; sp += 64) {
+          const float2 t = mlu[sp * G + g * HPW + jj];
+          l_all = fmaf(t.y, __expf(t.x - m), l_all);
+        }
         l_all = wave_sum_f(l_all);
         dn = wave_sum_f(lane < DEC_MP ? dn : 0.f);
       }

@@ -228,7 +228,8 @@ int n_sets(const im_config& c) { return c.batch * c.n_kv_heads / heads_per_set(c
   do { if (!(cond)) return set_err(h, IM_ERR_INVALID_ARG, "%s: %s", __func__, msg); } while (0)
 
 // The last launch of a fused step: a workgroup of 16 waves fills a CU, so it takes the fewest query heads with which the
-// launch fits the chip once.
+// launch fits the chip once.  Passes over 32 layer-steps with 1, 2, 4 heads, us: 32 units of 4 heads 724, 744, 804; 64 of 4 589, 585,
+// 654; 64 of 7 893, 793, 829.
 template <int HPW, int DI>
 void launch_finish_as(const DecArgs& a, hipStream_t s) {
   const int units = a.B * a.H_kv, x = units % 8 == 0 ? 8 : 1;
@@ -875,14 +876,17 @@ static int32_t decode_launch(im_handle* h, const im_params* p, const im_state* s
   a.alpha_denom = sqrt((double)(c.n_idx_heads * c.idx_dim));
   a.hs = c.head_shared; a.H_set = heads_per_set(c); a.di = c.idx_dim; a.score = no_score ? 0 : 1;
   // projection blocks take two weight rows (U_q and G where the step scores, U_k in the head-shared layout) and 4 batch rows each (a
-  // shorter chain per block) while the roles then still are one generation of workgroups (4 per CU), else 8
+  // shorter chain per block) while the roles then still are one generation of workgroups (4 per CU), else 8: 16 sequences x 4 heads,
+  // 32 layer-steps 845 us with 4, 802 with 8
   const int row_pairs = (a.score ? c.n_idx_heads * c.idx_dim / 2 + (c.n_idx_heads + 1) / 2 : 0) + (a.hs ? IM_DI_SHARED / 2 : 0);
   const int prep_rows = a.score && row_pairs * ((c.batch + 3) / 4) + (1 + DEC_MP) * units > 4 * 256 ? 8 : 4;
   a.n_proj = row_pairs * ((c.batch + prep_rows - 1) / prep_rows);
   const int n_roles = ((1 + DEC_MP) * units + a.n_proj + 7) / 8 * 8;
-  // 16-key tiles per wave of the scoring launch: about one wave per SIMD (1024) where there are so many keys
+  // 16-key tiles per wave of the scoring launch: a wave's fixed chain is paid once for its tiles, and few waves leave SIMDs without one.
+  // Passes over 32 layer-steps with 1, 2, 4 tiles, us: 1312 tiles in all 550, 560, 555; 1824: 602, 588, 617; 2080: 603, 597, 610; 2056
+  // (8 sets): 640, 592, 598; 2112 (64 sets) 786, 783, 801; 4128: 830, 748, 725
   const long long key_tiles = (long long)n_sets(c) * ((h->max_live + 15) / 16);
-  const int tiles = key_tiles > 2048 ? 4 : key_tiles > 1024 ? 2 : 1;
+  const int tiles = key_tiles > 3072 ? 4 : key_tiles > 1536 ? 2 : 1;
   a.n_pick = a.score ? (a.max_live + 16 * tiles - 1) / (16 * tiles) : 0;
   const bool prof = h->prof_ev && h->prof_n < h->prof_max;
   hipEvent_t ev0 = prof ? h->prof_ev[2 * h->prof_n] : nullptr, ev1 = prof ? h->prof_ev[2 * h->prof_n + 1] : nullptr;

@@ -33,8 +33,9 @@ def test_query_heads_per_workgroup(shared, batch, hq, hkv):
 
 @pytest.mark.parametrize("batch,hq,hkv,budget", [
     (1, 32, 8, 15), (1, 32, 8, 16), (1, 32, 8, 127), (1, 32, 8, 128),   # one tile a wave; splits and tiles that end at the new token
-    (2, 32, 8, 1030), (2, 16, 4, 2070), (1, 64, 8, 2064),               # two tiles (1024 waves or more)
-    (4, 32, 8, 1056), (8, 16, 4, 1100), (2, 64, 8, 2100)])              # four tiles
+    (2, 32, 8, 1030), (2, 16, 4, 2070), (1, 64, 8, 2064),
+    (4, 32, 8, 1056), (8, 16, 4, 1100), (2, 64, 8, 2100),               # two tiles (more than 1536 in all)
+    (4, 32, 8, 1535), (4, 32, 8, 1536), (2, 64, 8, 3100)])              # two and four (more than 3072)
 def test_tiles_per_scoring_wave(batch, hq, hkv, budget):
     _run(False, batch, hq, hkv, budget + 7, budget, n_recent=3 if budget > 16 else 0)
 
