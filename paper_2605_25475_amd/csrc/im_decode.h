@@ -672,10 +672,10 @@ template <int HPW, int DI>
 struct DecFinishSmem {
   float mrg[HPW][16][IM_D];   // numerators: the waves' shares of the splits
   float phe[IM_DM];                  // phi_e
-  float xl[HPW], xe[HPW];            // logits of the last live entry and of the evicted one
   float hrow[2][16][IM_D];           // head-shared layout: the evicted rows (K, V) of the set's heads,
   float bar[2][IM_D];                // and their sums over the heads
   bf16_t kn[16];                     // head-shared layout: the new token's indexer key
+  float xl[HPW], xe[HPW];            // logits of the last live entry and of the evicted one (behind what is read 16 bytes at a time)
   int e;                             // the evicted slot
 };
 
@@ -709,7 +709,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
   const int m_rows = (IM_DM + members - 1) / members, m0 = member * m_rows, m1 = min(IM_DM, m0 + m_rows);   // the workgroup's rows of M
   float* Mu = a.M + (size_t)su * IM_DM * IM_D;
   im_c4 Mr[4];
-  uint4 Wr[4];                               // waves 8 - 15: rows 16 (w - 8) + l16 of W_theta, dims 32 c + 8 kq ..
+  uint4 Wr[4];                               // waves 8 - 15: rows 16 (w - 8) + l16 of W_theta; wave 5: query head l16; dims 32 c + 8 kq ..
   float b_old;
   const float* qm = a.qm + (size_t)u * G * DEC_QM;
   // (no initial values, no arithmetic on what is loaded in a branch: either makes the wave wait at the branch's end)
@@ -717,14 +717,14 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
   bf16_t v_last, v_e;
   float2 dq;
   float m_all = -1e30f, l_all = 0.f;
-  uint32_t kl_w, q_w, ke_w;
-  constexpr int XW = HPW <= 4 ? 4 : 8;       // waves XW .. take the logits of single entries
+  uint32_t kl_w, q_w;
+  constexpr int XW = HPW <= 4 ? 4 : 8;       // waves XW .. take the last live entry's logits
   constexpr int PRE = HPW == 1 ? 2 : 1;   // splits per wave and head whose numerators are loaded ahead
   float2 ml[HPW], po[HPW][PRE];              // (lane = split); the wave's splits, dims 2 lane, 2 lane + 1
   constexpr int NMV = DI == 16 ? 8 : 1;
   dec_u4 mv[NMV], mvk;                       // wave 7: the last live entry's rows (they move into the hole)
   int mvpos;
-  const float* pu = a.part + (size_t)u * a.S * G * IM_D;
+  const float* pu = a.part + (size_t)u * a.S * G * IM_D;   // (offsets of 64 bits: a unit's partials exceed 2^31 floats from 2^28 entries on)
   const float2* mlu = a.part_ml + (size_t)u * a.S * G;
   auto merge_loads = [&]() {
 #pragma unroll
@@ -733,7 +733,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       ml[jj] = mlu[min(lane, a.S - 1) * G + j];
 #pragma unroll
       for (int k = 0; k < PRE; ++k)
-        if (w + 16 * k < n_act) po[jj][k] = *(const float2*)(pu + ((w + 16 * k) * G + j) * IM_D + 2 * lane);
+        if (w + 16 * k < n_act) po[jj][k] = *(const float2*)(pu + (size_t)((w + 16 * k) * G + j) * IM_D + 2 * lane);
     }
   };
   auto wave_loads = [&]() {   // what a wave has to do behind the decision
@@ -741,7 +741,11 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
 #pragma unroll
       for (int c = 0; c < 4; ++c) Wr[c] = *(const uint4*)(a.Wt + (16 * (w - 8) + l16) * IM_D + 32 * c + 8 * kq);
     }
-    if (w >= XW && w < XW + heads) {   // logits of single entries: a wave per head
+    if (w == 5) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) Wr[c] = *(const uint4*)(qg + min(l16, heads - 1) * IM_D + 32 * c + 8 * kq);
+    }
+    if (w >= XW && w < XW + heads) {   // the last live entry's logits: a wave per head
       kl_w = *(const uint32_t*)(Ku + (size_t)(n - 1) * IM_D + 2 * lane);
       q_w = *(const uint32_t*)(qg + (w - XW) * IM_D + 2 * lane);
     }
@@ -802,7 +806,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       for (int sp = w + 16 * PRE; sp < n_act; sp += 16) {
         const int at = sp * G + g * HPW + jj;
         const float sc = __expf(mlu[at].x - m);
-        const float2 v = *(const float2*)(pu + at * IM_D + 2 * lane);
+        const float2 v = *(const float2*)(pu + (size_t)at * IM_D + 2 * lane);
         o0 = fmaf(sc, v.x, o0);
         o1 = fmaf(sc, v.y, o1);
       }
@@ -863,20 +867,21 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
         }
       }
     } else {
-      if (w >= 8) {
+      if (w == 5 || w >= 8) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) ke[c] = *(const uint4*)(Ke + 32 * c + 8 * kq);
       }
       ve_w = *(const uint2*)(Ve + 4 * d4);
     }
     if (out_wave) v_e = Ve[d];
-    if (w >= XW && w < XW + heads) ke_w = *(const uint32_t*)(Ke + 2 * lane);
   }
   merge();
-  if (w >= XW && w < XW + heads) {
-    const float xe = e < 0 ? 0.f : wave_sum_f(fmaf(bf_lo(ke_w), bf_lo(q_w), bf_hi(ke_w) * bf_hi(q_w))) * a.scale;
-    if (lane == 0) sm.xe[w - XW] = xe;
-  }
+  // The evicted entry's logits by the product that its split has used, operands on the same sides: the same bits, so that what is
+  // subtracted below is what its partial holds, however large the logits are (another order of the 128 terms: off by up to 1e-4 at 300)
+  auto evicted_logits = [&]() {
+    const im_c4 z = att_logits(ke, Wr);
+    if (kq == 0 && l16 < heads) sm.xe[l16] = z[0] * a.scale;
+  };
   if (DI == 16 && e >= 0) {
     __syncthreads();
     if (tid < 2 * IM_D) {
@@ -884,8 +889,18 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       for (int i = 0; i < a.H_kv; ++i) t += sm.hrow[tid >> 7][i][d];
       sm.bar[tid >> 7][d] = t;
     }
+    if (w == 5) {   // (its row is in LDS by now: no registers for it meanwhile)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint4 lo = *(const uint4*)&sm.hrow[0][h][32 * c + 8 * kq], hi = *(const uint4*)&sm.hrow[0][h][32 * c + 8 * kq + 4];
+        ke[c] = make_uint4(__builtin_amdgcn_perm(lo.y, lo.x, 0x07060302u), __builtin_amdgcn_perm(lo.w, lo.z, 0x07060302u),
+                           __builtin_amdgcn_perm(hi.y, hi.x, 0x07060302u), __builtin_amdgcn_perm(hi.w, hi.z, 0x07060302u));
+      }
+      evicted_logits();
+    }
     __syncthreads();
   }
+  if (DI == 64 && w == 5 && e >= 0) evicted_logits();
   // ---- phi_e = W_theta k_e on the matrix cores (products exact, fp32 sums; a sum over heads in three exact bf16 parts):
   // waves 8 - 15 take 16 rows each, every column of the product is k_e
   if (e >= 0 && w >= 8) {
@@ -924,8 +939,13 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
     // the splits' maximum and denominator, the waves' shares, the last live entry, less the evicted one
     float m = m_all, l = l_all, o = 0.f;
     const int shares = min(n_act, 16);
+    float sizes = 0.f;   // of the shares
 #pragma unroll 4
-    for (int i = 0; i < shares; ++i) o += sm.mrg[jw][i][d];
+    for (int i = 0; i < shares; ++i) {
+      const float x = sm.mrg[jw][i][d];
+      o += x;
+      sizes += fabsf(x);
+    }
     const float xl = sm.xl[jw], ve_last = bf2f(v_last), ve_d = e >= 0 ? bf2f(v_e) : 0.f;
     auto add = [&](float m2, float l2, float o2) {
       const float mn = fmaxf(m, m2), s1 = __expf(m - mn), s2 = __expf(m2 - mn);
@@ -936,13 +956,18 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
     if (e != n - 1) {
       add(xl, 1.f, ve_last);
       if (e >= 0) {
-        // The evicted entry is in its split's partial.  Taking it out of the sums costs no precision where it is a small part of
-        // them; else (or with an infinity or NaN in sight) its split is taken again without it.
+        // The evicted entry is in its split's partial, and its share of the sums has their rounding errors.  They are subtracted
+        // where that leaves sums of the same order: at least half of the denominator, and in this dim no less than 1 / 16 (up to two splits:
+        // 1 / 64) of the evicted entry's part.  What stays is at least the sum of the sizes of the waves' shares without it.  Else (or with an
+        // infinity or NaN in sight) its split is taken again without it.  With one or two splits the sums are near zero by chance more often:
+        // of N(0, 1) values, half a head (a wave) of 100 entries is taken again in 2.1 % of the steps at 1 / 16, in 0.2 % at 1 / 64; of 256 entries in
+        // 0.05 % and none; of 512 and more in none.
         const float pe = __expf(sm.xe[jw] - m), pv = pe * ve_d, l0 = l;
+        const float to_m = __expf(m_all - m), share = sm.mrg[jw][(e / DEC_KEYS) & 15][d];
+        const float stays = fmaf(to_m, sizes - fabsf(share), fabsf(fmaf(to_m, share, -pv)) + fabsf(__expf(xl - m) * ve_last));
         l -= pe;
         o -= pv;
-        const float top = wave_max_f(fabsf(o));
-        if (__builtin_expect(__any(!(pe <= 0.99609375f * l0) || !(fabsf(pv) <= 256.f * top) || !(fabsf(pv) < 1e37f)), 0)) {
+        if (__builtin_expect(__any(!(pe <= 0.5f * l0) || !(fabsf(pv) <= (n_act > 2 ? 16.f : 64.f) * stays) || !(stays < 1e37f)), 0)) {
           // (the hole may be filled meanwhile: its row is not read)
           const int se = e / DEC_KEYS, k0 = se * DEC_KEYS, nk = min(DEC_KEYS, n - 1 - k0);
           float lg[2], p2[2];
@@ -987,7 +1012,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
             for (int i = 0; i < 8; ++i) {
               const int at = min(sp + i, n_act - 1) * G + j;
               r[i] = mlu[at];
-              ov[i] = pu[at * IM_D + d];
+              ov[i] = pu[(size_t)at * IM_D + d];
             }
 #pragma unroll
             for (int i = 0; i < 8; ++i)

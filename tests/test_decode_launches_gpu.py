@@ -84,3 +84,111 @@ def test_evicted_entry_leaves_the_attention_sums(what, n):
             assert np.array_equal(f64(st.K[b, h, :n]), ls.ref.K[b, h, :n])
             assert np.array_equal(st.pos[b, h, :n].cpu().numpy(), ls.ref.pos[b, h, :n])
             assert int(st.len[b, h]) == n
+
+
+def _without_the_evicted(shared, batch, hq, hkv, n, edit, tag, finite=None):
+    """A follower step that names a slot, against the oracle without that entry.  edit(ls, unit_q, slot) prepares K and V (and
+    returns the size of the largest logit).  The step leaves the entry's value out of the memory's readout (eta = 1e-24).
+
+    Bar: a logit is an fp32 sum of 128 products, of size L in all: 16 x 2^-24 L covers its rounding in any order (the bound of a random
+    walk of 128 roundings is 11), which moves a weight by as much, and the output by that and the other weights' times the largest |V|.
+    Then the output is rounded to bf16, by the oracle, too (2^-7 |o| is a whole step)."""
+    w = WORKLOADS["cfg1"].scaled(n_layers=1, batch=batch, n_q_heads=hq, n_kv_heads=hkv, context=n, budget=n, decode_steps=1)
+    ids = dict(batch_ids=[0, batch - 1]) if batch > 4 else {}
+    ls = LockStepShared(w.shared(), capacity=n + 1, **ids) if shared else LockStep(w, capacity=n + 1, **ids)
+    q = ls.Q[:, n].float().view(batch, hkv, w.group, w.head_dim)
+    slot = (2 * n) // 3
+    largest = edit(ls, q, slot)
+    ls.Q[:, n] = q.reshape(batch, hq, w.head_dim).to(torch.bfloat16)
+    d = lambda t: t.contiguous().to("cuda")
+    pos = torch.arange(n + 1, dtype=torch.int32).repeat(batch, 1)
+    named = torch.full((batch,) if shared else (batch, hkv), slot, dtype=torch.int32, device="cuda")
+    im.im_set_max_live(ls.handle, n + 1)
+    ids = ls.batch_ids
+    old, new = slice(0, n), slice(n, n + 1)
+    if shared:
+        im.im_append_kv_hidden(ls.handle, ls.params, ls.gpu.st, d(ls.K[:, :, old]), d(ls.V[:, :, old]), d(ls.X[:, old]), d(pos[:, old]))
+        for s in (old, new):
+            ls.ref.append_kv_hidden(f64(ls.K[ids][:, :, s]), f64(ls.V[ids][:, :, s]), f64(ls.X[ids][:, s]), pos[ids][:, s].numpy())
+        evict = [np.array([slot]) for _ in ids]
+        keep = [np.delete(np.arange(n + 1), slot) for _ in ids]
+    else:
+        im.im_append_kv(ls.handle, ls.gpu.st, d(ls.K[:, :, old]), d(ls.V[:, :, old]), d(pos[:, old]))
+        for s in (old, new):
+            ls.ref.append_kv(f64(ls.K[ids][:, :, s]), f64(ls.V[ids][:, :, s]), pos[ids][:, s].numpy())
+        evict = [[np.array([slot]) for _ in range(hkv)] for _ in ids]
+        keep = [[np.delete(np.arange(n + 1), slot) for _ in range(hkv)] for _ in ids]
+    x_new = dict(x_new=d(ls.X[:, new])) if shared else {}
+    ls.gpu.follow_step(d(ls.K[:, :, new]), d(ls.V[:, :, new]), d(pos[:, n]), d(ls.Q[:, n]), named, w.lam, 1e-24, debug=True, **x_new)
+    torch.cuda.synchronize()
+    assert im.im_query_status(ls.handle) == 0
+    with np.errstate(invalid="ignore"):
+        ls.ref.memory_update(evict, w.lam, 1e-24)
+        ls.ref.compact_kv(keep, evict)
+        out, _ = ls.ref.decode_attn_with_readout(f64(ls.Q[ids, n]))
+    got = f64(ls.gpu.out)[ids].reshape(len(ids), hkv, w.group, w.head_dim)
+    v = ls.ref.V[:, :, :n]
+    atol = 32 * 2.0 ** -24 * (1 + largest) * float(np.max(np.abs(v[np.isfinite(v) & (np.abs(v) < 100)])))
+    dims = np.ones(w.head_dim, bool) if finite is None else finite
+    assert_out_close(tag, got[..., dims], out[..., dims], atol=atol, rtol=2.0 ** -7)
+    st = ls.gpu.st
+    for ib, b in enumerate(ids):   # the cache itself: the last entry has moved into the hole
+        assert np.array_equal(f64(st.K[b, :, :n]), ls.ref.K[ib, :, :n])
+        assert np.array_equal(f64(st.V[b, :, :n]), ls.ref.V[ib, :, :n], equal_nan=True)
+    return got, out
+
+
+GROUPS = [(2, 32, 8), (16, 28, 4), (16, 64, 8), (40, 64, 8)]   # 1, 2, 4, 8 query heads per workgroup of the last launch
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("n,batch,hq,hkv", [(40, *GROUPS[0]), (300, *GROUPS[0]), (1500, *GROUPS[0])] + [(129, *g) for g in GROUPS[1:]])
+@pytest.mark.parametrize("size,share", [(10, 0.3), (10, 0.97), (40, 0.6), (40, 0.99), (300, 0.9), (300, 0.99), (300, 0.9999)])
+def test_evicted_entry_with_a_share_of_the_weight(shared, n, batch, hq, hkv, size, share):
+    """All logits near `size`, the evicted entry's so much larger that it has about `share` of every head's weight."""
+    def edit(ls, q, slot):
+        g = torch.Generator().manual_seed(5)
+        r = torch.randn(q.shape[0], q.shape[1], 128, generator=g)
+        a = {10: 1.0, 40: 2.0, 300: 4.0}[size]
+        unit = a * (r * r).sum(-1) * 128 ** -0.5          # the logit of a row r under the query a r
+        q[:] = a * (r[:, :, None] + 0.02 * torch.randn(q.shape, generator=g))
+        up = np.log((n - 1) * np.exp(0.5) * share / (1 - share))
+        K = (size / unit)[..., None, None] * r[:, :, None] + torch.randn(ls.K.shape, generator=g) / a
+        K[:, :, slot] = ((size + up) / unit)[..., None] * r
+        ls.K[:] = K.to(torch.bfloat16)
+        lg = torch.einsum("bhjd,bhkd->bhjk", q.to(torch.bfloat16).double(), ls.K.double()) * 128 ** -0.5
+        p = torch.softmax(lg, -1)[..., slot]
+        assert (abs(torch.log(p / (1 - p)) - np.log(share / (1 - share))) < 2.5).all()   # (the test is about this share)
+        return float(lg.abs().max())
+    _without_the_evicted(shared, batch, hq, hkv, n, edit, f"{share} of the weight at logits of {size}")
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("n,batch,hq,hkv", [(40, *GROUPS[0]), (300, *GROUPS[0]), (1500, *GROUPS[0])] + [(129, *g) for g in GROUPS[1:]])
+@pytest.mark.parametrize("large", [1e4, 1e6, 1e9])
+def test_evicted_entry_with_a_channel_of_its_own(shared, n, batch, hq, hkv, large):
+    """The evicted entry's value is large in one channel, a kept entry's as large in another one of the same half, at the same weight: what
+    is left of the first channel has nothing to do with the largest output."""
+    def edit(ls, q, slot):
+        ls.K[:, :, 3] = ls.K[:, :, slot]
+        ls.V[:, :, slot, 1] = large
+        ls.V[:, :, 3, 0] = large
+        return float((torch.einsum("bhjd,bhkd->bhjk", q, ls.K.float()) * 128 ** -0.5).abs().max())
+    _without_the_evicted(shared, batch, hq, hkv, n, edit, f"channel {large}")
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("n,batch,hq,hkv", [(300, *GROUPS[0]), (129, *GROUPS[2])])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan"), 3e37])
+def test_evicted_entry_that_is_not_finite(shared, n, batch, hq, hkv, bad):
+    """Not finite in two channels, which the memory then holds; and a kept entry's infinity stays one."""
+    def edit(ls, q, slot):
+        ls.V[:, :, slot, 5] = bad
+        ls.V[:, :, slot, 70] = -bad
+        ls.V[:, :, 7, 9] = float("inf")
+        return float((torch.einsum("bhjd,bhkd->bhjk", q, ls.K.float()) * 128 ** -0.5).abs().max())
+    dims = np.ones(128, bool)
+    dims[[5, 70] if bad != 3e37 else [], ] = False
+    dims[9] = False
+    got, _ = _without_the_evicted(shared, batch, hq, hkv, n, edit, f"value {bad}", finite=dims)
+    assert np.isposinf(got[..., 9]).all()
