@@ -540,12 +540,15 @@ struct DecScoreSmem {
 
 // A scoring workgroup (part `part` of a set's keys): 4 waves of T tiles of 16 keys.  Scores on the fp64 matrix cores, in their 4x4x4
 // form: four blocks of 4 heads x 4 keys x 4 dims an instruction (16 cycles), so that 8 heads waste no columns (4 tiles: 1.75 us, 2.2
-// in the 16x16x4 form, whose columns they half fill); HG groups of 4 heads.  The wave's entry ranked last by (score, then position,
+// in the 16x16x4 form, whose columns they half fill); HG groups of 4 heads, at most two at a time where a wave has several tiles: the kernel
+// also streams the cache, and with all of 4 groups (184 to 210 registers) half as many workgroups fit a CU: 4 x 2048 entries, 64 query heads 30.9 us a
+// layer-step with four at a time, 28.4 with two; 40 query heads 27.2, 24.8; 16 x 512, 40 heads 36.4, 34.2.  The wave's entry ranked last by (score, then position,
 // then slot), with sinks and the recent window forced to the top, goes to the workspace, and the scores to the caller, if wanted.
 // Bound by its chain (arguments, features, norm, products, rank): 7 us alone, hidden beside the split workgroups (10.8 us alone).
 template <int DI, int T, int HG>
 __device__ __forceinline__ void dec_score_block(const DecArgs& a, const int su, const int part, DecScoreSmem<DI>& sm) {
   constexpr int NH = DI == 64 ? 4 : 1, DPL = DI / 4;   // heads per wave (DI = 16: per row of 16 lanes); dims per lane of an operand
+  constexpr int GP = T == 1 ? HG : 2;                  // head groups per pass over the keys (which stay in registers)
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = DI == 16 || a.H_kv == 1 ? su : (int)__umulhi((unsigned)su, a.kv_magic);
@@ -596,45 +599,58 @@ __device__ __forceinline__ void dec_score_block(const DecArgs& a, const int su, 
   const int n_tiles = (n - key0 + 15) / 16;   // (of the wave that hold live keys; may be <= 0)
   float sc = 0.f;
   if (n_tiles > 0) {
-    // left operand of head group g: lane (i = l16 % 4, kq) supplies dims DPL kq .. of head 4 g + i, alike in the 4 blocks
-    float qf[HG][DPL];
-#pragma unroll
-    for (int g = 0; g < HG; ++g)
-#pragma unroll
-      for (int m = 0; m < DPL; m += 4) *(float4*)&qf[g][m] = *(const float4*)&sm.q[4 * g + (l16 & 3)][DPL * kq + m];
     if constexpr (DI == 16) {
 #pragma unroll
       for (int t = 0; t < T; ++t)
         if (key0 + 16 * t + l16 == n_old) *(uint2*)&kf[t][0] = *(const uint2*)(sm.kn + 4 * kq);
     }
-    double z[T][HG];
+    double sum[T];
 #pragma unroll
-    for (int t = 0; t < T; ++t)
+    for (int t = 0; t < T; ++t) sum[t] = 0.0;
+#pragma unroll 1
+    for (int g0 = 0; g0 < HG; g0 += GP) {   // GP head groups at a time
+      if constexpr (HG > GP) {   // (else the keys' conversions to fp64, 2 registers a value, move in front of the loop)
 #pragma unroll
-      for (int g = 0; g < HG; ++g) z[t][g] = 0.0;
-    auto tiles = [&](auto first, auto last) {   // tiles [first, last) together: independent chains of products
+        for (int t = 0; t < T; ++t)
 #pragma unroll
-      for (int m = 0; m < DPL; ++m) {
-#pragma unroll
-        for (int t = first; t < last; ++t) {
-          const uint4& u = kf[t][m >> 3];
-          const uint32_t wd = ((m >> 1) & 3) == 0 ? u.x : ((m >> 1) & 3) == 1 ? u.y : ((m >> 1) & 3) == 2 ? u.z : u.w;
-          const double k = (double)((m & 1) ? bf_hi(wd) : bf_lo(wd));
-#pragma unroll
-          for (int g = 0; g < HG; ++g) z[t][g] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)qf[g][m], k, z[t][g], 0, 0, 0);
-        }
+          for (int i = 0; i < DPL / 8; ++i) asm volatile("" : "+v"(kf[t][i].x), "+v"(kf[t][i].y), "+v"(kf[t][i].z), "+v"(kf[t][i].w));
       }
-    };
-    if (T == 1 || n_tiles == 1) tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
-    else tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, T>{});
-    // result: lane (l16, kq) holds head 4 g + kq, key l16
+      // left operand of head group g: lane (i = l16 % 4, kq) supplies dims DPL kq .. of head 4 g + i, alike in the 4 blocks
+      float qf[GP][DPL];
+#pragma unroll
+      for (int g = 0; g < GP; ++g)
+#pragma unroll
+        for (int m = 0; m < DPL; m += 4) *(float4*)&qf[g][m] = *(const float4*)&sm.q[4 * (g0 + g) + (l16 & 3)][DPL * kq + m];
+      double z[T][GP];
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int g = 0; g < GP; ++g) z[t][g] = 0.0;
+      auto tiles = [&](auto first, auto last) {   // tiles [first, last) together: independent chains of products
+#pragma unroll
+        for (int m = 0; m < DPL; ++m) {
+#pragma unroll
+          for (int t = first; t < last; ++t) {
+            const uint4& u = kf[t][m >> 3];
+            const uint32_t wd = ((m >> 1) & 3) == 0 ? u.x : ((m >> 1) & 3) == 1 ? u.y : ((m >> 1) & 3) == 2 ? u.z : u.w;
+            const double k = (double)((m & 1) ? bf_hi(wd) : bf_lo(wd));
+#pragma unroll
+            for (int g = 0; g < GP; ++g) z[t][g] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)qf[g][m], k, z[t][g], 0, 0, 0);
+          }
+        }
+      };
+      if (T == 1 || n_tiles == 1) tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+      else tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, T>{});
+      // result: lane (l16, kq) holds head 4 g + kq, key l16
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int g = 0; g < GP; ++g) sum[t] = fma((double)sm.al[4 * (g0 + g) + kq], fmax(z[t][g], 0.0), sum[t]);
+    }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      double sum = 0.0;
-#pragma unroll
-      for (int g = 0; g < HG; ++g) sum = fma((double)sm.al[4 * g + kq], fmax(z[t][g], 0.0), sum);
-      sum = rows_sum_d(sum);
-      sc = kq == t ? (float)sum : sc;
+      const double all = rows_sum_d(sum[t]);
+      sc = kq == t ? (float)all : sc;
     }
   }
   if (DI == 16 && own == n_old) p = newpos;
@@ -653,7 +669,7 @@ __device__ __forceinline__ void dec_score_block(const DecArgs& a, const int su, 
 
 // grid: sets * ceil(n_pick / 4) scoring workgroups, idle ones up to a multiple of 8 (n_score in all), then units * S split workgroups
 template <int DI, int T, int HG>
-__global__ __launch_bounds__(256, HG == 2 ? 4 : 2) void k_dec_score(DEC_HEAD, const int n_score, const int U, const DecArgs a) {
+__global__ __launch_bounds__(256, 4) void k_dec_score(DEC_HEAD, const int n_score, const int U, const DecArgs a) {
   __shared__ __attribute__((aligned(16))) union SM { DecSplitSmem sm; DecScoreSmem<DI> sc; __device__ SM() {} } s;
   if ((int)blockIdx.x >= n_score) {
     dec_split_block(a, DecHead{len, K, C, max_live, H_kv, kv_magic, H_set}, blockIdx.x - n_score, U, s.sm);
@@ -831,7 +847,13 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
         if ((int)x.z >= 0 && ((int)r.z < 0 || x.x < r.x || (x.x == r.x && x.y <= r.y))) r = x;
       };
       later(r2);
-      for (int i = lane + 128; i < a.n_pick; i += 64) later(pick[i]);
+      for (int i = lane + 128; i - lane < a.n_pick; i += 256) {   // (four at a time: a load that is waited for by itself is a round trip)
+        uint4 x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[k] = pick[min(i + 64 * k, a.n_pick - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) later(x[k]);
+      }
       const bool on = (int)r.z >= 0;
       const uint32_t khi = on ? r.x : 0xffffffffu, klo = on ? r.y : 0xffffffffu;
       const uint32_t mh = wave_min_u(khi);

@@ -249,9 +249,12 @@ template <int DI, int HG>
 void launch_score(const DecArgs& a, int tiles, hipStream_t s) {
   const int units = a.B * a.H_kv, sets = units / a.H_set, n_score = (sets * ((a.n_pick + 3) / 4) + 7) / 8 * 8;
   const int blocks = n_score + units * a.S;
-  if (tiles == 4) k_dec_score<DI, 4, HG><<<blocks, 256, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, n_score, units, a);
-  else if (tiles == 2) k_dec_score<DI, 2, HG><<<blocks, 256, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, n_score, units, a);
-  else k_dec_score<DI, 1, HG><<<blocks, 256, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, n_score, units, a);
+  auto launch = [&](auto kernel) { kernel<<<blocks, 256, 0, s>>>(a.len, a.K, a.C, a.max_live, a.H_kv, a.kv_magic, a.H_set, n_score, units, a); };
+  if constexpr (DI == IM_DI_SHARED || HG == 2) {
+    if (tiles == 4) return launch(k_dec_score<DI, 4, HG>);
+  }
+  if (tiles >= 2) launch(k_dec_score<DI, 2, HG>);
+  else launch(k_dec_score<DI, 1, HG>);
 }
 void launch_step(const DecArgs& a, int n_roles, int prep_rows, int tiles, hipEvent_t begin, hipEvent_t end, hipStream_t s) {
   const int units = a.B * a.H_kv;
@@ -884,9 +887,11 @@ static int32_t decode_launch(im_handle* h, const im_params* p, const im_state* s
   const int n_roles = ((1 + DEC_MP) * units + a.n_proj + 7) / 8 * 8;
   // 16-key tiles per wave of the scoring launch: a wave's fixed chain is paid once for its tiles, and few waves leave SIMDs without one.
   // Passes over 32 layer-steps with 1, 2, 4 tiles, us: 1312 tiles in all 550, 560, 555; 1824: 602, 588, 617; 2080: 603, 597, 610; 2056
-  // (8 sets): 640, 592, 598; 2112 (64 sets) 786, 783, 801; 4128: 830, 748, 725
+  // (8 sets): 640, 592, 598; 2112 (64 sets) 786, 783, 801; 4128: 830, 748, 725.  With more than 8 indexer heads a tile is twice the work, and
+  // there are 1 or 2; us per layer-step with 1, 2 (64 query heads): 520 tiles in all 19.4, 20.0; 1032: 21.8, 21.6; 1056: 21.5, 22.1; 1704: 23.9,
+  // 21.9; 2056: 25.2, 23.9; 4128: 31.4, 28.4; 8704: 112.8, 110.0
   const long long key_tiles = (long long)n_sets(c) * ((h->max_live + 15) / 16);
-  const int tiles = key_tiles > 3072 ? 4 : key_tiles > 1536 ? 2 : 1;
+  const int tiles = key_tiles > 3072 && (c.n_idx_heads <= 8 || c.head_shared) ? 4 : key_tiles > 1536 ? 2 : 1;
   a.n_pick = a.score ? (a.max_live + 16 * tiles - 1) / (16 * tiles) : 0;
   const bool prof = h->prof_ev && h->prof_n < h->prof_max;
   hipEvent_t ev0 = prof ? h->prof_ev[2 * h->prof_n] : nullptr, ev1 = prof ? h->prof_ev[2 * h->prof_n + 1] : nullptr;

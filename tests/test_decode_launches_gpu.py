@@ -35,7 +35,8 @@ def test_query_heads_per_workgroup(shared, batch, hq, hkv):
     (1, 32, 8, 15), (1, 32, 8, 16), (1, 32, 8, 127), (1, 32, 8, 128),   # one tile a wave; splits and tiles that end at the new token
     (2, 32, 8, 1030), (2, 16, 4, 2070), (1, 64, 8, 2064),
     (4, 32, 8, 1056), (8, 16, 4, 1100), (2, 64, 8, 2100),               # two tiles (more than 1536 in all)
-    (4, 32, 8, 1535), (4, 32, 8, 1536), (2, 64, 8, 3100)])              # two and four (more than 3072)
+    (4, 32, 8, 1535), (4, 32, 8, 1536),                                 # two and four (more than 3072)
+    (1, 40, 8, 3071), (1, 40, 8, 3072), (1, 36, 6, 4190), (2, 64, 8, 3100)])   # more than 8 indexer heads: one and two
 def test_tiles_per_scoring_wave(batch, hq, hkv, budget):
     _run(False, batch, hq, hkv, budget + 7, budget, n_recent=3 if budget > 16 else 0)
 
