@@ -29,6 +29,10 @@
 
 #define DEC_KEYS 128                 // keys per split workgroup (4 waves of 32)
 #define DEC_GMAX 8                   // query heads per KV head supported
+// The counters of k_dec_finish lie on cache lines of their own (in 32-bit words): arrivals at one line are taken one after another, also
+// at different counters.  256 workgroups, all counters on one or two lines / one a line, us per layer-step (an index-reuse
+// follower): head-shared 4 x 2048, 8 x 8 heads 18.6 / 17.3, 8 x 1024, 4 x 8 heads 17.7 / 16.6; per-unit 4 x 2048, 8 x 8 heads 17.1 / 16.5
+#define DEC_LINE 32
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -53,7 +57,7 @@ struct DecArgs {
   double *qy, *alpha;   // U_q q, G x
   double* xk;           // head-shared layout: U_k x of the new token, [B][16]
   int32_t *status, *maxpos;
-  int32_t* arrived;     // [sets] workgroups of k_dec_finish that are done with the cache
+  int32_t* arrived;     // [sets * DEC_LINE] workgroups of k_dec_finish that are done with the cache
   float* part;          // [units][S][G][128] numerators
   float2* part_ml;      // [units][S][G] maximum, denominator
   float* qm;            // per unit: the eviction-independent terms of the memory readout (DEC_QM floats per head)
@@ -293,7 +297,7 @@ __device__ __forceinline__ void dec_prep_unit(const DecArgs& a, const int u, Dec
     newrow = *(const uint4*)(((t < 16) ? a.k_new : a.v_new) + (size_t)u * IM_D + (t & 15) * 8);
   }
   const int newpos = a.pos_new[b];
-  if (lead && tid == 0) a.arrived[su] = 0;
+  if (lead && tid == 0) a.arrived[DEC_LINE * su] = 0;
   if (a.n_recent > 0 && a.score && lead) {  // newest position of the set (new token included) for the recent window
     int m = INT_MIN;
     const int nn = min(n_old, a.max_live);
@@ -954,7 +958,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's reads of the cache have returned ...
   __syncthreads();                                    // ... and those of the whole workgroup
   int arrived = 0;
-  if (w == 7 && lane == 0) arrived = __hip_atomic_fetch_add(a.arrived + su, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (w == 7 && lane == 0) arrived = __hip_atomic_fetch_add(a.arrived + DEC_LINE * su, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // ---- output of (head jw, dim d)
   if (out_wave) {
     const int j = g * HPW + jw;

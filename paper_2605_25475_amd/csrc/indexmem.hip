@@ -193,7 +193,7 @@ void layout(const im_config* c, im_handle* h) {
   h->off_dqm = take(step, units * G * DEC_QM * sizeof(float));
   h->off_xk = take(step, c->head_shared ? B * c->capacity * IM_DI_SHARED * sizeof(double) : 0);
   h->off_dpick = take(step, sets * ((c->capacity + 15) / 16) * sizeof(uint4));
-  h->off_darrived = take(step, sets * sizeof(int32_t));
+  h->off_darrived = take(step, DEC_LINE * sets * sizeof(int32_t));
   h->total = score;
   for (size_t end : {mem, attn, step}) h->total = end > h->total ? end : h->total;
 }
