@@ -692,9 +692,9 @@ template <int HPW, int DI>
 struct DecFinishSmem {
   float mrg[HPW][16][IM_D];   // numerators: the waves' shares of the splits
   float phe[IM_DM];                  // phi_e
-  float hrow[2][16][IM_D];           // head-shared layout: the evicted rows (K, V) of the set's heads,
-  float bar[2][IM_D];                // and their sums over the heads
-  bf16_t kn[16];                     // head-shared layout: the new token's indexer key
+  float vrow[DI == 16 ? 16 : 1][IM_D];                  // head-shared layout: the evicted entry's V rows of the set's heads
+  dec_u4 moved[DI == 16 ? 8 : 1][64];                   // head-shared layout: the last live entry's rows, pieces of 16 bytes
+  bf16_t kn[16];                                        // head-shared layout: the new token's indexer key
   float xl[HPW], xe[HPW];            // logits of the last live entry and of the evicted one (behind what is read 16 bytes at a time)
   int e;                             // the evicted slot
 };
@@ -742,7 +742,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
   constexpr int PRE = HPW == 1 ? 2 : 1;   // splits per wave and head whose numerators are loaded ahead
   float2 ml[HPW], po[HPW][PRE];              // (lane = split); the wave's splits, dims 2 lane, 2 lane + 1
   constexpr int NMV = DI == 16 ? 8 : 1;
-  dec_u4 mv[NMV], mvk;                       // wave 7: the last live entry's rows (they move into the hole)
+  dec_u4 mv, mvk;                            // wave 7: the last live entry's rows (they move into the hole; head-shared: in LDS)
   int mvpos;
   const float* pu = a.part + (size_t)u * a.S * G * IM_D;   // (offsets of 64 bits: a unit's partials exceed 2^31 floats from 2^28 entries on)
   const float2* mlu = a.part_ml + (size_t)u * a.S * G;
@@ -780,13 +780,16 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (32 * i < m_rows) Mr[i] = *(const im_c4*)(Mu + min(m0 + rg + 32 * i, IM_DM - 1) * IM_D + 4 * d4);   // (rows past m1: not used)
+      if (32 * i < m_rows) Mr[i] = *(const im_c4*)(Mu + min(m0 + rg + 32 * i, m1 - 1) * IM_D + 4 * d4);   // (rows past m1: not used)
     if (member == 0 && (w == 2 || w == 3)) b_old = a.bvec[(size_t)su * IM_DM + d];
     if (w == 7) {
 #pragma unroll
       for (int i = 0; i < NMV; ++i) {   // pieces of 16 bytes: head (lane >> 5) + 2 i, K then V
+        if (2 * i >= a.H_set) break;    // (uniform)
         const int hm = min((lane >> 5) + 2 * i, a.H_set - 1), pc = lane & 31;
-        mv[i] = *(const dec_u4*)(((pc < 16) ? a.K : a.V) + (((size_t)su * a.H_set + hm) * a.C + (n - 1)) * IM_D + (pc & 15) * 8);
+        const bf16_t* src = ((pc < 16) ? a.K : a.V) + (((size_t)su * a.H_set + hm) * a.C + (n - 1)) * IM_D + (pc & 15) * 8;
+        if constexpr (DI == 16) copy_to_lds_1k((const char*)src, (char*)sm.moved[i]);
+        else mv = *(const dec_u4*)src;
       }
       mvk = *(const dec_u4*)(a.Kidx + ((size_t)su * a.C + (n - 1)) * DI + min(lane, DI / 8 - 1) * 8);
       mvpos = a.pos[(size_t)su * a.C + (n - 1)];
@@ -883,20 +886,23 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
   if (e >= 0) {
     const bf16_t* Ke = Ku + (size_t)e * IM_D;
     const bf16_t* Ve = Vu + (size_t)e * IM_D;
-    if (DI == 16) {   // the memory takes the rows summed over the set's heads: waves 0 - 7 K, 8 - 15 V
+    if (w == 5 || w >= 8) {   // (the memory takes the rows summed over the set's heads: column l16 of the product below is head l16's)
+      const bf16_t* kr = DI == 64 || w == 5 ? Ke : a.K + (((size_t)su * a.H_kv + min(l16, a.H_kv - 1)) * a.C + e) * IM_D;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int hm = (w & 7) + 8 * i;
-        if (hm < a.H_kv) {
-          const uint32_t x = *(const uint32_t*)(((w < 8) ? a.K : a.V) + (((size_t)su * a.H_kv + hm) * a.C + e) * IM_D + 2 * lane);
-          *(float2*)&sm.hrow[w >> 3][hm][2 * lane] = make_float2(bf_lo(x), bf_hi(x));
+      for (int c = 0; c < 4; ++c) ke[c] = *(const uint4*)(kr + 32 * c + 8 * kq);
+    }
+    if (DI == 16) {
+      if (w < 8) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int hm = w + 8 * i;
+          if (hm < a.H_kv) {
+            const uint32_t x = *(const uint32_t*)(a.V + (((size_t)su * a.H_kv + hm) * a.C + e) * IM_D + 2 * lane);
+            *(float2*)&sm.vrow[hm][2 * lane] = make_float2(bf_lo(x), bf_hi(x));
+          }
         }
       }
     } else {
-      if (w == 5 || w >= 8) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) ke[c] = *(const uint4*)(Ke + 32 * c + 8 * kq);
-      }
       ve_w = *(const uint2*)(Ve + 4 * d4);
     }
     if (out_wave) v_e = Ve[d];
@@ -904,54 +910,23 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
   merge();
   // The evicted entry's logits by the product that its split has used, operands on the same sides: the same bits, so that what is
   // subtracted below is what its partial holds, however large the logits are (another order of the 128 terms: off by up to 1e-4 at 300)
-  auto evicted_logits = [&]() {
+  if (w == 5 && e >= 0) {
     const im_c4 z = att_logits(ke, Wr);
     if (kq == 0 && l16 < heads) sm.xe[l16] = z[0] * a.scale;
-  };
-  if (DI == 16 && e >= 0) {
-    __syncthreads();
-    if (tid < 2 * IM_D) {
-      float t = 0.f;
-      for (int i = 0; i < a.H_kv; ++i) t += sm.hrow[tid >> 7][i][d];
-      sm.bar[tid >> 7][d] = t;
-    }
-    if (w == 5) {   // (its row is in LDS by now: no registers for it meanwhile)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const uint4 lo = *(const uint4*)&sm.hrow[0][h][32 * c + 8 * kq], hi = *(const uint4*)&sm.hrow[0][h][32 * c + 8 * kq + 4];
-        ke[c] = make_uint4(__builtin_amdgcn_perm(lo.y, lo.x, 0x07060302u), __builtin_amdgcn_perm(lo.w, lo.z, 0x07060302u),
-                           __builtin_amdgcn_perm(hi.y, hi.x, 0x07060302u), __builtin_amdgcn_perm(hi.w, hi.z, 0x07060302u));
-      }
-      evicted_logits();
-    }
-    __syncthreads();
   }
-  if (DI == 64 && w == 5 && e >= 0) evicted_logits();
-  // ---- phi_e = W_theta k_e on the matrix cores (products exact, fp32 sums; a sum over heads in three exact bf16 parts):
-  // waves 8 - 15 take 16 rows each, every column of the product is k_e
+  // ---- phi_e = W_theta k_e on the matrix cores: waves 8 - 15 take 16 rows each.  Every column of the product is k_e; head-shared
+  // layout: column l16 is head l16's key, and the columns are added.  Products are exact, and the four parts of a sum are added as a tree:
+  // a chain through the accumulator has 6.0e-8 of the sum as its error, the tree 4.8e-8, 128 terms on the vector ALU 5.1e-8.
   if (e >= 0 && w >= 8) {
-    im_c4 z = {0.f, 0.f, 0.f, 0.f};
+    im_c4 part[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      part[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(im_bf8, Wr[c]), __builtin_bit_cast(im_bf8, ke[c]),
+                                                       im_c4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    im_c4 z = (part[0] + part[1]) + (part[2] + part[3]);
     if constexpr (DI == 16) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        float x[8];
-        *(float4*)&x[0] = *(const float4*)&sm.bar[0][32 * c + 8 * kq];
-        *(float4*)&x[4] = *(const float4*)&sm.bar[0][32 * c + 8 * kq + 4];
-#pragma unroll
-        for (int s = 0; s < 3; ++s) {
-          uint32_t wd[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            wd[i] = __builtin_amdgcn_perm(__float_as_uint(x[2 * i + 1]), __float_as_uint(x[2 * i]), 0x07060302u);
-            x[2 * i] -= bf_lo(wd[i]);
-            x[2 * i + 1] -= bf_hi(wd[i]);
-          }
-          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(im_bf8, Wr[c]),
-                                                      __builtin_bit_cast(im_bf8, make_uint4(wd[0], wd[1], wd[2], wd[3])), z, 0, 0, 0);
-        }
-      }
-    } else {
-      z = att_logits(Wr, ke);
+      for (int r = 0; r < 4; ++r) z[r] = row16_sum_f(l16 < a.H_kv ? z[r] : 0.f);
     }
     if (l16 == 0) *(float4*)&sm.phe[16 * (w - 8) + 4 * kq] = make_float4(z[0], z[1], z[2], z[3]);
   }
@@ -965,6 +940,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
     // the splits' maximum and denominator, the waves' shares, the last live entry, less the evicted one
     float m = m_all, l = l_all, o = 0.f;
     const int shares = min(n_act, 16);
+    const float xl = sm.xl[jw], xe = sm.xe[jw], share_e = sm.mrg[jw][(max(e, 0) / DEC_KEYS) & 15][d];   // (on their way beside the shares)
     float sizes = 0.f;   // of the shares
 #pragma unroll 4
     for (int i = 0; i < shares; ++i) {
@@ -972,7 +948,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       o += x;
       sizes += fabsf(x);
     }
-    const float xl = sm.xl[jw], ve_last = bf2f(v_last), ve_d = e >= 0 ? bf2f(v_e) : 0.f;
+    const float ve_last = bf2f(v_last), ve_d = e >= 0 ? bf2f(v_e) : 0.f;
     auto add = [&](float m2, float l2, float o2) {
       const float mn = fmaxf(m, m2), s1 = __expf(m - mn), s2 = __expf(m2 - mn);
       o = fmaf(o, s1, s2 * o2);
@@ -988,9 +964,9 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
         // infinity or NaN in sight) its split is taken again without it.  With one or two splits the sums are near zero by chance more often:
         // of N(0, 1) values, half a head (a wave) of 100 entries is taken again in 2.1 % of the steps at 1 / 16, in 0.2 % at 1 / 64; of 256 entries in
         // 0.05 % and none; of 512 and more in none.
-        const float pe = __expf(sm.xe[jw] - m), pv = pe * ve_d, l0 = l;
-        const float to_m = __expf(m_all - m), share = sm.mrg[jw][(e / DEC_KEYS) & 15][d];
-        const float stays = fmaf(to_m, sizes - fabsf(share), fabsf(fmaf(to_m, share, -pv)) + fabsf(__expf(xl - m) * ve_last));
+        const float pe = __expf(xe - m), pv = pe * ve_d, l0 = l;
+        const float to_m = __expf(m_all - m);
+        const float stays = fmaf(to_m, sizes - fabsf(share_e), fabsf(fmaf(to_m, share_e, -pv)) + fabsf(__expf(xl - m) * ve_last));
         l -= pe;
         o -= pv;
         if (__builtin_expect(__any(!(pe <= 0.5f * l0) || !(fabsf(pv) <= (n_act > 2 ? 16.f : 64.f) * stays) || !(stays < 1e37f)), 0)) {
@@ -1058,7 +1034,12 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       const float dt = wave_sum_f(fmaf(dq.x, pp.x, dq.y * pp.y));
       const float sq = wave_sum_f(fmaf(dq.x * dq.x, pp.x * pp.x, dq.y * dq.y * pp.y * pp.y));
       dn = fmaf(a.lambda, dn, a.eta * sq);
-      mr = fmaf(a.lambda, mr, a.eta * dt * (DI == 16 ? sm.bar[1][d] : ve_d));
+      float v_sum = ve_d;
+      if constexpr (DI == 16) {
+        v_sum = 0.f;
+        for (int i = 0; i < a.H_kv; ++i) v_sum += sm.vrow[i][d];
+      }
+      mr = fmaf(a.lambda, mr, a.eta * dt * v_sum);
     }
     const float res = gate * (mr / (dn + a.mem_eps));
     const size_t oi = ((size_t)b * a.H + h * G + j) * IM_D + d;
@@ -1067,7 +1048,18 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
   }
   if (e >= 0) {
     // M <- lambda M + eta phi_e v_e^T for this thread's rows, 4 columns each; b <- lambda b + eta phi_e^2
-    const float4 ve4 = DI == 16 ? *(const float4*)&sm.bar[1][4 * d4] : make_float4(bf_lo(ve_w.x), bf_hi(ve_w.x), bf_lo(ve_w.y), bf_hi(ve_w.y));
+    float4 ve4;
+    if constexpr (DI == 16) {
+      ve4 = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (m0 + rg < m1) {
+        for (int i = 0; i < a.H_kv; ++i) {
+          const float4 v = *(const float4*)&sm.vrow[i][4 * d4];
+          ve4.x += v.x; ve4.y += v.y; ve4.z += v.z; ve4.w += v.w;
+        }
+      }
+    } else {
+      ve4 = make_float4(bf_lo(ve_w.x), bf_hi(ve_w.x), bf_lo(ve_w.y), bf_hi(ve_w.y));
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = m0 + rg + 32 * i;
@@ -1093,7 +1085,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
     for (int i = 0; i < NMV; ++i) {
       const int hm = (lane >> 5) + 2 * i, pc = lane & 31;
       if (hm < a.H_set)
-        *(dec_u4*)(((pc < 16) ? a.K : a.V) + (((size_t)su * a.H_set + hm) * a.C + e) * IM_D + (pc & 15) * 8) = mv[i];
+        *(dec_u4*)(((pc < 16) ? a.K : a.V) + (((size_t)su * a.H_set + hm) * a.C + e) * IM_D + (pc & 15) * 8) = DI == 16 ? sm.moved[i][lane] : mv;
     }
     if (lane < DI / 8 && !new_key) *(dec_u4*)(a.Kidx + ((size_t)su * a.C + e) * DI + lane * 8) = mvk;
     if (lane == 0) a.pos[(size_t)su * a.C + e] = mvpos;

@@ -193,3 +193,39 @@ def test_evicted_entry_that_is_not_finite(shared, n, batch, hq, hkv, bad):
     dims[9] = False
     got, _ = _without_the_evicted(shared, batch, hq, hkv, n, edit, f"value {bad}", finite=dims)
     assert np.isposinf(got[..., 9]).all()
+
+
+@pytest.mark.parametrize("shared", [False, True])
+def test_memory_state_keeps_its_digits(shared):
+    """Twelve evictions one after another into an empty memory, against fp64, root mean square over the state.  A phi is a sum of 128 exact
+    products in four parts (4.8e-8 of its size; head-shared: of each head's, then 8 are added), and every step rounds phi v, or phi^2, and
+    the sum once (2^-24 / sqrt(3) = 3.4e-8 each, of a state that grows to its last size as sqrt(t)): 8e-8 for b, which sums squares, and 9e-8
+    for M (head-shared, with the eight roundings of the sum over the heads: 10e-8).  Bars: a sixth more."""
+    n, steps = 40, 12
+    w = WORKLOADS["cfg1"].scaled(n_layers=1, batch=8, n_q_heads=32, n_kv_heads=8, context=n + steps, budget=n, decode_steps=1)
+    ls = LockStepShared(w.shared(), capacity=n + 1) if shared else LockStep(w, capacity=n + 1)
+    d = lambda t: t.contiguous().to("cuda")
+    pos = torch.arange(n + steps, dtype=torch.int32).repeat(w.batch, 1)
+    old = slice(0, n)
+    if shared:
+        im.im_append_kv_hidden(ls.handle, ls.params, ls.gpu.st, d(ls.K[:, :, old]), d(ls.V[:, :, old]), d(ls.X[:, old]), d(pos[:, old]))
+    else:
+        im.im_append_kv(ls.handle, ls.gpu.st, d(ls.K[:, :, old]), d(ls.V[:, :, old]), d(pos[:, old]))
+    im.im_set_max_live(ls.handle, n + 1)
+    W = f64(ls.params.Wtheta)
+    M = b = 0.0
+    for t in range(n, n + steps):
+        e = (7 * t) % n
+        ke, ve = f64(ls.gpu.st.K[:, :, e]), f64(ls.gpu.st.V[:, :, e])
+        ke, ve = (ke.sum(1), ve.sum(1)) if shared else (ke, ve)
+        named = torch.full((w.batch,) if shared else (w.batch, w.n_kv_heads), e, dtype=torch.int32, device="cuda")
+        ls.gpu.follow_step(d(ls.K[:, :, t:t + 1]), d(ls.V[:, :, t:t + 1]), d(pos[:, t]), d(ls.Q[:, t]), named, w.lam, w.eta,
+                           **(dict(x_new=d(ls.X[:, t:t + 1])) if shared else {}))
+        phi = ke @ W.T
+        M = w.lam * M + w.eta * phi[..., :, None] * ve[..., None, :]
+        b = w.lam * b + w.eta * phi * phi
+    torch.cuda.synchronize()
+    assert im.im_query_status(ls.handle) == 0
+    off = lambda got, want: float(np.linalg.norm(f64(got) - want) / np.linalg.norm(want))
+    err = off(ls.gpu.st.M, M), off(ls.gpu.st.b, b)
+    assert err[0] <= (11.5e-8 if shared else 10.5e-8) and err[1] <= 9.3e-8, err
