@@ -228,8 +228,10 @@ int n_sets(const im_config& c) { return c.batch * c.n_kv_heads / heads_per_set(c
   do { if (!(cond)) return set_err(h, IM_ERR_INVALID_ARG, "%s: %s", __func__, msg); } while (0)
 
 // The last launch of a fused step: a workgroup of 16 waves fills a CU, so it takes the fewest query heads with which the
-// launch fits the chip once.  Passes over 32 layer-steps with 1, 2, 4 heads, us: 32 units of 4 heads 724, 744, 804; 64 of 4 589, 585,
-// 654; 64 of 7 893, 793, 829.
+// launch fits the chip once, or all of the unit's.  us per layer-step with 1, 2, 4, 8 heads, per unit: 32 units of 4 heads 21.4, 22.1, 23.9, 24.5; 64 of
+// 4 23.0, 23.7, 25.6, 26.1; 64 of 7 24.9, 22.3, 23.4, 25.5; 64 of 8 35.7, 33.1, 34.6, 36.8; 128 of 8 50.7, 44.8, 43.0, 44.7; 320 of 8 88.5, 74.9, 71.7, 71.4; 512
+// of 8 147, 124, 116, 111; 512 of 4 79, 70, 66, 67.  Head-shared: 32 of 8 23.2, 23.4, 25.4, 28.3; 64 of 8 28.5, 24.8, 26.5, 28.2; 128 of 8 41.1, 33.8, 30.8, 32.4;
+// 320 of 8 71.6, 54.0, 48.4, 45.4; 512 of 4 81.6, 66.2, 60.5, 61.7; 512 of 8 116, 87, 75, 66.
 template <int HPW, int DI>
 void launch_finish_as(const DecArgs& a, hipStream_t s) {
   const int units = a.B * a.H_kv, x = units % 8 == 0 ? 8 : 1;
@@ -253,8 +255,10 @@ void launch_score(const DecArgs& a, int tiles, hipStream_t s) {
   if constexpr (DI == IM_DI_SHARED || HG == 2) {
     if (tiles == 4) return launch(k_dec_score<DI, 4, HG>);
   }
-  if (tiles >= 2) launch(k_dec_score<DI, 2, HG>);
-  else launch(k_dec_score<DI, 1, HG>);
+  if constexpr (DI == IM_DI) {
+    if (tiles == 1) return launch(k_dec_score<DI, 1, HG>);
+  }
+  launch(k_dec_score<DI, 2, HG>);
 }
 void launch_step(const DecArgs& a, int n_roles, int prep_rows, int tiles, hipEvent_t begin, hipEvent_t end, hipStream_t s) {
   const int units = a.B * a.H_kv;
@@ -889,9 +893,13 @@ static int32_t decode_launch(im_handle* h, const im_params* p, const im_state* s
   // Passes over 32 layer-steps with 1, 2, 4 tiles, us: 1312 tiles in all 550, 560, 555; 1824: 602, 588, 617; 2080: 603, 597, 610; 2056
   // (8 sets): 640, 592, 598; 2112 (64 sets) 786, 783, 801; 4128: 830, 748, 725.  With more than 8 indexer heads a tile is twice the work, and
   // there are 1 or 2; us per layer-step with 1, 2 (64 query heads): 520 tiles in all 19.4, 20.0; 1032: 21.8, 21.6; 1056: 21.5, 22.1; 1704: 23.9,
-  // 21.9; 2056: 25.2, 23.9; 4128: 31.4, 28.4; 8704: 112.8, 110.0
+  // 21.9; 2056: 25.2, 23.9; 4128: 31.4, 28.4; 8704: 112.8, 110.0.  Head-shared, where a tile is a quarter of the work, 2 or 4; us per layer-step
+  // with 1, 2, 4: 129 tiles in all 15.4, 15.0, 15.0; 516: 20.3, 20.2, 20.4; 903: 27.5, 25.5, 25.6; 1040: 32.0, 30.6, 30.7; 1560: 39.7, 40.1, 40.3; 2080: 48.6,
+  // 48.1, 48.2; 4160: 86.5, 85.1, 84.5; 64 query heads, 1040: 39.2, 37.9, 37.8
   const long long key_tiles = (long long)n_sets(c) * ((h->max_live + 15) / 16);
-  const int tiles = key_tiles > 3072 && (c.n_idx_heads <= 8 || c.head_shared) ? 4 : key_tiles > 1536 ? 2 : 1;
+  int tiles = key_tiles > 3072 ? 4 : key_tiles > 1536 ? 2 : 1;
+  if (c.head_shared) tiles = max(tiles, 2);
+  else if (c.n_idx_heads > 8) tiles = min(tiles, 2);
   a.n_pick = a.score ? (a.max_live + 16 * tiles - 1) / (16 * tiles) : 0;
   const bool prof = h->prof_ev && h->prof_n < h->prof_max;
   hipEvent_t ev0 = prof ? h->prof_ev[2 * h->prof_n] : nullptr, ev1 = prof ? h->prof_ev[2 * h->prof_n + 1] : nullptr;

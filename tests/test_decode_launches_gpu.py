@@ -46,6 +46,13 @@ def test_tiles_per_scoring_wave_head_shared(budget):
     _run(True, 2, 32, 8, budget + 5, budget)
 
 
+@pytest.mark.parametrize("batch,hq,hkv,budget", [
+    (2, 32, 8, 15), (2, 32, 8, 31), (2, 32, 8, 32), (2, 64, 8, 2048),   # two tiles a wave: the new token first and last of a wave's keys
+    (64, 32, 8, 783), (64, 32, 8, 784), (64, 64, 8, 784)])              # four (more than 3072 in all), the new token last and first of a tile
+def test_new_token_in_a_scoring_wave_head_shared(batch, hq, hkv, budget):
+    _run(True, batch, hq, hkv, budget + 5, budget, n_recent=3 if budget > 16 else 0)
+
+
 @pytest.mark.parametrize("what", ["plain", "all-the-weight", "large-value", "last-entry"])
 @pytest.mark.parametrize("n", [40, 129, 300])
 def test_evicted_entry_leaves_the_attention_sums(what, n):
