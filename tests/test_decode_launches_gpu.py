@@ -53,6 +53,30 @@ def test_new_token_in_a_scoring_wave_head_shared(batch, hq, hkv, budget):
     _run(True, batch, hq, hkv, budget + 5, budget, n_recent=3 if budget > 16 else 0)
 
 
+@pytest.mark.parametrize("hq,hkv,n", [(16, 2, 8193), (8, 1, 9000)])
+def test_more_than_64_splits(hq, hkv, n):
+    """Decode steps and one step that only attends, with more splits than a wave has lanes (and more last-ranked entries than it looks at first)."""
+    steps = 3
+    w = WORKLOADS["cfg1"].scaled(n_layers=1, batch=1, n_q_heads=hq, n_kv_heads=hkv, context=n, budget=n, decode_steps=steps)
+    ls = LockStep(w, capacity=n + 1, max_queries=4)
+    d = lambda t: t.contiguous().to("cuda")
+    pos = torch.arange(n + steps, dtype=torch.int32).view(1, -1)
+    k, v, q, win, last = ls.K[:, :, :n], ls.V[:, :, :n], ls.Q[:, n - 4:n], slice(n - 4, n), ls.Q[:, n - 1]
+    ls.gpu.step(d(k), d(v), d(pos[:, :n]), d(q), d(q).view(1, 4, -1), d(pos[:, win]), d(last), n, w.lam, w.eta)
+    ls.ref.step(f64(k), f64(v), pos[:, :n].numpy(), f64(q), f64(q).reshape(1, 4, -1), pos[:, win].numpy(), f64(last), n, w.lam, w.eta)
+    im.im_set_max_live(ls.handle, n + 1)
+    for t in range(n, n + steps - 1):
+        ls.event_fused(t, n, f"decode@{t}")
+    t = n + steps - 1
+    new = [ls.K[:, :, t:t + 1], ls.V[:, :, t:t + 1], pos[:, t:t + 1]]
+    ls.gpu.attend_step(*(d(x) for x in new), d(ls.Q[:, t]))
+    ls.ref.append_kv(f64(new[0]), f64(new[1]), new[2].numpy())
+    out, res = ls.ref.decode_attn_with_readout(f64(ls.Q[:, t]))
+    torch.cuda.synchronize()
+    ls.compare(None, None, None, out, res, f"attend@{t}", lists=False)
+    assert im.im_query_status(ls.handle) == 0
+
+
 @pytest.mark.parametrize("what", ["plain", "all-the-weight", "large-value", "last-entry"])
 @pytest.mark.parametrize("n", [40, 129, 300])
 def test_evicted_entry_leaves_the_attention_sums(what, n):
