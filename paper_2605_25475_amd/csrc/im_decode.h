@@ -739,6 +739,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
   float m_all = -1e30f, l_all = 0.f;
   uint32_t kl_w, q_w;
   constexpr int XW = HPW <= 4 ? 4 : 8;       // waves XW .. take the last live entry's logits
+  constexpr int RT = 3;                      // tiles of 16 keys in flight where a split is taken again (4: scratch)
   constexpr int PRE = HPW == 1 ? 2 : 1;   // splits per wave and head whose numerators are loaded ahead
   float2 ml[HPW], po[HPW][PRE];              // (lane = split); the wave's splits, dims 2 lane, 2 lane + 1
   constexpr int NMV = DI == 16 ? 8 : 1;
@@ -959,52 +960,81 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       add(xl, 1.f, ve_last);
       if (e >= 0) {
         // The evicted entry is in its split's partial, and its share of the sums has their rounding errors.  They are subtracted
-        // where that leaves sums of the same order: at least half of the denominator, and in this dim no less than 1 / 16 (up to two splits:
-        // 1 / 64) of the evicted entry's part.  What stays is at least the sum of the sizes of the waves' shares without it.  Else (or with an
-        // infinity or NaN in sight) its split is taken again without it.  With one or two splits the sums are near zero by chance more often:
-        // of N(0, 1) values, half a head (a wave) of 100 entries is taken again in 2.1 % of the steps at 1 / 16, in 0.2 % at 1 / 64; of 256 entries in
-        // 0.05 % and none; of 512 and more in none.
+        // where that leaves enough of the sums: 1 / 16 of the denominator (the errors count 16 times: 1e-6 of the output, whose half step is 2e-3),
+        // and in this dim 1 / 256 of the evicted entry's part (by chance or design a dim may have next to nothing else: 2e-5 of it).  What stays
+        // is at least the sum of the sizes of the waves' shares without it.  Else (or with an infinity or NaN in sight) its split is taken again
+        // without it, which costs the launch 5 us (13 with a row a lane): with lines of 1 / 2 and 1 / 16 that is every launch where a few keys
+        // dominate (16 x 512 entries, one key in 20 four times as long: 891 us a pass, 776 now).
         const float pe = __expf(xe - m), pv = pe * ve_d, l0 = l;
         const float to_m = __expf(m_all - m);
         const float stays = fmaf(to_m, sizes - fabsf(share_e), fabsf(fmaf(to_m, share_e, -pv)) + fabsf(__expf(xl - m) * ve_last));
         l -= pe;
         o -= pv;
-        if (__builtin_expect(__any(!(pe <= 0.5f * l0) || !(fabsf(pv) <= (n_act > 2 ? 16.f : 64.f) * stays) || !(stays < 1e37f)), 0)) {
-          // (the hole may be filled meanwhile: its row is not read)
+        if (__builtin_expect(__any(!(pe <= 0.9375f * l0) || !(fabsf(pv) <= 256.f * stays) || !(stays < 1e37f)), 0)) {
+          // (the hole may be filled meanwhile: its row is not read).  The wave's shares have been read; its half of their rows is scratch now
           const int se = e / DEC_KEYS, k0 = se * DEC_KEYS, nk = min(DEC_KEYS, n - 1 - k0);
+          float (*tmp)[IM_D] = (float (*)[IM_D])&sm.mrg[jw][0][64 * (w & 1)];   // [16][64], rows IM_D apart
+          auto in = [&](int key) { return key < nk && k0 + key != e; };
+          auto row = [&](int key) { return in(key) ? k0 + key : n - 1; };   // (others: the last live entry's, not added)
+          {
+            uint4 qf[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) qf[c] = *(const uint4*)(qg + jw * IM_D + 32 * c + 8 * kq);
+#pragma unroll 1
+            for (int t0 = 0; 16 * t0 < nk; t0 += RT) {   // (every load of RT tiles, then the products; all columns are the head)
+              uint4 kf[RT][4];
+#pragma unroll
+              for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) kf[t][c] = *(const uint4*)(Ku + (size_t)row(16 * (t0 + t) + l16) * IM_D + 32 * c + 8 * kq);
+#pragma unroll
+              for (int t = 0; t < RT; ++t) {
+                const im_c4 z = att_logits(kf[t], qf);
+                const int key = 16 * (t0 + t) + 4 * kq;
+                if (l16 == 0) *(float4*)&tmp[key >> 6][key & 63] = make_float4(z[0], z[1], z[2], z[3]);
+              }
+            }
+          }
           float lg[2], p2[2];
 #pragma unroll
           for (int x = 0; x < 2; ++x) {   // lane: keys lane, lane + 64
             const int key = lane + 64 * x;
-            const bool in = key < nk && k0 + key != e;
-            const bf16_t* kr = Ku + (size_t)(in ? k0 + key : n - 1) * IM_D;
-            float s = 0.f;
-#pragma unroll 4
-            for (int c = 0; c < IM_D; c += 8) {
-              float kv[8], qv[8];
-              unpack8(*(const uint4*)(kr + c), kv);
-              unpack8(*(const uint4*)(qg + jw * IM_D + c), qv);
-#pragma unroll
-              for (int i = 0; i < 8; ++i) s = fmaf(kv[i], qv[i], s);
-            }
-            lg[x] = in ? s * a.scale : -INFINITY;
+            lg[x] = in(key) ? tmp[x][lane] * a.scale : -INFINITY;
           }
           m = fmaxf(wave_max_f(fmaxf(lg[0], lg[1])), -1e30f);
-          p2[0] = __expf(lg[0] - m);
-          p2[1] = __expf(lg[1] - m);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            p2[x] = __expf(lg[x] - m);
+            tmp[x][lane] = p2[x];
+          }
           l = wave_sum_f(p2[0] + p2[1]);
-          o = 0.f;
-          // (rows past the split, and the hole: the last live entry's, not added)
+          {
+            const int rw = lane >> 3, dc = 8 * (lane & 7);   // 8 rows of 64 dims a load
+            float acc[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] = 0.f;
 #pragma unroll 1
-          for (int k = 0; k < nk; k += 16) {
-            bf16_t vr[16];
+            for (int k = 0; k < nk; k += 64) {
+              uint4 vr[8];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) vr[i] = Vu[(size_t)(k + i < nk && k0 + k + i != e ? k0 + k + i : n - 1) * IM_D + d];
+              for (int i = 0; i < 8; ++i) vr[i] = *(const uint4*)(Vu + (size_t)row(k + 8 * i + rw) * IM_D + 64 * (w & 1) + dc);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              const float pr = readlane_f(k < 64 ? p2[0] : p2[1], (k + i) & 63);
-              if (k + i < nk && k0 + k + i != e) o = fmaf(pr, bf2f(vr[i]), o);
+              for (int i = 0; i < 8; ++i) {
+                const int key = k + 8 * i + rw;
+                const float pr = tmp[key >> 6][key & 63];
+                float v[8];
+                unpack8(vr[i], v);
+                if (in(key)) {
+#pragma unroll
+                  for (int c = 0; c < 8; ++c) acc[c] = fmaf(pr, v[c], acc[c]);
+                }
+              }
             }
+            *(float4*)&tmp[2 + rw][dc] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+            *(float4*)&tmp[2 + rw][dc + 4] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+            o = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o += tmp[2 + i][lane];
           }
 #pragma unroll 1
           for (int sp = 0; sp < n_act; sp += 8) {
