@@ -18,8 +18,8 @@
 // Split and scoring workgroups are different ones, so the decision is not known to a partial: it holds all of its keys, and
 // k_dec_finish takes the evicted one out again.  With the roles as waves of one workgroup that met at a barrier, every split left its
 // last-ranked entry out and wrote it to a record, and the last launch staged all records: 23.9 us a layer-step of 4 x 2048 entries x
-// 8 heads, 22.6 now (1 x 4096: 21.4, 18.4; 8 x 1024 with index reuse over four layers: 20.7, 18.3; head-shared 4 x 2048, with a
-// launch of its own for the scores: 26.8, 21.6).
+// 8 heads, 22.8 now (1 x 4096: 21.4, 18.5; 8 x 1024 with index reuse over four layers: 20.7, 18.0; head-shared 4 x 2048, with a
+// launch of its own for the scores: 26.8, 20.4).
 // Same results as append -> index_score (n_q = 1) -> topb_select -> memory_update -> compact_kv
 // -> decode_attn_with_readout whenever every unit enters with len <= budget.
 #pragma once
@@ -165,7 +165,7 @@ __device__ __forceinline__ void dec_gemv2(const bf16_t* __restrict__ A, const bf
 // The terms of the memory readout that do not depend on this step's eviction, for the G query heads
 // of one unit against the memory state as it stands: phi_q = W_theta q, phi_q^T M, sum_c phi_q[c]^2
 // b[c], and the gate sigmoid(w_g . q + c_g).  Workgroup mp of a unit takes rows 32 mp .. 32 mp + 31
-// of the memory (its slice of phi_q, and partial sums over those rows).  The tail kernel applies
+// of the memory (its slice of phi_q, and partial sums over those rows).  k_dec_finish applies
 // the rank-one update of this step to these terms instead of reading the updated state back.
 // LDS of the prep roles (a struct, so that a kernel that also holds split workgroups can overlay it)
 struct DecPrepSmem {
@@ -701,9 +701,11 @@ struct DecFinishSmem {
 
 // grid: (X, ceil(G / HPW), units / X), a workgroup per (unit, group of HPW query heads); X = 8 puts unit u on XCD u % 8, whose L2
 // has seen its partials and readout terms.  Nobody waits for another: what they read of the cache and one of them has to
-// change (the hole, the length) is changed by the last to arrive at a counter, when all have read it.
-// Bound by its chain: length, partials and ranked entries, the evicted rows, the sums (6.0 us at 4 x 2048 entries x 8 heads; the form
-// that staged a record per split took 6.1 behind a launch of 13.6 instead of 11.0).
+// change (the hole, the length) is changed by the last to arrive at a counter, when all have read it.  The counter needs no release and
+// no acquire: every wave waits for its loads and the workgroup for its waves before it counts, so what the counter orders is reads that are
+// over before one writer, and nothing that a workgroup has written is read by another in this launch.
+// Bound by its chain: length, partials and ranked entries, the evicted rows, the sums (5.6 us at 4 x 2048 entries x 8 heads, 5.3 with
+// the logits' digits left to chance; the form that staged a record per split took 6.1 behind a launch of 13.6 instead of 11.3).
 template <int HPW, int DI>
 __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a) {
   __shared__ __attribute__((aligned(16))) DecFinishSmem<HPW, DI> sm;

@@ -359,7 +359,7 @@ class LockStepShared:
         return ref
 
     def event_fused(self, t: int, budget: int, tag: str, check=True):
-        """One decode token through im_decode_step (four launches in this layout)."""
+        """One decode token through im_decode_step (three launches in this layout, too)."""
         w, dev = self.w, self.dev
         d = lambda x: x.to(dev)
         k_new = self.K[:, :, t:t + 1].contiguous(); v_new = self.V[:, :, t:t + 1].contiguous()

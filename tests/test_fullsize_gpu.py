@@ -84,6 +84,6 @@ def test_cfg3_head_shared_full_size_sampled_sequence():
 
 
 def test_cfg3_head_shared_full_size_fused_decode():
-    # configuration 3's own 512 decode steps through the four-launch step of this layout
+    # configuration 3's own 512 decode steps through the three-launch step of this layout
     w = WORKLOADS["cfg3"].shared(n_layers=1, decode_steps=512)
     LockStepShared(w, gen_device="cuda", batch_ids=[1]).run_schedule(fused_decode=True, full_every=32)
