@@ -942,16 +942,38 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
     const int j = g * HPW + jw;
     // the splits' maximum and denominator, the waves' shares, the last live entry, less the evicted one
     float m = m_all, l = l_all, o = 0.f;
-    const int shares = min(n_act, 16);
     const float xl = sm.xl[jw], xe = sm.xe[jw], share_e = sm.mrg[jw][(max(e, 0) / DEC_KEYS) & 15][d];   // (on their way beside the shares)
     float sizes = 0.f;   // of the shares
-#pragma unroll 4
-    for (int i = 0; i < shares; ++i) {
-      const float x = sm.mrg[jw][i][d];
-      o += x;
-      sizes += fabsf(x);
-    }
+    auto shares = [&](auto count) {   // (all reads first: one latency instead of one for every four)
+      float x[count];
+#pragma unroll
+      for (int i = 0; i < count; ++i) x[i] = sm.mrg[jw][i][d];
+#pragma unroll
+      for (int i = 0; i < count; ++i) {
+        const float y = i < n_act ? x[i] : 0.f;   // (the others hold nothing)
+        o += y;
+        sizes += fabsf(y);
+      }
+    };
+    if (n_act > 4) shares(std::integral_constant<int, 16>{});
+    else shares(std::integral_constant<int, 4>{});
     const float ve_last = bf2f(v_last), ve_d = e >= 0 ? bf2f(v_e) : 0.f;
+    // phi_q . phi_e, the readout's denominator, and
+    // phi_q^T (lambda M + eta phi_e v_e^T) = lambda phi_q^T M + eta (phi_q . phi_e) v_e.  (Without a branch around it, and before the
+    // branch below: a chain beside the other)
+    float mr = (rp[0] + rp[1]) + (rp[2] + rp[3]);
+    static_assert(DEC_MP == 4, "four parts of phi_q^T M");
+    const float2 pp = *(const float2*)&sm.phe[2 * lane];
+    const float dt = wave_sum_f(fmaf(dq.x, pp.x, dq.y * pp.y));
+    const float sq = wave_sum_f(fmaf(dq.x * dq.x, pp.x * pp.x, dq.y * dq.y * pp.y * pp.y));
+    float v_sum = ve_d;
+    if constexpr (DI == 16) {
+      v_sum = 0.f;
+      for (int i = 0; i < a.H_kv; ++i) v_sum += sm.vrow[i][d];
+    }
+    dn = e >= 0 ? fmaf(a.lambda, dn, a.eta * sq) : dn;
+    mr = e >= 0 ? fmaf(a.lambda, mr, a.eta * dt * v_sum) : mr;
+    const float res = gate * (mr / (dn + a.mem_eps));
     auto add = [&](float m2, float l2, float o2) {
       const float mn = fmaxf(m, m2), s1 = __expf(m - mn), s2 = __expf(m2 - mn);
       o = fmaf(o, s1, s2 * o2);
@@ -1057,23 +1079,6 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       }
     }
     const float o_attn = (l > 0.f) ? o / l : 0.f;
-    // phi_q . phi_e, the readout's denominator, and
-    // phi_q^T (lambda M + eta phi_e v_e^T) = lambda phi_q^T M + eta (phi_q . phi_e) v_e
-    float mr = (rp[0] + rp[1]) + (rp[2] + rp[3]);
-    static_assert(DEC_MP == 4, "four parts of phi_q^T M");
-    if (e >= 0) {
-      const float2 pp = *(const float2*)&sm.phe[2 * lane];
-      const float dt = wave_sum_f(fmaf(dq.x, pp.x, dq.y * pp.y));
-      const float sq = wave_sum_f(fmaf(dq.x * dq.x, pp.x * pp.x, dq.y * dq.y * pp.y * pp.y));
-      dn = fmaf(a.lambda, dn, a.eta * sq);
-      float v_sum = ve_d;
-      if constexpr (DI == 16) {
-        v_sum = 0.f;
-        for (int i = 0; i < a.H_kv; ++i) v_sum += sm.vrow[i][d];
-      }
-      mr = fmaf(a.lambda, mr, a.eta * dt * v_sum);
-    }
-    const float res = gate * (mr / (dn + a.mem_eps));
     const size_t oi = ((size_t)b * a.H + h * G + j) * IM_D + d;
     a.out[oi] = f2bf_rne(o_attn + res);
     if (a.readout) a.readout[oi] = res;
