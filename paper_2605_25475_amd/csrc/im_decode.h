@@ -985,7 +985,9 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
       if (e >= 0) {
         // The evicted entry is in its split's partial, and its share of the sums has their rounding errors.  They are subtracted
         // where that leaves enough of the sums: 1 / 16 of the denominator (the errors count 16 times: 1e-6 of the output, whose half step is 2e-3),
-        // and in this dim 1 / 256 of the evicted entry's part (by chance or design a dim may have next to nothing else: 2e-5 of it).  What stays
+        // and in this dim 1 / 256 of the evicted entry's part (by chance or design a dim may have next to nothing else: 2e-5 of it), more of it
+        // the further its logit lies below the maximum: an exponent of size D is rounded by 2^-24 D, so the errors grow as 4 + D and the line
+        // goes down with them (D = 25 with 1 / 256: 4e-4 of the dim).  What stays
         // is at least the sum of the sizes of the waves' shares without it.  Else (or with an infinity or NaN in sight) its split is taken again
         // without it, which costs the launch 5 us (13 with a row a lane): with lines of 1 / 2 and 1 / 16 that is every launch where a few keys
         // dominate (16 x 512 entries, one key in 20 four times as long: 891 us a pass, 776 now).
@@ -994,7 +996,7 @@ __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a
         const float stays = fmaf(to_m, sizes - fabsf(share_e), fabsf(fmaf(to_m, share_e, -pv)) + fabsf(__expf(xl - m) * ve_last));
         l -= pe;
         o -= pv;
-        if (__builtin_expect(__any(!(pe <= 0.9375f * l0) || !(fabsf(pv) <= 256.f * stays) || !(stays < 1e37f)), 0)) {
+        if (__builtin_expect(__any(!(pe <= 0.9375f * l0) || !(fabsf(pv) * (4.f + (m - xe)) <= 1024.f * stays) || !(stays < 1e37f)), 0)) {
           // (the hole may be filled meanwhile: its row is not read).  The wave's shares have been read; its half of their rows is scratch now
           const int se = e / DEC_KEYS, k0 = se * DEC_KEYS, nk = min(DEC_KEYS, n - 1 - k0);
           float (*tmp)[IM_D] = (float (*)[IM_D])&sm.mrg[jw][0][64 * (w & 1)];   // [16][64], rows IM_D apart

@@ -118,9 +118,9 @@ def test_evicted_entry_leaves_the_attention_sums(what, n):
             assert int(st.len[b, h]) == n
 
 
-def _without_the_evicted(shared, batch, hq, hkv, n, edit, tag, finite=None):
+def _without_the_evicted(shared, batch, hq, hkv, n, edit, tag, finite=None, eta=1e-24):
     """A follower step that names a slot, against the oracle without that entry.  edit(ls, unit_q, slot) prepares K and V (and
-    returns the size of the largest logit).  The step leaves the entry's value out of the memory's readout (eta = 1e-24).
+    returns the size of the largest logit).  The step leaves the entry's value out of the memory's readout (a tiny eta).
 
     Bar: a logit is an fp32 sum of 128 products, of size L in all: 16 x 2^-24 L covers its rounding in any order (the bound of a random
     walk of 128 roundings is 11), which moves a weight by as much, and the output by that and the other weights' times the largest |V|.
@@ -151,11 +151,11 @@ def _without_the_evicted(shared, batch, hq, hkv, n, edit, tag, finite=None):
         evict = [[np.array([slot]) for _ in range(hkv)] for _ in ids]
         keep = [[np.delete(np.arange(n + 1), slot) for _ in range(hkv)] for _ in ids]
     x_new = dict(x_new=d(ls.X[:, new])) if shared else {}
-    ls.gpu.follow_step(d(ls.K[:, :, new]), d(ls.V[:, :, new]), d(pos[:, n]), d(ls.Q[:, n]), named, w.lam, 1e-24, debug=True, **x_new)
+    ls.gpu.follow_step(d(ls.K[:, :, new]), d(ls.V[:, :, new]), d(pos[:, n]), d(ls.Q[:, n]), named, w.lam, eta, debug=True, **x_new)
     torch.cuda.synchronize()
     assert im.im_query_status(ls.handle) == 0
     with np.errstate(invalid="ignore"):
-        ls.ref.memory_update(evict, w.lam, 1e-24)
+        ls.ref.memory_update(evict, w.lam, eta)
         ls.ref.compact_kv(keep, evict)
         out, _ = ls.ref.decode_attn_with_readout(f64(ls.Q[ids, n]))
     got = f64(ls.gpu.out)[ids].reshape(len(ids), hkv, w.group, w.head_dim)
@@ -207,6 +207,33 @@ def test_evicted_entry_with_a_channel_of_its_own(shared, n, batch, hq, hkv, larg
         ls.V[:, :, 3, 0] = large
         return float((torch.einsum("bhjd,bhkd->bhjk", q, ls.K.float()) * 128 ** -0.5).abs().max())
     _without_the_evicted(shared, batch, hq, hkv, n, edit, f"channel {large}")
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("n,batch,hq,hkv", [(300, *GROUPS[0]), (129, *GROUPS[1])])
+@pytest.mark.parametrize("below,part", [(3, 60), (3, 200), (20, 25), (45, 15), (45, 200)])
+def test_evicted_entry_far_below_the_largest_logit(shared, n, batch, hq, hkv, below, part):
+    """The evicted entry's logit lies about `below` under the others', and its part of 32 dims is `part` times what the others have there.
+    An exponent of size D is rounded by 2^-24 D, a weight by as much, and by about four roundings more: subtracted up to
+    1024 / (4 + D) of the rest, that is at most 1024 x 2^-24 of the dim, and an output of 8 bits (a step is at least 2^-8 of it) is rounded
+    the other way in at most one case in 64."""
+    def edit(ls, q, slot):
+        g = torch.Generator().manual_seed(7)
+        r = torch.randn(q.shape[0], q.shape[1], 128, generator=g)
+        unit = (r * r).sum(-1) * 128 ** -0.5          # the logit of a row r under the query r
+        q[:] = r[:, :, None] + 0.005 * torch.randn(q.shape, generator=g)
+        K = (10 / unit)[..., None, None] * r[:, :, None] + 0.3 * torch.randn(ls.K.shape, generator=g)
+        K[:, :, slot] = ((10 - below) / unit)[..., None] * r
+        ls.K[:] = K.to(torch.bfloat16)
+        ls.V[..., ::4] = ls.V[..., ::4].abs() + 0.5
+        lg = torch.einsum("bhjd,bhkd->bhjk", q.to(torch.bfloat16).double(), ls.K.double()) * 128 ** -0.5
+        lg = lg[..., :n + 1]
+        odds = torch.exp(torch.logsumexp(torch.cat([lg[..., :slot], lg[..., slot + 1:]], -1), -1) - lg[..., slot]).mean(-1)
+        ls.V[:, :, slot, ::4] = (1.3 * part * odds)[..., None].to(torch.bfloat16)   # (the others' mean is 1.3)
+        return float(lg.abs().max())
+    got, out = _without_the_evicted(shared, batch, hq, hkv, n, edit, f"{part} times the rest, {below} below", eta=1e-36)
+    differ = float(np.mean(got[..., ::4] != out[..., ::4]))
+    assert differ <= 1 / 64, differ
 
 
 @pytest.mark.parametrize("shared", [False, True])
