@@ -18,8 +18,8 @@
 // Split and scoring workgroups are different ones, so the decision is not known to a partial: it holds all of its keys, and
 // k_dec_finish takes the evicted one out again.  With the roles as waves of one workgroup that met at a barrier, every split left its
 // last-ranked entry out and wrote it to a record, and the last launch staged all records: 23.9 us a layer-step of 4 x 2048 entries x
-// 8 heads, 22.8 now (1 x 4096: 21.4, 18.5; 8 x 1024 with index reuse over four layers: 20.7, 18.0; head-shared 4 x 2048, with a
-// launch of its own for the scores: 26.8, 20.4).
+// 8 heads, 22.8 now (1 x 4096: 21.4, 18.2; 8 x 1024 with index reuse over four layers: 20.7, 18.0; head-shared 4 x 2048, with a
+// launch of its own for the scores: 26.8, 20.2).
 // Same results as append -> index_score (n_q = 1) -> topb_select -> memory_update -> compact_kv
 // -> decode_attn_with_readout whenever every unit enters with len <= budget.
 #pragma once
@@ -179,7 +179,7 @@ struct DecPrepSmem {
 };
 
 // Workgroups go to the 8 XCDs round-robin by their index.  Everything a unit owns (its memory state,
-// readout terms, split records, appended rows) is touched by several launches per step; with the
+// readout terms, split partials, appended rows) is touched by several launches per step; with the
 // unit's workgroups of every launch on XCD u % 8 those lines are found in that XCD's L2.  For a block
 // range that starts at a multiple of 8 and holds `per` workgroups for each of U units (U a multiple of
 // 8), index r maps to unit (r % 8) + 8 ((r / 8) / per) and item (r / 8) % per; else plain division.
@@ -704,7 +704,7 @@ struct DecFinishSmem {
 // change (the hole, the length) is changed by the last to arrive at a counter, when all have read it.  The counter needs no release and
 // no acquire: every wave waits for its loads and the workgroup for its waves before it counts, so what the counter orders is reads that are
 // over before one writer, and nothing that a workgroup has written is read by another in this launch.
-// Bound by its chain: length, partials and ranked entries, the evicted rows, the sums (5.6 us at 4 x 2048 entries x 8 heads, 5.3 with
+// Bound by its chain: length, partials and ranked entries, the evicted rows, the sums (5.8 us at 4 x 2048 entries x 8 heads, 5.6 with
 // the logits' digits left to chance; the form that staged a record per split took 6.1 behind a launch of 13.6 instead of 11.3).
 template <int HPW, int DI>
 __global__ __launch_bounds__(DEC_FT) void k_dec_finish(DEC_HEAD, const DecArgs a) {
